@@ -265,7 +265,9 @@ __device__ __forceinline__ void singular_chunk(const BlockArgs &a, const Lds &l,
       g.E1i[c] = c == 0, g.E2i[c] = c == 1, g.E1j[c] = -(c == 2), g.E2j[c] = 0, g.n[c] = 0;
     g.scale = 0.0;
   }
-  const Acc<KERNEL> v = ss_pair_lane<KERNEL, LAYER>(g, a.ss, cls, a.kappa);
+  Acc<KERNEL> v;
+  ss_pair_lane<KERNEL, LAYER>(g, a.ss, cls, a.kappa, LAYER == BEM_SLP ? &v : nullptr,
+                              LAYER == BEM_SLP ? nullptr : &v);
   if (have) {
     store_as<KERNEL, MIXED>(a.out, dst, v, a.flags);
     if (mdst >= 0) store_as<KERNEL, MIXED>(a.out, mdst, v, a.flags);
@@ -274,9 +276,9 @@ __device__ __forceinline__ void singular_chunk(const BlockArgs &a, const Lds &l,
 
 // Phase E of the one-pass form (both layers, in FP64): the pair (i, j) of a
 // listed code in both layers and, if the block has a mirror, the transposed
-// pair (j, i): its double layer evaluated as (j, i), its single layer copied
-// (vertex and near-singular pairs: equal up to rounding) or evaluated as
-// (j, i) (edge pairs: that rule is not symmetric).  The class is uniform
+// pair (j, i): an edge pair evaluated as (j, i) (that rule is not symmetric);
+// else its single layer copied and its double layer summed over the same
+// directions (vertex pairs) or evaluated as (j, i) (near-singular pairs).  The class is uniform
 // across the chunk.
 template <int KERNEL, bool MIXED>
 __device__ __forceinline__ void singular_chunk_both(const BlockArgs &a, const Lds &l,
@@ -315,17 +317,17 @@ __device__ __forceinline__ void singular_chunk_both(const BlockArgs &a, const Ld
   if (active)
     have = pair_geometry(a.v, a.tri, a.nv, a.geo, a.ldg, l.rid[rl], l.cid[cl], cls, a.flags, &g);
   if (!have) idle(&g);
-  // a Helmholtz pair with an edge or a vertex in common takes both layers
-  // from one pass over its eta points (uniform branch: the class is the
-  // wave's)
-  const bool fuse = KERNEL == BEM_HELMHOLTZ && cls != CLS_IDENTICAL;
-  Acc<KERNEL> vs, vd;
-  if constexpr (KERNEL == BEM_HELMHOLTZ) {
-    if (fuse) ss_pair_lane_both(g, a.ss, cls, a.kappa, &vs, &vd);
-  }
-  if (!fuse) {
-    vs = ss_pair_lane<KERNEL, BEM_SLP>(g, a.ss, cls, a.kappa);
-    vd = ss_pair_lane<KERNEL, BEM_DLP>(g, a.ss, cls, a.kappa);
+  // a vertex pair's directions serve (j, i) too: its rule is symmetric (the
+  // class and the mirror are uniform across the wave)
+  const bool mirror = h.moff >= 0 && !(h.diag && cls == CLS_IDENTICAL);
+  Acc<KERNEL> vs, vd, md;
+  if (cls == CLS_VERTEX && mirror) {
+    double ni[3] = {0.0, 0.0, 0.0};
+    if (have)
+      for (int c = 0; c < 3; ++c) ni[c] = l.rn[c * a.tr + rl];
+    ss_pair_lane<KERNEL, kSS, true>(g, a.ss, cls, a.kappa, &vs, &vd, &md, ni);
+  } else {
+    ss_pair_lane<KERNEL, kSS>(g, a.ss, cls, a.kappa, &vs, &vd);
   }
   if (have) {
     store_as<KERNEL, MIXED>(a.out, dst, vs, a.flags);
@@ -333,18 +335,14 @@ __device__ __forceinline__ void singular_chunk_both(const BlockArgs &a, const Ld
   }
   // uniform: no mirror, or an identical pair of a diagonal block (its own
   // transpose, already written)
-  if (h.moff < 0 || (h.diag && cls == CLS_IDENTICAL)) return;
-  have = false;
-  if (active)
-    have = pair_geometry(a.v, a.tri, a.nv, a.geo, a.ldg, l.cid[cl], l.rid[rl], cls, a.flags, &g);
-  if (!have) idle(&g);
-  Acc<KERNEL> ms = vs, md;
-  if constexpr (KERNEL == BEM_HELMHOLTZ) {
-    if (cls == CLS_EDGE) ss_pair_lane_both(g, a.ss, cls, a.kappa, &ms, &md);
-  }
-  if (KERNEL != BEM_HELMHOLTZ || cls != CLS_EDGE) {
-    md = ss_pair_lane<KERNEL, BEM_DLP>(g, a.ss, cls, a.kappa);
-    if (cls == CLS_EDGE) ms = ss_pair_lane<KERNEL, BEM_SLP>(g, a.ss, cls, a.kappa);
+  if (!mirror) return;
+  Acc<KERNEL> ms = vs;
+  if (cls == CLS_EDGE) {
+    have = false;
+    if (active)
+      have = pair_geometry(a.v, a.tri, a.nv, a.geo, a.ldg, l.cid[cl], l.rid[rl], cls, a.flags, &g);
+    if (!have) idle(&g);
+    ss_pair_lane<KERNEL, kSS>(g, a.ss, cls, a.kappa, &ms, &md);
   }
   if (have) {
     store_as<KERNEL, MIXED>(a.out, mdst, ms, a.flags);

@@ -104,68 +104,58 @@ int get_rules(bem_ctx *ctx, const bem_op *op, const bem::DevRules **out) {
     return BEM_OK;
   }
   bem::DevRules d;
-  // the tables of a failed build are released (nothing is kept half-built)
-  struct Release {
-    bem::DevRules *d;
-    ~Release() {
-      if (!d) return;
-      for (void *m : {(void *)d->tri, (void *)d->xi, (void *)d->ss[0], (void *)d->ss[1],
-                      (void *)d->ss[2], (void *)d->ss[3]})
-        if (m) (void)hipFree(m);
-    }
-  } release{&d};
   try {
+    std::vector<double> h;  // all tables, each at an even offset
+    auto put = [&](std::initializer_list<const std::vector<double> *> cols) {
+      h.resize((h.size() + 1) & ~size_t(1));
+      const size_t at = h.size();
+      for (const auto *c : cols) h.insert(h.end(), c->begin(), c->end());
+      return at;
+    };
     const bem::TriRule tr = bem::triangle_rule(op->regular_rule, op->q_regular);
     d.nq = (int)tr.s.size();
-    std::vector<double> h;
-    h.insert(h.end(), tr.s.begin(), tr.s.end());
-    h.insert(h.end(), tr.t.begin(), tr.t.end());
-    h.insert(h.end(), tr.w.begin(), tr.w.end());
-    hipError_t e = dev_malloc((void **)&d.tri, h.size() * sizeof(double));
-    if (e != hipSuccess) return hip_fail(ctx, e, "hipMalloc(rule)");
-    e = hipMemcpy(d.tri, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice);
-    if (e != hipSuccess) return hip_fail(ctx, e, "hipMemcpy(rule)");
-    {
-      const bem::XiRule xr = bem::xi_rule(op->q_singular);
-      const int q = op->q_singular;
-      // [xi_a | w_a xi_a^2 | w_a xi_a | M1 = sum w xi, M2 = sum w xi^2]
-      std::vector<double> hx(3 * q + 2, 0.0);
-      double m1 = 0, m2 = 0;
-      for (int k = 0; k < q; ++k) {
-        hx[k] = xr.x[k];
-        hx[q + k] = xr.w3[k] / xr.x[k];
-        hx[2 * q + k] = xr.w3[k] / (xr.x[k] * xr.x[k]);
-        m1 += hx[2 * q + k];
-        m2 += hx[q + k];
-      }
-      hx[3 * q] = m1;
-      hx[3 * q + 1] = m2;
-      d.nxi = q;
-      e = dev_malloc((void **)&d.xi, hx.size() * sizeof(double));
-      if (e != hipSuccess) return hip_fail(ctx, e, "hipMalloc(xi rule)");
-      e = hipMemcpy(d.xi, hx.data(), hx.size() * sizeof(double), hipMemcpyHostToDevice);
-      if (e != hipSuccess) return hip_fail(ctx, e, "hipMemcpy(xi rule)");
-    }
-    for (int cls = 0; cls <= 3; ++cls) {
-      const bem::SSRule r = cls ? bem::ss_rule(cls, op->q_singular)
-                                : bem::ss_rule_identical_symmetric(op->q_singular);
+    const size_t at_tri = put({&tr.s, &tr.t, &tr.w});
+    const bem::XiRule xr = bem::xi_rule(op->q_singular);
+    std::vector<double> w2(xr.x.size());
+    for (size_t k = 0; k < w2.size(); ++k) w2[k] = xr.w3[k] / xr.x[k];
+    d.nxi = op->q_singular;
+    const size_t at_xi = put({&xr.x, &w2});
+    size_t at_ss[4] = {}, at_sing[4] = {};
+    for (int cls = 1; cls <= 3; ++cls) {
+      const bem::SSRule r = bem::ss_rule(cls, op->q_singular);
       d.np[cls] = (int)r.w.size();
-      std::vector<double> hs;
-      for (const auto *vec : {&r.xs, &r.xt, &r.ys, &r.yt, &r.w}) hs.insert(hs.end(), vec->begin(), vec->end());
-      e = dev_malloc((void **)&d.ss[cls], hs.size() * sizeof(double));
-      if (e != hipSuccess) return hip_fail(ctx, e, "hipMalloc(ss rule)");
-      e = hipMemcpy(d.ss[cls], hs.data(), hs.size() * sizeof(double), hipMemcpyHostToDevice);
-      if (e != hipSuccess) return hip_fail(ctx, e, "hipMemcpy(ss rule)");
+      at_ss[cls] = put({&r.xs, &r.xt, &r.ys, &r.yt, &r.w});
+      const bem::SingularRule sr = bem::singular_rule(cls, op->q_singular);
+      d.nd[cls] = (int)sr.w.size();
+      d.nr[cls] = (int)sr.p.size();
+      const std::vector<double> series(&sr.series[0][0], &sr.series[0][0] + 4 * bem::kSeries);
+      at_sing[cls] = put({&series, &sr.g[0], &sr.g[1], &sr.g[2], &sr.g[3], &sr.w, &sr.p, &sr.ws, &sr.wd});
     }
+    hipError_t e = dev_malloc((void **)&d.mem, h.size() * sizeof(double));
+    if (e != hipSuccess) return hip_fail(ctx, e, "hipMalloc(quadrature tables)");
+    e = hipMemcpy(d.mem, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+      (void)hipFree(d.mem);
+      return hip_fail(ctx, e, "hipMemcpy(quadrature tables)");
+    }
+    d.tri = d.mem + at_tri;
+    d.xi = d.mem + at_xi;
+    for (int cls = 1; cls <= 3; ++cls) d.ss[cls] = d.mem + at_ss[cls], d.sing[cls] = d.mem + at_sing[cls];
+    auto ins = ctx->rules.emplace(key, d);
+    *out = &ins.first->second;
   } catch (const std::bad_alloc &) {
+    if (d.mem) (void)hipFree(d.mem);
     return fail(ctx, BEM_ENOMEM, "host allocation failed");
   } catch (const std::exception &ex) {
     return fail(ctx, BEM_EINVAL, ex.what());
   }
-  auto ins = ctx->rules.emplace(key, d);
-  release.d = nullptr;  // kept by the context
-  *out = &ins.first->second;
   return BEM_OK;
+}
+
+SSArgs ss_args(const DevRules &r) {
+  SSArgs s{};
+  for (int c = 1; c <= 3; ++c) s.tab[c] = r.sing[c], s.nd[c] = r.nd[c], s.nr[c] = r.nr[c];
+  return s;
 }
 
 // both: the near field of both layers in one pass (out: single layer, out2:
@@ -238,9 +228,7 @@ int assemble_blocks(bem_ctx *ctx, const bem_mesh *mesh, const bem_op *op,
                              both))
     return fail(ctx, BEM_EUNSUPPORTED, "quadrature order too high for the LDS budget");
   a.near_ratio = op->near_singular_ratio;
-  for (int c = 0; c < 4; ++c) a.ss.eta[c] = rules->ss[c], a.ss.np[c] = rules->np[c];
-  a.ss.xi = rules->xi;
-  a.ss.q = rules->nxi;
+  a.ss = bem::ss_args(*rules);
   a.kappa = op->kernel == BEM_HELMHOLTZ ? op->kappa : 0.0;
   a.flags = ctx->flags;
   e = both ? bem::launch_blocks_both(op->kernel, mixed, a, lds, s)
@@ -291,12 +279,7 @@ void bem_destroy(bem_ctx *ctx) {
     DeviceGuard g(ctx->device);
     (void)hipDeviceSynchronize();
     bem::detach_plans(ctx);
-    for (auto &kv : ctx->rules) {
-      (void)hipFree(kv.second.tri);
-      if (kv.second.xi) (void)hipFree(kv.second.xi);
-      for (int c = 0; c < 4; ++c)
-        if (kv.second.ss[c]) (void)hipFree(kv.second.ss[c]);
-    }
+    for (auto &kv : ctx->rules) (void)hipFree(kv.second.mem);
     if (ctx->geo) (void)hipFree(ctx->geo);
     if (ctx->mlp_scratch) (void)hipFree(ctx->mlp_scratch);
     if (ctx->sel_scratch) (void)hipFree(ctx->sel_scratch);
@@ -497,9 +480,7 @@ int bem_eval_entries(bem_ctx *ctx, const bem_mesh *mesh, const bem_op *op, int64
   a.out = out;
   a.rule = rules->tri;
   a.nq = rules->nq;
-  for (int c = 0; c < 4; ++c) a.ss.eta[c] = rules->ss[c], a.ss.np[c] = rules->np[c];
-  a.ss.xi = rules->xi;
-  a.ss.q = rules->nxi;
+  a.ss = bem::ss_args(*rules);
   a.kappa = op->kernel == BEM_HELMHOLTZ ? op->kappa : 0.0;
   a.flags = ctx->flags;
   e = bem::launch_entries(op->kernel, op->layer, op->precision == BEM_MIXED, a, s);
@@ -631,7 +612,7 @@ int bem_p1_pairs(bem_ctx *ctx, const bem_mesh *mesh, const bem_op *op, int64_t n
   a.out = out;
   a.rule = rules->tri;
   a.nq = rules->nq;
-  for (int c = 0; c < 4; ++c) a.ss.eta[c] = rules->ss[c], a.ss.np[c] = rules->np[c];
+  for (int c = 1; c < 4; ++c) a.ss.eta[c] = rules->ss[c], a.ss.np[c] = rules->np[c];
   a.ss.xi = rules->xi;
   a.ss.q = rules->nxi;
   a.kappa = op->kernel == BEM_HELMHOLTZ ? op->kappa : 0.0;

@@ -5,6 +5,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "bem_internal.h"
 
 namespace bem {
@@ -243,13 +245,16 @@ __device__ __forceinline__ void relabel(int i0, int i1, int i2, int j0, int j1, 
 }
 
 // ---------------------------------------------------------- Sauter-Schwab
-// After relabelling, both affine maps start at a common vertex, so for a rule
-// point (x^, y^) = xi g(eta) the difference is x - y = xi d(eta) with
-//   d = g1 E1_i + g2 E2_i - g3 E1_j - g4 E2_j,   r = xi |d|.
-// With the Jacobian's factor xi^3 the xi sum of the Laplace kernels is a
-// moment of the xi rule:  SLP  sum_a w_a xi_a^2 / |d|,
-//                         DLP  sum_a w_a xi_a <d, n_j> / |d|^3;
-// the Helmholtz kernels keep the xi sum (e^{i kappa xi |d|}).
+// After relabelling, both affine maps start at a common vertex and the rule
+// factors (singular_rule): x - y = p d(eta) with p a product of the rule's
+// radial nodes and
+//   d = g1 E1_i + g2 E2_i - g3 E1_j - g4 E2_j
+// over 2 q^3 directions for a common vertex, 5 q^2 for a common edge (where
+// E1_i = E1_j and g3 = 0) and 3 q for an identical pair (g3 = g4 = 0).  The
+// Laplace kernels' radial sums are moments; the Helmholtz kernels' are power
+// series in theta = kappa |d| whose coefficients hold the rule's own radial
+// nodes (no other quadrature), taken up to theta = 2, where the first term
+// left out is below 1e-17 of the sum; a larger theta sums the radial nodes.
 struct PairGeo {
   double E1i[3], E2i[3], E1j[3], E2j[3], n[3];
   double scale;  // sqrt(g_i) sqrt(g_j) / (4 pi)
@@ -290,74 +295,6 @@ __device__ __forceinline__ bool pair_geometry(const double *v, const int32_t *tr
   return true;
 }
 
-// Adds the contribution of one eta point (map g at xi = 1, eta weight w).
-// Laplace sums are completed by the xi moment in ss_finish.
-template <int KERNEL, int LAYER>
-__device__ __forceinline__ void eta_point(const PairGeo &g, double g1, double g2, double g3,
-                                          double g4, double w, const SSArgs &ss, double kappa,
-                                          double *are, double *aim) {
-  double d[3];
-#pragma unroll
-  for (int c = 0; c < 3; ++c)
-    d[c] = fma(g1, g.E1i[c], fma(g2, g.E2i[c], fma(-g3, g.E1j[c], -g4 * g.E2j[c])));
-  const double rho2 = fma(d[0], d[0], fma(d[1], d[1], d[2] * d[2]));
-  const double z = rsqrt_newton(rho2);  // 1 / |d|
-  if constexpr (KERNEL == BEM_LAPLACE) {
-    if constexpr (LAYER == BEM_SLP) {
-      *are = fma(w, z, *are);
-    } else {
-      const double dn = fma(d[0], g.n[0], fma(d[1], g.n[1], d[2] * g.n[2]));
-      *are = fma(w * dn, z * z * z, *are);
-    }
-  } else {
-    const double rho = rho2 * z;
-    const uniform_ptr X = (uniform_ptr)(ss.xi);
-    const int q = ss.q;
-    double base = w * z;  // SLP: w_a xi_a^2 e^{i k xi rho} / rho
-    if constexpr (LAYER == BEM_DLP)
-      base = w * fma(d[0], g.n[0], fma(d[1], g.n[1], d[2] * g.n[2])) * z * z * z;
-    for (int a = 0; a < q; ++a) {
-      const double xa = X[a];
-      const double kr = kappa * xa * rho;
-      double sn, cs;
-      sincos_cw(kr, &sn, &cs);
-      if constexpr (LAYER == BEM_SLP) {
-        const double c = base * X[q + a];  // w_a xi_a^2
-        *are = fma(c, cs, *are);
-        *aim = fma(c, sn, *aim);
-      } else {  // w_a xi_a e^{i kr} (1 - i kr) <d, n> / |d|^3
-        const double c = base * X[2 * q + a];
-        *are = fma(c, fma(kr, sn, cs), *are);
-        *aim = fma(c, fma(-kr, cs, sn), *aim);
-      }
-    }
-  }
-}
-
-template <int KERNEL, int LAYER>
-__device__ __forceinline__ Acc<KERNEL> ss_finish(const PairGeo &g, const SSArgs &ss, double are,
-                                                 double aim) {
-  Acc<KERNEL> r;
-  if constexpr (KERNEL == BEM_LAPLACE) {
-    const uniform_ptr X = (uniform_ptr)(ss.xi);
-    const double moment = LAYER == BEM_SLP ? X[3 * ss.q + 1] : X[3 * ss.q];
-    r.re = are * moment * g.scale;
-  } else {
-    r.re = are * g.scale;
-    r.im = aim * g.scale;
-  }
-  return r;
-}
-
-// One singular pair per lane; all lanes of the wave share the class, so the
-// eta table is read with wave-uniform (scalar) loads.
-// Table of a class for this kernel: identical pairs of a single layer use
-// the symmetric half-table; for a double layer an identical pair's entry
-// vanishes (on a flat triangle <x - y, n> = 0), so no point is summed.
-template <int LAYER>
-__device__ __forceinline__ int ss_table(int cls) {
-  return cls == CLS_IDENTICAL && LAYER == BEM_SLP ? 0 : cls;
-}
 // Element k of a four-entry argument array by selects, not by an index: a
 // kernel that copies its arguments into registers (the persistent form) would
 // otherwise keep the whole copy in scratch memory.
@@ -365,134 +302,243 @@ template <class T>
 __device__ __forceinline__ T pick4(const T (&v)[4], int k) {
   return k == 0 ? v[0] : k == 1 ? v[1] : k == 2 ? v[2] : v[3];
 }
-template <int LAYER>
-__device__ __forceinline__ int ss_points(const SSArgs &ss, int cls) {
-  return cls == CLS_IDENTICAL && LAYER == BEM_DLP ? 0 : pick4(ss.np, ss_table<LAYER>(cls));
+
+constexpr int kSS = 2;  // layer value of the singular sums: both layers
+
+// Largest squared distance of a point of tau_i from one of tau_j: between two
+// vertices (every direction d of the rule is such a difference).
+__device__ __forceinline__ double pair_extent2(const PairGeo &g) {
+  double m = 0.0;
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      double r2 = 0.0;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const double x = a == 0 ? 0.0 : a == 1 ? g.E1i[c] : g.E1i[c] + g.E2i[c];
+        const double y = b == 0 ? 0.0 : b == 1 ? g.E1j[c] : g.E1j[c] + g.E2j[c];
+        r2 = fma(x - y, x - y, r2);
+      }
+      m = fmax(m, r2);
+    }
+  return m;
 }
 
-template <int KERNEL, int LAYER>
-__device__ __forceinline__ Acc<KERNEL> ss_pair_lane(const PairGeo &g, const SSArgs &ss, int cls,
-                                                    double kappa) {
-  const uniform_ptr T = (uniform_ptr)(pick4(ss.eta, ss_table<LAYER>(cls)));
-  const int n = ss_points<LAYER>(ss, cls);
-  // U eta points per step into U accumulators, written stage by stage so
-  // that the independent chains interleave (the sum order is fixed)
-  constexpr int U = KERNEL == BEM_LAPLACE ? 4 : 2;
-  double are[U], aim[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) are[u] = 0.0, aim[u] = 0.0;
-  int p = 0;
-  if constexpr (KERNEL == BEM_LAPLACE) {
-    for (; p + U <= n; p += U) {
-      double d0[U], d1[U], d2[U], r2[U], h[U], w[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const double g1 = T[p + u], g2 = T[n + p + u], g3 = T[2 * n + p + u], g4 = T[3 * n + p + u];
-        w[u] = T[4 * n + p + u];
-        d0[u] = fma(g1, g.E1i[0], fma(g2, g.E2i[0], fma(-g3, g.E1j[0], -g4 * g.E2j[0])));
-        d1[u] = fma(g1, g.E1i[1], fma(g2, g.E2i[1], fma(-g3, g.E1j[1], -g4 * g.E2j[1])));
-        d2[u] = fma(g1, g.E1i[2], fma(g2, g.E2i[2], fma(-g3, g.E1j[2], -g4 * g.E2j[2])));
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) r2[u] = fma(d0[u], d0[u], fma(d1[u], d1[u], d2[u] * d2[u]));
-#pragma unroll
-      for (int u = 0; u < U; ++u) h[u] = __builtin_amdgcn_rsq(r2[u]);
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        // one Newton step: z = h + h (1 - r2 h^2) / 2 ~ 1 / |d|
-        const double z = fma(0.5 * h[u], fma(-(r2[u] * h[u]), h[u], 1.0), h[u]);
-        if constexpr (LAYER == BEM_SLP) {
-          are[u] = fma(w[u], z, are[u]);
-        } else {
-          const double dn = fma(d0[u], g.n[0], fma(d1[u], g.n[1], d2[u] * g.n[2]));
-          are[u] = fma(w[u] * dn, z * z * z, are[u]);
-        }
-      }
-    }
-  } else {
-    for (; p + U <= n; p += U) {
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        eta_point<KERNEL, LAYER>(g, T[p + u], T[n + p + u], T[2 * n + p + u], T[3 * n + p + u],
-                                 T[4 * n + p + u], ss, kappa, &are[u], &aim[u]);
-    }
-  }
-  for (; p < n; ++p)
-    eta_point<KERNEL, LAYER>(g, T[p], T[n + p], T[2 * n + p], T[3 * n + p], T[4 * n + p], ss,
-                             kappa, &are[0], &aim[0]);
-  double re = are[0], im = aim[0];
-#pragma unroll
-  for (int u = 1; u < U; ++u) re += are[u], im += aim[u];
-  return ss_finish<KERNEL, LAYER>(g, ss, re, im);
-}
+// Sums of a singular pair over directions: single layer, double layer of
+// (i, j), and (with MIRROR) the double layer of (j, i) over the same
+// directions (vertex pairs: the rule is symmetric).
+struct SSSum {
+  double sr = 0.0, si = 0.0, dr = 0.0, di = 0.0, mr = 0.0, mi = 0.0;
+};
 
-// Both layers of one Helmholtz singular pair per lane in one pass over the
-// eta points (edge- and vertex-adjacent pairs, whose single and double
-// layer share the eta table): the difference vector, its length and the
-// sine and cosine of every xi point serve both sums.  Each sum takes the
-// same operands in the same order as ss_pair_lane's for its layer.
-__device__ __forceinline__ void ss_pair_lane_both(const PairGeo &g, const SSArgs &ss, int cls,
-                                                  double kappa, Acc<BEM_HELMHOLTZ> *vs,
-                                                  Acc<BEM_HELMHOLTZ> *vd) {
-  const uniform_ptr T = (uniform_ptr)(pick4(ss.eta, cls));
-  const uniform_ptr X = (uniform_ptr)(ss.xi);
-  const int n = pick4(ss.np, cls), q = ss.q;
-  constexpr int U = 2;
-  double sre[U], sim[U], dre[U], dim[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) sre[u] = sim[u] = dre[u] = dim[u] = 0.0;
-  auto point = [&](int p, int u) {
-    const double g1 = T[p], g2 = T[n + p], g3 = T[2 * n + p], g4 = T[3 * n + p];
-    const double w = T[4 * n + p];
-    double d[3];
+// Direction p of the table; VERTEX: four coefficients.
+template <bool VERTEX, class P>
+__device__ __forceinline__ void ss_direction(const PairGeo &g, P T, int n, int p, double d[3]) {
+  const double g1 = T[p], g2 = T[n + p], g4 = T[3 * n + p];
+  if constexpr (VERTEX) {
+    const double g3 = T[2 * n + p];
 #pragma unroll
     for (int c = 0; c < 3; ++c)
       d[c] = fma(g1, g.E1i[c], fma(g2, g.E2i[c], fma(-g3, g.E1j[c], -g4 * g.E2j[c])));
-    const double rho2 = fma(d[0], d[0], fma(d[1], d[1], d[2] * d[2]));
-    const double z = rsqrt_newton(rho2);  // 1 / |d|
-    const double rho = rho2 * z;
-    const double bs = w * z;
-    const double bd = w * fma(d[0], g.n[0], fma(d[1], g.n[1], d[2] * g.n[2])) * z * z * z;
-    for (int a = 0; a < q; ++a) {
-      const double xa = X[a];
-      const double kr = kappa * xa * rho;
-      double sn, cs;
-      sincos_cw(kr, &sn, &cs);
-      const double c1 = bs * X[q + a];  // w_a xi_a^2
-      sre[u] = fma(c1, cs, sre[u]);
-      sim[u] = fma(c1, sn, sim[u]);
-      const double c2 = bd * X[2 * q + a];  // w_a xi_a
-      dre[u] = fma(c2, fma(kr, sn, cs), dre[u]);
-      dim[u] = fma(c2, fma(-kr, cs, sn), dim[u]);
-    }
-  };
-  int p = 0;
-  for (; p + U <= n; p += U) {
+  } else {
 #pragma unroll
-    for (int u = 0; u < U; ++u) point(p + u, u);
+    for (int c = 0; c < 3; ++c) d[c] = fma(g1, g.E1i[c], fma(g2, g.E2i[c], -g4 * g.E2j[c]));
   }
-  for (; p < n; ++p) point(p, 0);
-  double a0 = sre[0], a1 = sim[0], b0 = dre[0], b1 = dim[0];
-#pragma unroll
-  for (int u = 1; u < U; ++u) a0 += sre[u], a1 += sim[u], b0 += dre[u], b1 += dim[u];
-  *vs = ss_finish<BEM_HELMHOLTZ, BEM_SLP>(g, ss, a0, a1);
-  *vd = ss_finish<BEM_HELMHOLTZ, BEM_DLP>(g, ss, b0, b1);
 }
 
-// One singular pair per wave: lanes stride over the eta points, then a
+// Adds direction d with squared length r2, hardware estimate h of 1/|d| and
+// weight w.  LAYER: BEM_SLP, BEM_DLP or kSS (both).  SER: Helmholtz by the
+// power series, else over the radial nodes.  m: normal of tau_i (MIRROR).
+template <int KERNEL, int LAYER, bool MIRROR, bool SER, class P>
+__device__ __forceinline__ void ss_add(const PairGeo &g, const double d[3], double r2, double h,
+                                       double w, P S, P R, int nr, double kappa, const double *m,
+                                       SSSum *a) {
+  // one Newton step: z = h + h (1 - r2 h^2) / 2 ~ 1 / |d|
+  const double z = fma(0.5 * h, fma(-(r2 * h), h, 1.0), h);
+  double wd = 0.0, wm = 0.0, z3 = 0.0;
+  if constexpr (LAYER != BEM_SLP) {
+    wd = w * fma(d[0], g.n[0], fma(d[1], g.n[1], d[2] * g.n[2]));
+    if constexpr (MIRROR) wm = -w * fma(d[0], m[0], fma(d[1], m[1], d[2] * m[2]));
+    z3 = z * z * z;
+  }
+  if constexpr (KERNEL == BEM_LAPLACE) {
+    if constexpr (LAYER != BEM_DLP) a->sr = fma(w, z, a->sr);
+    if constexpr (LAYER != BEM_SLP) a->dr = fma(wd, z3, a->dr);
+    if constexpr (MIRROR) a->mr = fma(wm, z3, a->mr);
+  } else if constexpr (SER) {
+    // even and odd series in t = theta^2; the odd ones lack a factor theta
+    // (single layer) resp. theta^3 (double layer: no linear term), put back
+    // by ss_finish as kappa and kappa^3 with the powers of 1 / |d|
+    const double t = kappa * kappa * r2;
+    constexpr int N = kSeries;
+    if constexpr (LAYER != BEM_DLP) {
+      double e = S[N - 1], o = S[2 * N - 1];
+#pragma unroll
+      for (int k = N - 2; k >= 0; --k) e = fma(e, t, S[k]), o = fma(o, t, S[N + k]);
+      a->sr = fma(w * z, e, a->sr);
+      a->si = fma(w, o, a->si);
+    }
+    if constexpr (LAYER != BEM_SLP) {
+      double e = S[3 * N - 1], o = S[4 * N - 1];
+#pragma unroll
+      for (int k = N - 2; k >= 0; --k) e = fma(e, t, S[2 * N + k]);
+#pragma unroll
+      for (int k = N - 2; k >= 1; --k) o = fma(o, t, S[3 * N + k]);
+      const double ez = z3 * e;
+      a->dr = fma(wd, ez, a->dr);
+      a->di = fma(wd, o, a->di);
+      if constexpr (MIRROR) a->mr = fma(wm, ez, a->mr), a->mi = fma(wm, o, a->mi);
+    }
+  } else {
+    const double kr = kappa * r2 * z, wz = w * z, wd3 = wd * z3, wm3 = wm * z3;
+    for (int k = 0; k < nr; ++k) {
+      const double t = kr * R[k];
+      double sn, cs;
+      sincos_cw(t, &sn, &cs);
+      if constexpr (LAYER != BEM_DLP) {
+        const double c = wz * R[nr + k];
+        a->sr = fma(c, cs, a->sr);
+        a->si = fma(c, sn, a->si);
+      }
+      if constexpr (LAYER != BEM_SLP) {  // e^{i t} (1 - i t)
+        const double v = R[2 * nr + k], fr = v * fma(t, sn, cs), fi = v * fma(-t, cs, sn);
+        a->dr = fma(wd3, fr, a->dr);
+        a->di = fma(wd3, fi, a->di);
+        if constexpr (MIRROR) a->mr = fma(wm3, fr, a->mr), a->mi = fma(wm3, fi, a->mi);
+      }
+    }
+  }
+}
+
+// Laplace: the radial moments; Helmholtz: the powers of kappa the series left.
+template <int KERNEL, bool SER, class P>
+__device__ __forceinline__ void ss_finish(const PairGeo &g, P S, double kappa, const SSSum &a,
+                                          Acc<KERNEL> *vs, Acc<KERNEL> *vd, Acc<KERNEL> *vm) {
+  if constexpr (KERNEL == BEM_LAPLACE) {
+    vs->re = a.sr * S[0] * g.scale;
+    vd->re = a.dr * S[2 * kSeries] * g.scale;
+    vm->re = a.mr * S[2 * kSeries] * g.scale;
+  } else {
+    const double ks = SER ? kappa * g.scale : g.scale;
+    const double kd = SER ? kappa * kappa * kappa * g.scale : g.scale;
+    vs->re = a.sr * g.scale;
+    vs->im = a.si * ks;
+    vd->re = a.dr * g.scale;
+    vd->im = a.di * kd;
+    vm->re = a.mr * g.scale;
+    vm->im = a.mi * kd;
+  }
+}
+
+// One singular pair per lane over the directions [first, n) in steps of
+// stride (P: a wave-uniform pointer when every lane takes all directions).
+// U directions per step into U accumulators, written stage by stage so that
+// the independent chains interleave; the sum order is fixed.
+template <int KERNEL, int LAYER, bool MIRROR, bool VERTEX, bool SER, int U, class P>
+__device__ __forceinline__ SSSum ss_sum(const PairGeo &g, P S, int n, int nr, double kappa,
+                                        const double *m, int first, int stride) {
+  const P T = S + 4 * kSeries, R = T + 5 * n;
+  SSSum acc[U];
+  int p = first;
+  for (; p + (U - 1) * stride < n; p += U * stride) {
+    double d[U][3], r2[U], h[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      ss_direction<VERTEX>(g, T, n, p + u * stride, d[u]);
+      r2[u] = fma(d[u][0], d[u][0], fma(d[u][1], d[u][1], d[u][2] * d[u][2]));
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) h[u] = __builtin_amdgcn_rsq(r2[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      ss_add<KERNEL, LAYER, MIRROR, SER>(g, d[u], r2[u], h[u], T[4 * n + p + u * stride], S, R, nr,
+                                         kappa, m, &acc[u]);
+  }
+  for (; p < n; p += stride) {
+    double d[3];
+    ss_direction<VERTEX>(g, T, n, p, d);
+    const double r2 = fma(d[0], d[0], fma(d[1], d[1], d[2] * d[2]));
+    ss_add<KERNEL, LAYER, MIRROR, SER>(g, d, r2, __builtin_amdgcn_rsq(r2), T[4 * n + p], S, R, nr,
+                                       kappa, m, &acc[0]);
+  }
+#pragma unroll
+  for (int u = 1; u < U; ++u) {
+    acc[0].sr += acc[u].sr, acc[0].si += acc[u].si;
+    acc[0].dr += acc[u].dr, acc[0].di += acc[u].di;
+    acc[0].mr += acc[u].mr, acc[0].mi += acc[u].mi;
+  }
+  return acc[0];
+}
+
+// One singular pair per lane; all lanes of the wave share the class, so the
+// tables are read with wave-uniform (scalar) loads.  LAYER = kSS: both layers
+// (vs, vd), with MIRROR (vertex pairs) the double layer of (j, i) too (vm;
+// ni: normal of tau_i).  Every sum takes the same operands in the same order
+// whichever layers are asked for.  Bound by FP64 issue and, for the few pairs
+// of a sub-tile, by the length of this one chain: about 30 (Laplace) to 70
+// (Helmholtz, both layers) instructions per direction.  Against the sums over
+// all q^3 eta points (q radial nodes each for Helmholtz, sine and cosine at
+// each) the one-pass near field takes 0.79 -> 0.69 ms (8192 triangles,
+// Laplace, q = 4) and 24.9 -> 22.3 ms (32768, Helmholtz, kappa = 4, q = 5).
+template <int KERNEL, int LAYER, bool MIRROR = false>
+__device__ __forceinline__ void ss_pair_lane(const PairGeo &g, const SSArgs &ss, int cls,
+                                             double kappa, Acc<KERNEL> *vs, Acc<KERNEL> *vd,
+                                             Acc<KERNEL> *vm = nullptr, const double *ni = nullptr) {
+  constexpr int U = KERNEL == BEM_LAPLACE ? 4 : 2;
+  const uniform_ptr S = (uniform_ptr)(pick4(ss.tab, cls));
+  int n = pick4(ss.nd, cls);
+  const int nr = pick4(ss.nr, cls);
+  if (LAYER == BEM_DLP && cls == CLS_IDENTICAL) n = 0;  // <x - y, n> = 0 on one flat triangle
+  Acc<KERNEL> none;
+  const bool ser = KERNEL == BEM_LAPLACE || kappa * kappa * pair_extent2(g) <= 4.0;
+  auto pass = [&](auto use_series) {
+    constexpr bool SER = decltype(use_series)::value;
+    SSSum a;
+    if (cls == CLS_VERTEX) {
+      a = ss_sum<KERNEL, LAYER, MIRROR, true, SER, U>(g, S, n, nr, kappa, ni, 0, 1);
+    } else if (LAYER == kSS && cls == CLS_IDENTICAL) {
+      a = ss_sum<KERNEL, BEM_SLP, false, false, SER, U>(g, S, n, nr, kappa, ni, 0, 1);
+    } else {
+      a = ss_sum<KERNEL, LAYER, false, false, SER, U>(g, S, n, nr, kappa, ni, 0, 1);
+    }
+    ss_finish<KERNEL, SER>(g, S, kappa, a, vs ? vs : &none, vd ? vd : &none, vm ? vm : &none);
+  };
+  if (ser) pass(std::true_type{});
+  if constexpr (KERNEL == BEM_HELMHOLTZ) {
+    if (!ser) pass(std::false_type{});
+  }
+}
+
+// One singular pair per wave: lanes stride over the directions, then a
 // butterfly sum.  Every lane returns the entry.
 template <int KERNEL, int LAYER>
 __device__ Acc<KERNEL> ss_pair_wave(const PairGeo &g, const SSArgs &ss, int cls, double kappa) {
   const int lane = threadIdx.x & (kWave - 1);
-  const double *T = pick4(ss.eta, ss_table<LAYER>(cls));
-  const int n = ss_points<LAYER>(ss, cls);
-  double are = 0.0, aim = 0.0;
-  for (int p = lane; p < n; p += kWave)
-    eta_point<KERNEL, LAYER>(g, T[p], T[n + p], T[2 * n + p], T[3 * n + p], T[4 * n + p], ss,
-                             kappa, &are, &aim);
-  are = wave_sum(are);
-  if constexpr (KERNEL == BEM_HELMHOLTZ) aim = wave_sum(aim);
-  return ss_finish<KERNEL, LAYER>(g, ss, are, aim);
+  const double *S = pick4(ss.tab, cls);
+  int n = pick4(ss.nd, cls);
+  const int nr = pick4(ss.nr, cls);
+  if (LAYER == BEM_DLP && cls == CLS_IDENTICAL) n = 0;
+  Acc<KERNEL> vs, vd, vm;
+  auto pass = [&](auto use_series) {
+    constexpr bool SER = decltype(use_series)::value;
+    SSSum a = cls == CLS_VERTEX
+                  ? ss_sum<KERNEL, LAYER, false, true, SER, 1>(g, S, n, nr, kappa, nullptr, lane, kWave)
+                  : ss_sum<KERNEL, LAYER, false, false, SER, 1>(g, S, n, nr, kappa, nullptr, lane, kWave);
+    if constexpr (LAYER == BEM_SLP) a.sr = wave_sum(a.sr);
+    else a.dr = wave_sum(a.dr);
+    if constexpr (KERNEL == BEM_HELMHOLTZ) {
+      if constexpr (LAYER == BEM_SLP) a.si = wave_sum(a.si);
+      else a.di = wave_sum(a.di);
+    }
+    ss_finish<KERNEL, SER>(g, S, kappa, a, &vs, &vd, &vm);
+  };
+  const bool ser = KERNEL == BEM_LAPLACE || kappa * kappa * pair_extent2(g) <= 4.0;  // uniform
+  if (ser) pass(std::true_type{});
+  if constexpr (KERNEL == BEM_HELMHOLTZ) {
+    if (!ser) pass(std::false_type{});
+  }
+  return LAYER == BEM_SLP ? vs : vd;
 }
 
 }  // namespace dev

@@ -38,8 +38,19 @@ struct XiRule {
 };
 enum { CLS_DISJOINT = 0, CLS_VERTEX = 1, CLS_EDGE = 2, CLS_IDENTICAL = 3 };
 SSRule ss_rule(int cls, int q);
-SSRule ss_rule_identical_symmetric(int q);  // 3 of the 6 identical regions, weights doubled
 XiRule xi_rule(int q);
+
+// Sauter-Schwab rule of one class for piecewise-constant entries, factored
+// into directions d = g1 E1_i + g2 E2_i - g3 E1_j - g4 E2_j with weight w and
+// radial nodes p (x - y = p d) with weights ws (single layer) and wd (double
+// layer); series: see singular_rule.
+constexpr int kSeries = 12;  // coefficients per power series
+struct SingularRule {
+  std::vector<double> g[4], w;
+  std::vector<double> p, ws, wd;
+  double series[4][kSeries];  // single layer even, odd; double layer even, odd
+};
+SingularRule singular_rule(int cls, int q);
 
 // --------------------------------------------------------------- geometry
 // Per-triangle geometry, structure of arrays: geo[f * ldg + i].
@@ -59,26 +70,39 @@ enum GeoField {
 // holds (mirrored edge-adjacent pairs of edges shared by many triangles)
 enum : unsigned { FLAG_EINVAL = 1u, FLAG_NONFINITE = 2u, FLAG_LIST = 4u };
 
-// Device copies of the quadrature tables of one (rule, q_regular, q_singular).
+// Device copies of the quadrature tables of one (rule, q_regular, q_singular),
+// in one allocation.
 struct DevRules {
-  int nq = 0;         // points per triangle (regular rule)
-  double *tri = nullptr;  // [3][nq]: s, t, w
-  // Sauter-Schwab eta tables per class (index = class 1..3); index 0 (no
-  // disjoint table is needed) holds the identical-pair table for kernels
-  // symmetric in x and y (ss_rule_identical_symmetric)
+  double *mem = nullptr;
+  int nq = 0;                   // points per triangle (regular rule)
+  const double *tri = nullptr;  // [3][nq]: s, t, w
+  // Sauter-Schwab eta tables per class 1..3 (piecewise-linear bases)
   int np[4] = {0, 0, 0, 0};
-  double *ss[4] = {nullptr, nullptr, nullptr, nullptr};  // [5][np]: xs, xt, ys, yt, w
-  int nxi = 0;               // Sauter-Schwab order q
-  double *xi = nullptr;      // [3q + 2]: xi, w xi^2, w xi, then M1 = sum w xi, M2 = sum w xi^2
+  const double *ss[4] = {nullptr, nullptr, nullptr, nullptr};  // [5][np]: xs, xt, ys, yt, w
+  int nxi = 0;                  // Sauter-Schwab order q
+  const double *xi = nullptr;   // [2][q]: xi, w xi^2
+  // factored singular rules per class 1..3 (piecewise-constant entries):
+  // series [4][kSeries], then directions [5][nd]: g1 .. g4, w, then radial
+  // nodes [3][nr]: p, ws, wd
+  int nd[4] = {0, 0, 0, 0}, nr[4] = {0, 0, 0, 0};
+  const double *sing[4] = {nullptr, nullptr, nullptr, nullptr};
 };
 
-// Device Sauter-Schwab tables as seen by the kernels.
+// Device Sauter-Schwab tables as seen by the kernels of piecewise-constant
+// entries (DevRules::sing).
 struct SSArgs {
-  const double *eta[4];  // per class [5][np]; [0]: identical pairs, symmetric kernels
+  const double *tab[4];
+  int32_t nd[4], nr[4];
+};
+
+// Tables of the piecewise-linear kernels (DevRules::ss, xi).
+struct P1Rules {
+  const double *eta[4];  // per class [5][np]
   int32_t np[4];
-  const double *xi;      // [4][q]
+  const double *xi;      // [2][q]
   int32_t q;
 };
+SSArgs ss_args(const DevRules &r);
 
 // Arguments of the block kernels (passed by value).
 struct BlockArgs {
@@ -218,7 +242,7 @@ struct P1Args {
   void *out;  // [n][9] entries
   const double *rule;
   int32_t nq;
-  SSArgs ss;
+  P1Rules ss;
   double kappa;
   unsigned *flags;
 };

@@ -294,9 +294,7 @@ int bem_assemble_nearfield_learned(bem_ctx *ctx, const bem_mesh *mesh, const bem
   size_t lds;
   if (!block_tile_shape(a.nq_pad, false, ctx->lds_budget, &a.tr, &a.tc, &lds))
     return fail(ctx, BEM_EUNSUPPORTED, "quadrature order too high for the LDS budget");
-  for (int c = 0; c < 4; ++c) a.ss.eta[c] = plain->ss[c], a.ss.np[c] = plain->np[c];
-  a.ss.xi = plain->xi;
-  a.ss.q = plain->nxi;
+  a.ss = ss_args(*plain);
   a.kappa = op->kernel == BEM_HELMHOLTZ ? op->kappa : 0.0;
   a.flags = ctx->flags;
   e = launch_blocks_learned(op->kernel, op->layer, a, o, lds, s);

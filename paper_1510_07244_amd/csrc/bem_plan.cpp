@@ -549,9 +549,7 @@ int bem_plan_batched(bem_ctx *ctx, const bem_op *op, int32_t nbatch, const bem_b
       a.nq_pad = (rules->nq + c.xc - 1) / c.xc * c.xc;
       a.tr = sh[k].first;
       a.tc = sh[k].second;
-      for (int q = 0; q < 4; ++q) a.ss.eta[q] = rules->ss[q], a.ss.np[q] = rules->np[q];
-      a.ss.xi = rules->xi;
-      a.ss.q = rules->nxi;
+      a.ss = ss_args(*rules);
       a.kappa = op->kernel == BEM_HELMHOLTZ ? op->kappa : 0.0;
       a.near_ratio = op->near_singular_ratio;
       a.flags = ctx->flags;

@@ -186,22 +186,104 @@ SSRule ss_rule(int cls, int q) {
   return r;
 }
 
-// Identical pairs with a kernel symmetric in x and y (single layers): the odd
-// regions are the mirror images (x^ <-> y^) of the even ones on the same
-// triangle, so their sums are equal and the even regions with doubled
-// weights give the same rule.
-SSRule ss_rule_identical_symmetric(int q) {
-  const SSRule full = ss_rule(CLS_IDENTICAL, q);
-  const size_t per = (size_t)q * q * q;
-  SSRule r;
-  for (int reg = 0; reg < 6; reg += 2)
-    for (size_t k = reg * per; k < (reg + 1) * per; ++k) {
-      r.xs.push_back(full.xs[k]);
-      r.xt.push_back(full.xt[k]);
-      r.ys.push_back(full.ys[k]);
-      r.yt.push_back(full.yt[k]);
-      r.w.push_back(2.0 * full.w[k]);
+// Singular rule of the piecewise-constant entries.  On a common edge or
+// triangle the difference of the two points is proportional to xi h1 (edge)
+// or xi h1 h2 (identical) as well: with p that product,
+//   x - y = p (g1 E1_i + g2 E2_i - g3 E1_j - g4 E2_j) = p d,
+// so that 1/|x - y| and <x - y, n> / |x - y|^3 factor into a power of p and a
+// function of d alone.  The q^4 points per region then split into few
+// directions d (2 q^3 for a vertex, 5 q^2 for an edge, 3 q for an identical
+// pair) and one set of radial nodes p for all of them -- the same rule, summed
+// in another order.  Differences are written without cancellation: with a
+// common edge or triangle E1_j = E1_i and g1 is the coefficient of their
+// difference.  Identical pairs serve the single layer only (the double layer
+// vanishes): the regions with x^ and y^ exchanged add the same sums again, so
+// three regions carry twice their weight.
+SingularRule singular_rule(int cls, int q) {
+  if (q < 1 || q > BEM_MAX_ORDER) throw std::invalid_argument("order");
+  std::vector<double> x(q), w(q);
+  gauss_legendre01(q, x.data(), w.data());
+  SingularRule r;
+  auto dir = [&](double g1, double g2, double g3, double g4, double wt) {
+    const double g[4] = {g1, g2, g3, g4};
+    for (int k = 0; k < 4; ++k) r.g[k].push_back(g[k]);
+    r.w.push_back(wt);
+  };
+  // the radial weights: Jacobian times |x - y|^-1 (single layer) resp. times
+  // <x - y, n> / |x - y|^3 ~ p^-2 (double layer), in powers of p's factors
+  auto radial = [&](double p, double ws, double wd) {
+    r.p.push_back(p);
+    r.ws.push_back(ws);
+    r.wd.push_back(wd);
+  };
+  switch (cls) {
+    case CLS_VERTEX:  // J = xi^3 h2
+      for (int a = 0; a < q; ++a)
+        for (int b = 0; b < q; ++b)
+          for (int c = 0; c < q; ++c) dir(1.0, x[a], x[b], x[b] * x[c], w[a] * w[b] * w[c] * x[b]);
+      for (int a = 0; a < q; ++a)
+        for (int b = 0; b < q; ++b)
+          for (int c = 0; c < q; ++c) dir(x[b], x[b] * x[c], 1.0, x[a], w[a] * w[b] * w[c] * x[b]);
+      for (int a = 0; a < q; ++a) radial(x[a], w[a] * x[a] * x[a], w[a] * x[a]);
+      break;
+    case CLS_EDGE:  // J = xi^3 h1^2 in the first region, xi^3 h1^2 h2 in the others; p = xi h1
+      for (int reg = 0; reg < 5; ++reg)
+        for (int b = 0; b < q; ++b)
+          for (int c = 0; c < q; ++c) {
+            const double u = x[b], v = x[c], wt = w[b] * w[c];
+            switch (reg) {
+              case 0: dir(u, v, 0.0, 1.0 - u, wt); break;
+              case 1: dir(u * v, 1.0, 0.0, u * (1.0 - v), wt * u); break;
+              case 2: dir(-u, 1.0 - u, 0.0, u * v, wt * u); break;
+              case 3: dir(-u * v, u * (1.0 - v), 0.0, 1.0, wt * u); break;
+              default: dir(-u * v, 1.0 - u * v, 0.0, u, wt * u); break;
+            }
+          }
+      // xi_a h_b = xi_b h_a: one node for both
+      for (int a = 0; a < q; ++a)
+        for (int b = a; b < q; ++b) {
+          double ws = w[a] * w[b] * x[a] * x[a] * x[b], wd = w[a] * w[b] * x[a];
+          if (b != a) ws += w[a] * w[b] * x[b] * x[b] * x[a], wd += w[a] * w[b] * x[b];
+          radial(x[a] * x[b], ws, wd);
+        }
+      break;
+    case CLS_IDENTICAL:  // J = xi^3 h1^2 h2; p = xi h1 h2
+      for (int a = 0; a < q; ++a) dir(x[a], 1.0, 0.0, 0.0, 2.0 * w[a]);
+      for (int a = 0; a < q; ++a) dir(1.0, x[a], 0.0, 0.0, 2.0 * w[a]);
+      for (int a = 0; a < q; ++a) dir(-x[a], 1.0 - x[a], 0.0, 0.0, 2.0 * w[a]);
+      for (int a = 0; a < q; ++a)
+        for (int b = a; b < q; ++b)
+          for (int c = b; c < q; ++c) {
+            // xi^2 h1 of every distinct order of the three nodes
+            const double t[3] = {x[a], x[b], x[c]};
+            double ws = 0.0;
+            int orders = 0;
+            for (int i = 0; i < 3; ++i)
+              for (int j = 0; j < 3; ++j)
+                if (i != j) ws += t[i] * t[i] * t[j], ++orders;
+            const int distinct = a == b && b == c ? 1 : a == b || b == c ? 3 : 6;
+            radial(t[0] * t[1] * t[2], ws * distinct / orders * w[a] * w[b] * w[c], 0.0);
+          }
+      break;
+    default: throw std::invalid_argument("class");
+  }
+  // Helmholtz: sum_p ws e^{i p t} and sum_p wd (1 - i p t) e^{i p t} as power
+  // series in t = kappa |d|, split into even and odd powers of t (the
+  // coefficient of (i t)^k is mu_k / k!, resp. nu_k (1 - k) / k!); the first
+  // even coefficients are the Laplace moments
+  double fact = 1.0;
+  for (int k = 0; k < 2 * kSeries; ++k) {
+    if (k) fact *= k;
+    double mu = 0.0, nu = 0.0;
+    for (size_t i = 0; i < r.p.size(); ++i) {
+      const double pk = std::pow(r.p[i], k);
+      mu += r.ws[i] * pk;
+      nu += r.wd[i] * pk;
     }
+    const double sgn = (k / 2) % 2 ? -1.0 : 1.0;
+    r.series[k % 2][k / 2] = sgn * mu / fact;
+    r.series[2 + k % 2][k / 2] = sgn * nu * (1 - k) / fact;
+  }
   return r;
 }
 
