@@ -239,7 +239,7 @@ int bem_eval_entries(bem_ctx *ctx, const bem_mesh *mesh, const bem_op *op, int64
  * bem_plan_batched and captured in a HIP graph (a counter-reset kernel,
  * the geometry kernels and the persistent kernel); bem_run_batched replays
  * it.  Entries are bitwise equal to those of bem_assemble_nearfield /
- * bem_assemble_coupling when the x-point chunk equals theirs (the default).
+ * bem_assemble_coupling.
  * --------------------------------------------------------------------- */
 
 typedef struct bem_plan bem_plan;
@@ -277,8 +277,9 @@ typedef struct {
                         bem_assemble_coupling's sub-tile (default: the
                         per-block kernel's) */
   int32_t tile_cols; /* sub-tile columns, 1..64, of the same lists */
-  int32_t x_chunk;   /* regular-rule points per register chunk: 4, 5, 7, 8 or 9
-                        (default: the per-block kernel's) */
+  int32_t x_chunk;   /* 4, 5, 7, 8 or 9, or 0: reported back (0: a divisor of
+                        the rule's points); the kernels choose their register
+                        chunks by the rule alone, entries do not depend on it */
   int32_t autotune;  /* 1: time the candidates of every field left 0 */
   int32_t granularity; /* work item of the queue: 1 whole blocks (each
                           popped block's sub-tiles in turn, like the

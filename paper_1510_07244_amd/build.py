@@ -14,7 +14,12 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libbem.so")
 ARCH = os.environ.get("BEM_OFFLOAD_ARCH", "gfx950")
 
-SOURCES = ["bem_blocks.hip", "bem_kernels.hip", "bem_bases.hip", "bem_mlp.hip", "bem_peak.hip",
+# the slowest to compile first
+SOURCES = ["bem_persistent_helmholtz.hip", "bem_blocks_helmholtz.hip",
+           "bem_persistent_helmholtz_mixed.hip", "bem_blocks_helmholtz_mixed.hip",
+           "bem_persistent_laplace.hip", "bem_blocks_laplace.hip", "bem_learned_helmholtz.hip",
+           "bem_persistent_laplace_mixed.hip", "bem_blocks_laplace_mixed.hip",
+           "bem_learned_laplace.hip", "bem_blocks.hip", "bem_kernels.hip", "bem_bases.hip", "bem_mlp.hip", "bem_peak.hip",
            "bem_h2mv.hip", "bem_p1.hip",
            "bem_quadrature.cpp", "bem_capi.cpp", "bem_plan.cpp", "bem_learned.cpp",
            "bem_h2_tree.cpp", "bem_h2_host.cpp"]

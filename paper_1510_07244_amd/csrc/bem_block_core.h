@@ -1,6 +1,6 @@
 // Building blocks of the block assembly kernels (gfx950, wave64): LDS layout
-// of a sub-tile and the per-entry regular sums in FP64 and in FP32.  Shared by
-// the per-block kernel and the persistent batched kernel (bem_blocks.hip).
+// of a sub-tile and the sums of one regular entry, in FP64 and in FP32.
+// Shared by the per-block, persistent and learned kernels.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -19,21 +19,35 @@ constexpr int kNearSingular = 0;     // list class of near-singular regular pair
 constexpr int kSortPad = 512;        // room for the padding of up to 8 groups
 constexpr int kBoth = 2;             // layer template value: single and double layer in one pass
 
+// Row geometry in coordinates doubled and relative to the block's origin c,
+// so that 1/r = h (3 - s h^2) with s = 4 r^2 and h ~ 1 / (2r).  A point of
+// the triangle is x = V + (s/2) A + (e/2) B with s = xi, e = xi (eta - 1/2)
+// in Duffy coordinates (xi, eta); with D = V - y
+//   4 |x - y|^2 = |D|^2 + s <D, A> + e <D, B> + s^2 k0 + s e c1 + e^2 a22.
+enum RowField {
+  R_V,             // 2 (v0 - c)
+  R_A = 3,         // 2 (2 e1 + e2)
+  R_B = 6,         // 4 e2
+  R_SG = 9,        // sqrt(g_i)
+  R_C1, R_K0, R_A22,  // <A, B> / 2, |A|^2 / 4, |B|^2 / 4
+  ROW_NF
+};
+
 // LDS layout of one sub-tile (up to TR rows x TC columns; triangle rule of nq
-// points padded to nqp with zero weights):
-//   ys[nqp][TC]    column points.  Plain: 6 doubles (-2Y0, -2Y1, -2Y2, |Y|^2,
-//                  w sqrt(g_j), <Y, n_j>) with Y = 2 (y - c) in block-local
-//                  coordinates.  Mixed: 8 floats (Y0, Y1, Y2, w sqrt(g_j),
-//                  <Y, n_j>, pad) with Y = 2 (y - v0_j) local to the column
-//                  triangle.  Read as 16-byte words (broadcast in a wave).
-//   rg[10][TR]     row geometry 2 (v0 - c), 2 e1, 2 e2, sqrt(g_i)
+// points, padded to nqp with zero weights by the general rules):
+//   ys[nqp][TC]    column points (Y, w sqrt(g_j)): four doubles, Y = 2 (y - c);
+//                  mixed: four floats, Y = 2 (y - v0_j) local to the triangle.
+//                  Read as 16-byte words (broadcast in a wave).
+//   rg[ROW_NF][TR] row geometry
 //   rule[3][nqp]   s, t, w of the triangle rule
-//   cn[3][TC]      column normals
+//   cn[4][TC]      column normals n_j, <Y, n_j> (one value on the triangle's
+//                  plane; mixed: unused)
+//   cc[3][TC]      column centroids, doubled (Helmholtz phases)
 //   both layers:   rn[3][TR] row normals
 //   mixed only:    cg[3][TC] = 2 (v0_j - c); rb[6][TR], cb[6][TC] boxes
-//   ints           rid[TR], rv[3][TR], cid[TC], cv[3][TC], count, bad,
-//                  rcount, pad, per-group counts[16] and cursors[16]
-//                  (classes at 0 .. 3, orders q at 8 + q)
+//   ints           rid[TR], rv[3][TR], rs[TR], cid[TC], cv[3][TC], cs[TC] (rs, cs: short phases),
+//                  count, bad, rcount, pad, per-group counts[16] and
+//                  cursors[16] (classes at 0 .. 3, orders q at 8 + q)
 //   list[TR*TC]    uint16 codes (row | col << 6 | group << 12, kSwapped) of the pairs
 //                  left to the FP64 pass (singular; near-singular if mixed),
 //                  from the front; with per-entry orders, the regular pairs
@@ -41,30 +55,33 @@ constexpr int kBoth = 2;             // layer template value: single and double 
 //   sorted[TR*TC + kSortPad]  codes grouped (by class or by order), each
 //                  group padded to a multiple of 64 with kNoPair
 struct Lds {
-  double *ys, *rg, *rule, *cn, *rn, *cg, *rb, *cb;
-  int *rid, *rv, *cid, *cv, *count, *bad, *rcount, *ccount, *cursor;
+  double *ys, *rg, *rule, *cn, *cc, *rn, *cg, *rb, *cb;
+  int *rid, *rv, *rs, *cid, *cv, *cs, *count, *bad, *rcount, *ccount, *cursor;
   uint16_t *list, *sorted;
 };
 
-__host__ __device__ __forceinline__ int ypoint_doubles(bool mixed) { return mixed ? 4 : 6; }
+__host__ __device__ __forceinline__ int ypoint_doubles(bool mixed) { return mixed ? 2 : 4; }
 
 template <bool MIXED>
 __device__ __forceinline__ Lds carve(double *base, int nqp, int TR, int TC, bool both = false) {
   Lds l;
   l.ys = base;
   l.rg = l.ys + ypoint_doubles(MIXED) * nqp * TC;
-  l.rule = l.rg + 10 * TR;
+  l.rule = l.rg + ROW_NF * TR;
   l.cn = l.rule + 3 * nqp;
-  l.rn = both ? l.cn + 3 * TC : nullptr;
-  l.cg = l.cn + 3 * TC + (both ? 3 * TR : 0);
+  l.cc = l.cn + 4 * TC;
+  l.rn = both ? l.cc + 3 * TC : nullptr;
+  l.cg = l.cc + 3 * TC + (both ? 3 * TR : 0);
   l.rb = l.cg + (MIXED ? 3 * TC : 0);
   l.cb = l.rb + (MIXED ? 6 * TR : 0);
   int *ib = reinterpret_cast<int *>(l.cb + (MIXED ? 6 * TC : 0));
   l.rid = ib;
   l.rv = l.rid + TR;
-  l.cid = l.rv + 3 * TR;
+  l.rs = l.rv + 3 * TR;
+  l.cid = l.rs + TR;
   l.cv = l.cid + TC;
-  l.count = l.cv + 3 * TC;
+  l.cs = l.cv + 3 * TC;
+  l.count = l.cs + TC;
   l.bad = l.count + 1;
   l.rcount = l.bad + 1;
   l.ccount = l.rcount + 2;
@@ -74,412 +91,584 @@ __device__ __forceinline__ Lds carve(double *base, int nqp, int TR, int TC, bool
   return l;
 }
 
-// FP64 sum over the point pairs of one regular entry (sub-tile row rl,
-// column cl): sum_b wy_b sum_a wx_a k'(x_a, y_b), where k' omits the factor
-// 1/(4 pi) and, for the double layer, the factor 1/2 of the scaled normal
-// distance.  4 |x - y|^2 = |X|^2 + |Y|^2 + X . (-2Y) in block-local
-// coordinates; 1/r from v_rsq_f64 and one Newton step.  The double layer's
-// wx <X - Y, n_j> is formed once per x-point (<Y, n_j> is constant on the
-// column triangle's plane).
-template <int KERNEL, int LAYER, int XC>
-__device__ __forceinline__ Acc<KERNEL> regular_entry(const Lds &l, int TR, int TC, int nqp, int rl,
-                                                     int cl, double kq) {
-  const double D0 = l.rg[0 * TR + rl], D1 = l.rg[1 * TR + rl], D2 = l.rg[2 * TR + rl];
-  const double A0 = l.rg[3 * TR + rl], A1 = l.rg[4 * TR + rl], A2 = l.rg[5 * TR + rl];
-  const double B0 = l.rg[6 * TR + rl], B1 = l.rg[7 * TR + rl], B2 = l.rg[8 * TR + rl];
-  const double SG = l.rg[9 * TR + rl];
-  double n0 = 0, n1 = 0, n2 = 0;
-  if constexpr (LAYER == BEM_DLP) {
-    n0 = l.cn[cl];
-    n1 = l.cn[TC + cl];
-    n2 = l.cn[2 * TC + cl];
-  }
-  const double2 *ycol = reinterpret_cast<const double2 *>(l.ys) + 3 * cl;
-  const int ystride = 3 * TC;  // double2 per point index
-  // <Y, n_j> takes one value on the column triangle's plane: that of its
-  // first point
-  const double YN = LAYER == BEM_DLP ? ycol[2].y : 0.0;
-  Acc<KERNEL> acc;
-  for (int ch = 0; ch < nqp; ch += XC) {
-    // WN = wx <X - Y, n_j>, the same for every column point
-    double X0[XC], X1[XC], X2[XC], XX[XC], WX[XC], WN[XC];
-#pragma unroll
-    for (int a = 0; a < XC; ++a) {
-      const double s = l.rule[ch + a], t = l.rule[nqp + ch + a], w = l.rule[2 * nqp + ch + a];
-      X0[a] = fma(s, A0, fma(t, B0, D0));
-      X1[a] = fma(s, A1, fma(t, B1, D1));
-      X2[a] = fma(s, A2, fma(t, B2, D2));
-      XX[a] = fma(X0[a], X0[a], fma(X1[a], X1[a], X2[a] * X2[a]));
-      WX[a] = w * SG;
-      if constexpr (LAYER == BEM_DLP)
-        WN[a] = WX[a] * (fma(X0[a], n0, fma(X1[a], n1, X2[a] * n2)) - YN);
-    }
-    // one column point: (-2Y, |Y|^2, w sqrt(g_j), <Y, n_j>) as three double2
-    auto point = [&](const double2 c0, const double2 c1, const double2 c2) {
-      const double M0 = c0.x, M1 = c0.y, M2 = c1.x, YY = c1.y, WY = c2.x;
-      // the XC chains are written stage by stage so that they interleave
-      double sq[XC], h[XC];
-#pragma unroll
-      for (int a = 0; a < XC; ++a)
-        sq[a] = fma(X2[a], M2, fma(X1[a], M1, fma(X0[a], M0, XX[a] + YY)));  // 4 r^2
-#pragma unroll
-      for (int a = 0; a < XC; ++a) h[a] = __builtin_amdgcn_rsq(sq[a]);     // ~ 1/(2r)
-      double ire = 0.0, iim = 0.0;
-#pragma unroll
-      for (int a = 0; a < XC; ++a) {
-        // one Newton step: z = h (3 - s h^2) ~ 1/r
-        const double z = h[a] * fma(-(sq[a] * h[a]), h[a], 3.0);
-        if constexpr (KERNEL == BEM_LAPLACE) {
-          if constexpr (LAYER == BEM_SLP) {
-            ire = fma(WX[a], z, ire);
-          } else {
-            ire = fma(WN[a], z * z * z, ire);  // wx 2 <x - y, n_j> / r^3
-          }
-        } else {
-          const double kr = kq * sq[a] * z;  // kappa r  (kq = kappa / 4)
-          double sn, cs;
-          sincos_cw(kr, &sn, &cs);
-          if constexpr (LAYER == BEM_SLP) {
-            const double wz = WX[a] * z;
-            ire = fma(wz, cs, ire);
-            iim = fma(wz, sn, iim);
-          } else {
-            const double u = WN[a] * z * z * z;
-            ire = fma(u, fma(kr, sn, cs), ire);
-            iim = fma(u, fma(-kr, cs, sn), iim);
-          }
-        }
-      }
-      acc.re = fma(WY, ire, acc.re);
-      if constexpr (KERNEL == BEM_HELMHOLTZ) acc.im = fma(WY, iim, acc.im);
-    };
-    // two points per step, the next one's LDS reads issued before the
-    // current one's arithmetic (no register copies between steps)
-    const double2 *yp = ycol;
-    double2 a0 = yp[0], a1 = yp[1], a2 = yp[2];
-    int kb = 0;
-    for (; kb + 2 <= nqp; kb += 2) {
-      const double2 *yn = yp + ystride;
-      const double2 b0 = yn[0], b1 = yn[1], b2 = yn[2];
-      __builtin_amdgcn_sched_barrier(0);  // keep the reads ahead of the arithmetic
-      point(a0, a1, a2);
-      yp = ycol + (kb + 2 < nqp ? kb + 2 : nqp - 1) * ystride;
-      a0 = yp[0], a1 = yp[1], a2 = yp[2];
-      __builtin_amdgcn_sched_barrier(0);
-      point(b0, b1, b2);
-    }
-    if (kb < nqp) point(a0, a1, a2);
-  }
-  return acc;
-}
+// ------------------------------------------------------------ regular sums
+// Arithmetic of the two precisions.  FP64: 1/r from the hardware estimate and
+// one Newton step, z = h u with u = 3 - s h^2.  FP32 (mixed form): the
+// estimate h itself.  kInv: 1/r = kInv z for coordinates doubled (s = 4 r^2).
+// Short phases take coordinates scaled by kappa kScale more, so that s u h
+// (FP32: s h) is kappa r itself and 1/r = kappa kInvK z.
+template <class T>
+struct Arith;
+template <>
+struct Arith<double> {
+  static constexpr double kInv = 1.0, kScale = 0.25, kInvK = 0.25;
+  static __device__ __forceinline__ double mad(double a, double b, double c) { return __builtin_fma(a, b, c); }
+  static __device__ __forceinline__ double rsq(double s) { return __builtin_amdgcn_rsq(s); }
+  static __device__ __forceinline__ double newton(double s, double h) { return mad(-(s * h), h, 3.0); }
+  static __device__ __forceinline__ double inv(double h, double u) { return h * u; }
+  // h0 u0 + h1 u1
+  static __device__ __forceinline__ double inv2(double h0, double u0, double h1, double u1) { return mad(h1, u1, h0 * u0); }
+  static constexpr double kPhase = 0.25;  // kappa r = (kPhase kappa) s z, unscaled
+  // factors of kappa r in scaled coordinates, and of a reference distance
+  static __device__ __forceinline__ double phase(double t, double u) { return t * u; }
+  static __device__ __forceinline__ double phase_from(double t, double u, double kr0) { return mad(t, u, -kr0); }
+  static __device__ __forceinline__ double ref(double s) { return 2.0 * (s * rsq(s)); }
+  static __device__ __forceinline__ void sincos(double x, double *s, double *c) { sincos_cw(x, s, c); }
+  static __device__ __forceinline__ void sincos_short(double x, double *s, double *c) { short_phase(x, s, c); }
+};
+template <>
+struct Arith<float> {
+  static constexpr double kInv = 2.0, kScale = 0.5, kInvK = 1.0;
+  static __device__ __forceinline__ float mad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+  static __device__ __forceinline__ float rsq(float s) { return __builtin_amdgcn_rsqf(s); }
+  static __device__ __forceinline__ float newton(float, float) { return 1.0f; }
+  static __device__ __forceinline__ float inv(float h, float) { return h; }
+  static __device__ __forceinline__ float inv2(float h0, float, float h1, float) { return h0 + h1; }
+  static constexpr double kPhase = 0.5;
+  static __device__ __forceinline__ float phase(float s, float h) { return s * h; }
+  static __device__ __forceinline__ float phase_from(float s, float h, float kr0) { return mad(s, h, -kr0); }
+  static __device__ __forceinline__ float ref(float s) { return s * rsq(s); }
+  static __device__ __forceinline__ void sincos(float x, float *s, float *c) { sincos_cw_f32(x, s, c); }
+  static __device__ __forceinline__ void sincos_short(float x, float *s, float *c) { short_phase_f32(x, s, c); }
+};
 
-// One pass over the point pairs of regular entry (rl, cl) for both layers
-// and for the double layer of the transposed pair (j, i), with k' as in
-// regular_entry.  The distance, its reciprocal root (and for Helmholtz the
-// sine and cosine) of a pair serve all three; with k3 the double layer's
-// radial factor and, per column point b,
-//   t1_b = sum_a wx_a k3_ab,   t2_b = sum_a wx_a <X_a - Y, n_j> k3_ab,
-//   SLP(i, j) = sum_b wy_b sum_a wx_a k_ab,
-//   DLP(i, j) = sum_b wy_b t2_b,
-//   DLP(j, i) = sum_b wy_b (<Y_b, n_i> - <X, n_i>) t1_b,
-// since <X_a, n_i> takes one value on the row triangle's plane and <Y_b, n_j>
-// one on the column triangle's.  The point pairs of (j, i) are those of
-// (i, j) with the roles of x and y exchanged: the same triangle rule on both.
-template <int KERNEL, int XC>
-__device__ __forceinline__ void regular_entry_both(const Lds &l, int TR, int TC, int nqp, int rl,
-                                                   int cl, double kq, Acc<KERNEL> *gs,
-                                                   Acc<KERNEL> *gd, Acc<KERNEL> *gm) {
-  const double D0 = l.rg[0 * TR + rl], D1 = l.rg[1 * TR + rl], D2 = l.rg[2 * TR + rl];
-  const double A0 = l.rg[3 * TR + rl], A1 = l.rg[4 * TR + rl], A2 = l.rg[5 * TR + rl];
-  const double B0 = l.rg[6 * TR + rl], B1 = l.rg[7 * TR + rl], B2 = l.rg[8 * TR + rl];
-  const double SG = l.rg[9 * TR + rl];
-  const double n0 = l.cn[cl], n1 = l.cn[TC + cl], n2 = l.cn[2 * TC + cl];
-  const double m0 = l.rn[rl], m1 = l.rn[TR + rl], m2 = l.rn[2 * TR + rl];
-  const double XN = fma(D0, m0, fma(D1, m1, D2 * m2));  // <X, n_i>
-  // -n_i / 2: <-2Y, -n_i / 2> = <Y, n_i>
-  const double p0 = -0.5 * m0, p1 = -0.5 * m1, p2 = -0.5 * m2;
-  const double2 *ycol = reinterpret_cast<const double2 *>(l.ys) + 3 * cl;
-  const int ystride = 3 * TC;
-  const double YN = ycol[2].y;  // <Y, n_j>: one value on the column triangle's plane
+// One entry's operands: the row triangle (V relative to the column triangle's
+// first vertex in the mixed form), the column's normal and centroid, the
+// row's normal (both layers).
+struct EntryGeo {
+  double V[3], A[3], B[3], sg, c1, k0, a22;
+  double n[3], yn;  // n_j, <Y, n_j>
+  double m[3];      // n_i
+  double cen[3];    // centroid of tau_j, doubled, in the coordinates of V
+};
+
+// Sums of an entry without the factor 1/(4 pi) (and 1/2 of the doubled normal
+// distance): single layer, double layer, double layer of (j, i).
+template <int KERNEL>
+struct Sums {
   Acc<KERNEL> s, d, m;
-  for (int ch = 0; ch < nqp; ch += XC) {
-    double X0[XC], X1[XC], X2[XC], XX[XC], WX[XC], WN[XC];
-#pragma unroll
-    for (int a = 0; a < XC; ++a) {
-      const double u = l.rule[ch + a], t = l.rule[nqp + ch + a], w = l.rule[2 * nqp + ch + a];
-      X0[a] = fma(u, A0, fma(t, B0, D0));
-      X1[a] = fma(u, A1, fma(t, B1, D1));
-      X2[a] = fma(u, A2, fma(t, B2, D2));
-      XX[a] = fma(X0[a], X0[a], fma(X1[a], X1[a], X2[a] * X2[a]));
-      WX[a] = w * SG;
-      WN[a] = WX[a] * (fma(X0[a], n0, fma(X1[a], n1, X2[a] * n2)) - YN);  // wx <X - Y, n_j>
-    }
-    auto point = [&](const double2 c0, const double2 c1, const double2 c2) {
-      const double M0 = c0.x, M1 = c0.y, M2 = c1.x, YY = c1.y, WY = c2.x;
-      double sq[XC], h[XC];
-#pragma unroll
-      for (int a = 0; a < XC; ++a)
-        sq[a] = fma(X2[a], M2, fma(X1[a], M1, fma(X0[a], M0, XX[a] + YY)));  // 4 r^2
-#pragma unroll
-      for (int a = 0; a < XC; ++a) h[a] = __builtin_amdgcn_rsq(sq[a]);
-      double sre = 0.0, sim = 0.0, t1r = 0.0, t1i = 0.0, t2r = 0.0, t2i = 0.0;
-#pragma unroll
-      for (int a = 0; a < XC; ++a) {
-        const double z = h[a] * fma(-(sq[a] * h[a]), h[a], 3.0);  // ~ 1/r
-        const double z3 = z * z * z;
-        if constexpr (KERNEL == BEM_LAPLACE) {
-          sre = fma(WX[a], z, sre);
-          t1r = fma(WX[a], z3, t1r);
-          t2r = fma(WN[a], z3, t2r);
-        } else {
-          const double kr = kq * sq[a] * z;
-          double sn, cs;
-          sincos_cw(kr, &sn, &cs);
-          const double wz = WX[a] * z;
-          sre = fma(wz, cs, sre);
-          sim = fma(wz, sn, sim);
-          const double fr = z3 * fma(kr, sn, cs), fi = z3 * fma(-kr, cs, sn);
-          t1r = fma(WX[a], fr, t1r);
-          t1i = fma(WX[a], fi, t1i);
-          t2r = fma(WN[a], fr, t2r);
-          t2i = fma(WN[a], fi, t2i);
-        }
-      }
-      const double wm = WY * (fma(M0, p0, fma(M1, p1, M2 * p2)) - XN);  // wy 2 <y - x, n_i>
-      s.re = fma(WY, sre, s.re);
-      d.re = fma(WY, t2r, d.re);
-      m.re = fma(wm, t1r, m.re);
-      if constexpr (KERNEL == BEM_HELMHOLTZ) {
-        s.im = fma(WY, sim, s.im);
-        d.im = fma(WY, t2i, d.im);
-        m.im = fma(wm, t1i, m.im);
-      }
-    };
-    const double2 *yp = ycol;
-    double2 a0 = yp[0], a1 = yp[1], a2 = yp[2];
-    int kb = 0;
-    for (; kb + 2 <= nqp; kb += 2) {
-      const double2 *yn = yp + ystride;
-      const double2 b0 = yn[0], b1 = yn[1], b2 = yn[2];
+};
+
+// Column points from LDS (b-th point of the rule).
+struct PointsLds64 {
+  const double2 *p;
+  int stride;
+  struct P { double2 a, b; };
+  __device__ __forceinline__ P get(int b) const { return {p[b * stride], p[b * stride + 1]}; }
+  static __device__ __forceinline__ void unpack(const P &q, double *y, double *w) { y[0] = q.a.x, y[1] = q.a.y, y[2] = q.b.x, *w = q.b.y; }
+};
+struct PointsLds32 {
+  const float4 *p;
+  int stride;
+  typedef float4 P;
+  __device__ __forceinline__ P get(int b) const { return p[b * stride]; }
+  static __device__ __forceinline__ void unpack(const P &q, float *y, float *w) { y[0] = q.x, y[1] = q.y, y[2] = q.z, *w = q.w; }
+};
+
+// Two points per step, the next one's LDS reads issued before the current
+// one's arithmetic (no register copies between steps).
+// ONE: one point per step with the copies (a third copy of a long body, for
+// the last of an odd number of points, costs registers).
+template <bool ONE, class PTS, class F>
+__device__ __forceinline__ void for_points(const PTS &pts, int n, F &&point) {
+  typename PTS::P a = pts.get(0);
+  int k = 0;
+  if constexpr (ONE) {
+    for (; k < n; ++k) {
+      const typename PTS::P b = pts.get(k + 1 < n ? k + 1 : n - 1);
       __builtin_amdgcn_sched_barrier(0);
-      point(a0, a1, a2);
-      yp = ycol + (kb + 2 < nqp ? kb + 2 : nqp - 1) * ystride;
-      a0 = yp[0], a1 = yp[1], a2 = yp[2];
-      __builtin_amdgcn_sched_barrier(0);
-      point(b0, b1, b2);
+      point(a);
+      a = b;
     }
-    if (kb < nqp) point(a0, a1, a2);
+    return;
   }
-  *gs = s;
-  *gd = d;
-  *gm = m;
+  for (; k + 2 <= n; k += 2) {
+    const typename PTS::P b = pts.get(k + 1);
+    __builtin_amdgcn_sched_barrier(0);  // keep the reads ahead of the arithmetic
+    point(a);
+    a = pts.get(k + 2 < n ? k + 2 : n - 1);
+    __builtin_amdgcn_sched_barrier(0);
+    point(b);
+  }
+  if (k < n) point(a);
 }
 
-// FP32 sum of one regular entry of the mixed form, in coordinates local to
-// the row triangle's first vertex v0_i (per entry, so that the FP32 rounding
-// of coordinates is relative to the pair's own size):
-//   X_a = 2 (x_a - v0_i),  Y'_b = D + Y_b,  D = 2 (v0_j - v0_i) rounded once,
-//   4 r^2 = |X|^2 + |Y'|^2 - 2 X . Y',  h = v_rsq_f32(4 r^2) = 1/(2r).
-// Returns the same sum as regular_entry (with k' as there).
-template <int KERNEL, int LAYER, int XC>
-__device__ __forceinline__ Acc<KERNEL> regular_entry_f32(const Lds &l, int TR, int TC, int nqp,
-                                                         int rl, int cl, double kappa) {
-  const double A0 = l.rg[3 * TR + rl], A1 = l.rg[4 * TR + rl], A2 = l.rg[5 * TR + rl];
-  const double B0 = l.rg[6 * TR + rl], B1 = l.rg[7 * TR + rl], B2 = l.rg[8 * TR + rl];
-  const double SG = l.rg[9 * TR + rl];
-  const float d0 = (float)(l.cg[cl] - l.rg[0 * TR + rl]);
-  const float d1 = (float)(l.cg[TC + cl] - l.rg[1 * TR + rl]);
-  const float d2 = (float)(l.cg[2 * TC + cl] - l.rg[2 * TR + rl]);
-  float n0 = 0, n1 = 0, n2 = 0, dn = 0;
-  if constexpr (LAYER == BEM_DLP) {
-    n0 = (float)l.cn[cl];
-    n1 = (float)l.cn[TC + cl];
-    n2 = (float)l.cn[2 * TC + cl];
-    dn = fmaf(d0, n0, fmaf(d1, n1, d2 * n2));
-  }
-  const float hk = 0.5f * (float)kappa;  // kappa r = (kappa / 2) (4 r^2) h
-  const float4 *ycol = reinterpret_cast<const float4 *>(l.ys) + 2 * cl;
-  const int ystride = 2 * TC;  // float4 per point index
-  float are = 0.0f, aim = 0.0f;
-  for (int ch = 0; ch < nqp; ch += XC) {
-    // WN = wx <X - Y', n_j> = wx (<X, n_j> - <D, n_j>): <Y_b, n_j> vanishes on
-    // the column triangle's plane
-    float X0[XC], X1[XC], X2[XC], XX[XC], WX[XC], WN[XC];
-#pragma unroll
-    for (int a = 0; a < XC; ++a) {
-      const double s = l.rule[ch + a], t = l.rule[nqp + ch + a], w = l.rule[2 * nqp + ch + a];
-      const float x0 = (float)fma(s, A0, t * B0), x1 = (float)fma(s, A1, t * B1),
-                  x2 = (float)fma(s, A2, t * B2);
-      XX[a] = fmaf(x0, x0, fmaf(x1, x1, x2 * x2));
-      X0[a] = -2.0f * x0;
-      X1[a] = -2.0f * x1;
-      X2[a] = -2.0f * x2;
-      // h = 1/(2r): the SLP's k' = 1/r = 2h, the DLP's k' = 2 <x - y, n> / r^3
-      // = 8 h^3 <X - Y', n> (same k' as the FP64 path)
-      WX[a] = (float)(w * SG) * (LAYER == BEM_SLP ? 2.0f : 8.0f);
-      if constexpr (LAYER == BEM_DLP) WN[a] = WX[a] * (fmaf(x0, n0, fmaf(x1, n1, x2 * n2)) - dn);
-    }
-    // one column point: (Y, w sqrt(g_j), <Y, n_j>) as two float4
-    auto point = [&](const float4 c0, const float4 c1) {
-      const float y0 = d0 + c0.x, y1 = d1 + c0.y, y2 = d2 + c0.z, WY = c0.w;
-      const float YY = fmaf(y0, y0, fmaf(y1, y1, y2 * y2));
-      // the XC chains are written stage by stage so that they interleave
-      float sq[XC], h[XC];
-#pragma unroll
-      for (int a = 0; a < XC; ++a)
-        sq[a] = fmaf(X2[a], y2, fmaf(X1[a], y1, fmaf(X0[a], y0, XX[a] + YY)));  // 4 r^2
-#pragma unroll
-      for (int a = 0; a < XC; ++a) h[a] = __builtin_amdgcn_rsqf(sq[a]);
-      float ire = 0.0f, iim = 0.0f;
-#pragma unroll
-      for (int a = 0; a < XC; ++a) {
-        if constexpr (KERNEL == BEM_LAPLACE) {
-          if constexpr (LAYER == BEM_SLP) {
-            ire = fmaf(WX[a], h[a], ire);
-          } else {
-            ire = fmaf(WN[a], h[a] * h[a] * h[a], ire);
-          }
+// Kernel values of one column point against x-points, summed with weights.
+// Everything a point pair costs beyond its distance is here:
+//   single layer  sum w k,   double layer  sum wn k3 (wn = w <X - Y, n_j>),
+//   both layers   t1 = sum w k3, t2 = sum wn k3 and the single layer's sum,
+// with k = 1/r, k3 = 1/r^3, times e^{i kappa r} resp. e^{i kappa r} (1 - i
+// kappa r) for Helmholtz.  SHORT: phases relative to kr0 (kappa r - kr0 in
+// [-1/2, 1/2]), the common factor e^{i kr0} left to the caller.
+template <int KERNEL, int LAYER, class T>
+struct PointSums {
+  T sr = 0, si = 0, t1r = 0, t1i = 0, t2r = 0, t2i = 0;
+};
+
+// One x-point at squared distance s with estimate h: the single layer's value
+// (kr_, ki_), the double layer's phase factor (fr, fi) and z^3 (Laplace: fr
+// unused).
+template <int KERNEL, int LAYER, bool SHORT, class T>
+struct PairValue {
+  typedef Arith<T> M;
+  T kr_, ki_, fr, fi, z3;
+  __device__ __forceinline__ void eval(T s, T h, T kq, T kr0) {
+    if constexpr (KERNEL == BEM_LAPLACE) {
+      const T z = M::inv(h, M::newton(s, h));
+      kr_ = z;
+      if constexpr (LAYER != BEM_SLP) z3 = z * z * z;
+    } else {
+      T z, kr = 0, sn, cs;
+      if constexpr (SHORT) {
+        T t, u;  // kappa r = t u
+        if constexpr (std::is_same<T, double>::value) {
+          t = s * h;
+          u = M::mad(-t, h, (T)3);
+          z = h * u;
         } else {
-          const float kr = hk * sq[a] * h[a];
-          float sn, cs;
-          sincos_cw_f32(kr, &sn, &cs);
-          if constexpr (LAYER == BEM_SLP) {
-            const float wz = WX[a] * h[a];
-            ire = fmaf(wz, cs, ire);
-            iim = fmaf(wz, sn, iim);
-          } else {
-            const float u = WN[a] * h[a] * h[a] * h[a];
-            ire = fmaf(u, fmaf(kr, sn, cs), ire);
-            iim = fmaf(u, fmaf(-kr, cs, sn), iim);
+          t = s;
+          u = z = h;
+        }
+        if constexpr (LAYER != BEM_SLP) {
+          kr = M::phase(t, u);
+          M::sincos_short(kr - kr0, &sn, &cs);
+        } else {
+          M::sincos_short(M::phase_from(t, u, kr0), &sn, &cs);
+        }
+      } else {
+        z = M::inv(h, M::newton(s, h));
+        kr = kq * s * z;
+        M::sincos(kr, &sn, &cs);
+      }
+      if constexpr (LAYER != BEM_DLP) kr_ = z * cs, ki_ = z * sn;
+      if constexpr (LAYER != BEM_SLP) {
+        z3 = z * z * z;
+        fr = M::mad(kr, sn, cs);
+        fi = M::mad(-kr, cs, sn);
+      }
+    }
+  }
+  // the double layer's value, times z^3
+  __device__ __forceinline__ T dr() const { return KERNEL == BEM_LAPLACE ? z3 : z3 * fr; }
+  __device__ __forceinline__ T di() const { return z3 * fi; }
+};
+
+// Adds one column point's sums, weighted: wy (entry), wm (transposed double
+// layer), both rotated by e^{i kr0} = (cy, sy) when SHORT.
+template <int KERNEL, int LAYER, bool SHORT, class T>
+struct EntrySums {
+  typedef Arith<T> M;
+  T sr = 0, si = 0, dr = 0, di = 0, mr = 0, mi = 0;
+  static __device__ __forceinline__ void rot(T w, T cy, T sy, T re, T im, T *ar, T *ai) {
+    if constexpr (KERNEL == BEM_LAPLACE) {
+      *ar = M::mad(w, re, *ar);
+    } else if constexpr (!SHORT) {
+      *ar = M::mad(w, re, *ar);
+      *ai = M::mad(w, im, *ai);
+    } else {
+      const T cw = w * cy, sw = w * sy;
+      *ar = M::mad(cw, re, M::mad(-sw, im, *ar));
+      *ai = M::mad(cw, im, M::mad(sw, re, *ai));
+    }
+  }
+  __device__ __forceinline__ void add(const PointSums<KERNEL, LAYER, T> &p, T wy, T wm, T cy, T sy) {
+    if constexpr (LAYER != BEM_DLP) rot(wy, cy, sy, p.sr, p.si, &sr, &si);
+    if constexpr (LAYER != BEM_SLP) rot(wy, cy, sy, p.t2r, p.t2i, &dr, &di);
+    if constexpr (LAYER == kBoth) rot(wm, cy, sy, p.t1r, p.t1i, &mr, &mi);
+  }
+  // to FP64, times sqrt(g_i) and the powers of inv (1/r = inv z); SHORT:
+  // rotated by e^{i kr00} = (c0, s0), conjugated for a negative kappa
+  __device__ __forceinline__ void finish(double sg, double inv, double c0, double s0, bool neg,
+                                         Sums<KERNEL> *o) const {
+    auto put = [&](double f, T re, T im, Acc<KERNEL> *v) {
+      const double r = f * (double)re;
+      if constexpr (KERNEL == BEM_LAPLACE) {
+        v->re = r;
+      } else {
+        const double i = f * (double)im;
+        if constexpr (SHORT) {
+          v->re = __builtin_fma(c0, r, -s0 * i);
+          const double w = __builtin_fma(c0, i, s0 * r);
+          v->im = neg ? -w : w;
+        } else {
+          v->re = r;
+          v->im = i;
+        }
+      }
+    };
+    const double f1 = sg * inv, f3 = f1 * inv * inv;
+    if constexpr (LAYER != BEM_DLP) put(f1, sr, si, &o->s);
+    if constexpr (LAYER != BEM_SLP) put(f3, dr, di, &o->d);
+    if constexpr (LAYER == kBoth) put(f3, mr, mi, &o->m);
+  }
+};
+
+template <class T>
+struct DuffyPtr;
+template <>
+struct DuffyPtr<double> {
+  typedef uniform_ptr type;
+  static __device__ __forceinline__ type of(const double *t) { return (type)t; }
+};
+template <>
+struct DuffyPtr<float> {
+  typedef const float __attribute__((address_space(4))) *type;
+  static __device__ __forceinline__ type of(const double *t);
+};
+
+// Offsets in the table of a Duffy rule of order Q (duffy_table): per xi
+// (xi, xi^2, w_xi xi, w_xi xi^2); the half-width nodes delta > 0 of eta =
+// 1/2 +- delta, their squares, the eta weights w (pairs, then the centre of an
+// odd order) and w delta of the pairs; and for every (xi, pair) xi delta and
+// (xi, eta) the full weight.
+template <int Q>
+struct DuffyAt {
+  static constexpr int H = Q / 2, HC = (Q + 1) / 2;
+  static constexpr int J = 0, D = 4 * Q, D2 = D + H, W = D2 + H, WD = W + HC, XD = WD + H,
+                       WF = XD + Q * H;
+};
+inline __device__ DuffyPtr<float>::type DuffyPtr<float>::of(const double *t) { return (type)t; }
+
+// Sums over the point pairs of one regular entry, Duffy rule of order Q on
+// both triangles.  Bound by FP64 (FP32) issue, so the point pair is cut to
+// what its own distance needs: on the row triangle the squared distance is a
+// quadratic polynomial of the Duffy coordinates whose coefficients take 12
+// operations per column point, then per xi two or three and per symmetric eta
+// pair 1/2 +- delta three (2 to 2.4 per point pair, from 4 for coordinates of
+// every x-point); equal weights of a pair are applied once, to its sum.  The
+// rule's constants are wave-uniform (scalar registers).
+// Laplace to order 4: every xi unrolled, products of constants and the double
+// layer's point weights w <X - Y, n_j> (w (n0 + xi na +- xi delta nb)) kept.
+// Else (ROLL) one xi at a time in a loop: unrolled, the chains of Q^2 sines
+// and cosines spill (the 32768-triangle Helmholtz near field took 34 ms);
+// the double layer's weights are formed at every point pair, or (both layers)
+// their three terms summed separately and combined per column point.
+// Per point pair (FP64 instructions, v_rsq_f64 as four): Laplace single, double,
+// both layers 12, 14, 16 -> 10.3, 12.8, 15.2; Helmholtz 46, 50, 55 -> 28, 34,
+// 43 with short phases.  Vector units 94 % busy (18432 triangles, Helmholtz
+// coupling): 38.6 -> 30.3 ms; Laplace coupling (8192, q = 4) 2.13 -> 1.82 ms,
+// one-pass near field 0.69 -> 0.59 ms, Helmholtz (32768, q = 5) 22.3 -> 17.9 ms.
+// FP64 and FP32 matrix instructions were no help: they do not overlap with the
+// vector unit's (a 16 x 16 x 4 product takes the 64 cycles of its multiply-adds).
+template <int KERNEL, int LAYER, int Q, bool SHORT, class T, class PTS>
+__device__ __forceinline__ void duffy_sums(const EntryGeo &g, const double *table, double kappa,
+                                           const PTS &pts, Sums<KERNEL> *out) {
+  typedef Arith<T> M;
+  typedef DuffyAt<Q> C;
+  constexpr int H = C::H, HC = C::HC;
+  constexpr bool ODD = Q & 1, HELM = KERNEL == BEM_HELMHOLTZ;
+  constexpr bool ROLL = HELM || Q >= 5;
+  constexpr bool LIN = ROLL && LAYER == kBoth;    // double-layer weights in three sums
+  constexpr bool FLY = ROLL && LAYER == BEM_DLP;  // formed at every point pair
+  const typename DuffyPtr<T>::type c = DuffyPtr<T>::of(table);
+  // short phases: coordinates scaled by f so that kappa r needs no factor
+  const double ka = fabs(kappa), f = HELM && SHORT ? ka * M::kScale : 1.0;
+  const T V0 = (T)(f * g.V[0]), V1 = (T)(f * g.V[1]), V2 = (T)(f * g.V[2]);
+  const T A0 = (T)(f * g.A[0]), A1 = (T)(f * g.A[1]), A2 = (T)(f * g.A[2]);
+  const T B0 = (T)(f * g.B[0]), B1 = (T)(f * g.B[1]), B2 = (T)(f * g.B[2]);
+  const T c1 = (T)(f * f * g.c1), k0 = (T)(f * f * g.k0), a22 = (T)(f * f * g.a22), mf = (T)-f;
+  T K[HC];
+#pragma unroll
+  for (int k = 0; k < H; ++k) K[k] = M::mad(c[C::D2 + k], a22, k0);
+  if (ODD) K[HC - 1] = k0;
+  T WN[ROLL ? 1 : Q][Q], n0 = 0, na = 0, nb = 0;
+  if constexpr (LAYER != BEM_SLP) {
+    n0 = (T)(fma(g.V[0], g.n[0], fma(g.V[1], g.n[1], g.V[2] * g.n[2])) - g.yn);
+    na = (T)(0.5 * fma(g.A[0], g.n[0], fma(g.A[1], g.n[1], g.A[2] * g.n[2])));
+    nb = (T)(0.5 * fma(g.B[0], g.n[0], fma(g.B[1], g.n[1], g.B[2] * g.n[2])));
+  }
+  if constexpr (LAYER != BEM_SLP && !ROLL) {
+#pragma unroll
+    for (int j = 0; j < Q; ++j) {
+      const T base = M::mad(c[4 * j], na, n0);
+#pragma unroll
+      for (int k = 0; k < H; ++k) {
+        const T e = c[C::XD + j * H + k] * nb;
+        WN[j][2 * k] = c[C::WF + j * HC + k] * (base + e);
+        WN[j][2 * k + 1] = c[C::WF + j * HC + k] * (base - e);
+      }
+      if (ODD) WN[j][Q - 1] = c[C::WF + j * HC + H] * base;
+    }
+  }
+  T NB[H];
+  if constexpr (FLY) {
+#pragma unroll
+    for (int k = 0; k < H; ++k) NB[k] = c[C::D + k] * nb;
+  }
+  T m0 = 0, m1 = 0, m2 = 0;
+  if constexpr (LAYER == kBoth) {
+    const double r = HELM && SHORT ? 1.0 / f : 1.0;
+    m0 = (T)(r * g.m[0]), m1 = (T)(r * g.m[1]), m2 = (T)(r * g.m[2]);
+  }
+  const T kq = (T)(M::kPhase * kappa);
+  T kr00 = 0;
+  double c0 = 1.0, s0 = 0.0;
+  if constexpr (HELM && SHORT) {
+    // kappa times the distance of the centroids
+    double r2 = 0.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const double d = fma(1.0 / 3.0, g.A[k], g.V[k]) - g.cen[k];
+      r2 = fma(d, d, r2);
+    }
+    kr00 = (T)(0.5 * ka * (r2 * rsqrt_newton(r2)));
+    sincos_cw((double)kr00, &s0, &c0);
+  }
+  EntrySums<KERNEL, LAYER, SHORT, T> sum;
+  for_points<ROLL>(pts, Q * Q, [&](const typename PTS::P &pt) {
+    T y[3], wy;
+    PTS::unpack(pt, y, &wy);
+    const T D0 = M::mad(mf, y[0], V0), D1 = M::mad(mf, y[1], V1), D2 = M::mad(mf, y[2], V2);
+    const T U = M::mad(D0, D0, M::mad(D1, D1, D2 * D2));
+    const T R = M::mad(D0, A0, M::mad(D1, A1, D2 * A2));
+    const T S = M::mad(D0, B0, M::mad(D1, B1, D2 * B2));
+    T kr0 = 0, cy = 1, sy = 0;
+    if constexpr (HELM && SHORT) {
+      // the row centroid (xi = 2/3, eta = 1/2); only the reference of the
+      // phases, so the hardware estimate serves
+      const T q0 = M::mad((T)(4.0 / 9.0), k0, M::mad((T)(2.0 / 3.0), R, U));
+      kr0 = M::ref(q0);
+      M::sincos_short(kr0 - kr00, &sy, &cy);
+    }
+    PointSums<KERNEL, LAYER, T> ps;
+    T txr = 0, txi = 0, tbr = 0, tbi = 0;  // LIN: xi and xi delta moments
+    // the q points of one xi (x), weight wx; j: its index if unrolled
+    auto row = [&](int j, T x, T x2, T wx, T wxx) {
+      const T E = M::mad(x, R, U);
+      T O = M::mad(x, c1, S);
+      if (ROLL) O *= x;
+      T s[Q], h[Q];
+#pragma unroll
+      for (int k = 0; k < H; ++k) {
+        const T mid = M::mad(x2, K[k], E);
+        const T dl = ROLL ? c[C::D + k] : c[C::XD + j * H + k];
+        s[2 * k] = M::mad(dl, O, mid);
+        s[2 * k + 1] = M::mad(-dl, O, mid);
+      }
+      if (ODD) s[Q - 1] = M::mad(x2, K[HC - 1], E);
+#pragma unroll
+      for (int k = 0; k < Q; ++k) h[k] = M::rsq(s[k]);
+      // weighted sums over eta: into the point's sums (full weights) or first
+      // into this xi's
+      PointSums<KERNEL, LAYER, T> in;
+      T ibr = 0, ibi = 0;
+      const T base = FLY ? M::mad(x, na, n0) : (T)0;
+      PointSums<KERNEL, LAYER, T> &w = ROLL ? in : ps;
+      auto wt = [&](int k) { return ROLL ? c[C::W + k] : c[C::WF + j * HC + k]; };
+      if constexpr (KERNEL == BEM_LAPLACE && LAYER == BEM_SLP) {
+#pragma unroll
+        for (int k = 0; k < H; ++k)
+          w.sr = M::mad(wt(k), M::inv2(h[2 * k], M::newton(s[2 * k], h[2 * k]), h[2 * k + 1],
+                                       M::newton(s[2 * k + 1], h[2 * k + 1])), w.sr);
+        if (ODD) w.sr = M::mad(wt(H), M::inv(h[Q - 1], M::newton(s[Q - 1], h[Q - 1])), w.sr);
+      } else {
+#pragma unroll
+        for (int k = 0; k < HC; ++k) {
+          const bool two = k < H;
+          const int a = two ? 2 * k : Q - 1;
+          PairValue<KERNEL, LAYER, SHORT, T> v, u;
+          v.eval(s[a], h[a], kq, kr0);
+          if (two) u.eval(s[a + 1], h[a + 1], kq, kr0);
+          if constexpr (LAYER != BEM_DLP) {
+            w.sr = M::mad(wt(k), two ? v.kr_ + u.kr_ : v.kr_, w.sr);
+            if constexpr (HELM) w.si = M::mad(wt(k), two ? v.ki_ + u.ki_ : v.ki_, w.si);
+          }
+          if constexpr (FLY) {
+            const T wa = two ? M::mad(x, NB[k], base) * v.z3 : base * v.z3;
+            const T wb = two ? M::mad(-x, NB[k], base) * u.z3 : (T)0;
+            if constexpr (HELM) {
+              const T pr = wa * v.fr, pi = wa * v.fi;
+              w.t2r = M::mad(wt(k), two ? M::mad(wb, u.fr, pr) : pr, w.t2r);
+              w.t2i = M::mad(wt(k), two ? M::mad(wb, u.fi, pi) : pi, w.t2i);
+            } else {
+              w.t2r = M::mad(wt(k), two ? wa + wb : wa, w.t2r);
+            }
+          } else if constexpr (LAYER != BEM_SLP) {
+            const T ar = v.dr(), br = two ? u.dr() : (T)0;
+            T ai = 0, bi = 0;
+            if constexpr (HELM) ai = v.di(), bi = two ? u.di() : (T)0;
+            if constexpr (LAYER == kBoth) {
+              w.t1r = M::mad(wt(k), two ? ar + br : ar, w.t1r);
+              if constexpr (HELM) w.t1i = M::mad(wt(k), two ? ai + bi : ai, w.t1i);
+            }
+            if constexpr (LIN) {
+              if (two) {
+                ibr = M::mad(c[C::WD + k], ar - br, ibr);
+                if constexpr (HELM) ibi = M::mad(c[C::WD + k], ai - bi, ibi);
+              }
+            } else {
+              ps.t2r = M::mad(WN[ROLL ? 0 : j][a], ar, ps.t2r);
+              if (two) ps.t2r = M::mad(WN[ROLL ? 0 : j][a + 1], br, ps.t2r);
+            }
           }
         }
       }
-      are = fmaf(WY, ire, are);
-      if constexpr (KERNEL == BEM_HELMHOLTZ) aim = fmaf(WY, iim, aim);
+      if constexpr (ROLL) {
+        if constexpr (LAYER != BEM_DLP) {
+          ps.sr = M::mad(wx, in.sr, ps.sr);
+          if constexpr (HELM) ps.si = M::mad(wx, in.si, ps.si);
+        }
+        if constexpr (FLY) {
+          ps.t2r = M::mad(wx, in.t2r, ps.t2r);
+          if constexpr (HELM) ps.t2i = M::mad(wx, in.t2i, ps.t2i);
+        }
+        if constexpr (LIN) {
+          ps.t1r = M::mad(wx, in.t1r, ps.t1r);
+          if constexpr (HELM) ps.t1i = M::mad(wx, in.t1i, ps.t1i);
+          txr = M::mad(wxx, in.t1r, txr);
+          tbr = M::mad(wxx, ibr, tbr);
+          if constexpr (HELM) {
+            txi = M::mad(wxx, in.t1i, txi);
+            tbi = M::mad(wxx, ibi, tbi);
+          }
+        }
+      }
     };
-    // two points per step, the next one's LDS reads issued first
-    const float4 *yp = ycol;
-    float4 a0 = yp[0], a1 = yp[1];
-    int kb = 0;
-    for (; kb + 2 <= nqp; kb += 2) {
-      const float4 *yn = yp + ystride;
-      const float4 b0 = yn[0], b1 = yn[1];
-      __builtin_amdgcn_sched_barrier(0);  // keep the reads ahead of the arithmetic
-      point(a0, a1);
-      yp = ycol + (kb + 2 < nqp ? kb + 2 : nqp - 1) * ystride;
-      a0 = yp[0], a1 = yp[1];
-      __builtin_amdgcn_sched_barrier(0);
-      point(b0, b1);
+    if constexpr (ROLL) {
+      // the next xi's constants are read before this one's arithmetic
+      T x = c[0], x2 = c[1], wx = c[2], wxx = c[3];
+#pragma unroll 1
+      for (int j = 0; j < Q; ++j) {
+        const int p = 4 * (j + 1 < Q ? j + 1 : j);
+        const T nx = c[p], nx2 = c[p + 1], nwx = c[p + 2], nwxx = c[p + 3];
+        row(0, x, x2, wx, wxx);
+        x = nx, x2 = nx2, wx = nwx, wxx = nwxx;
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < Q; ++j) row(j, c[4 * j], c[4 * j + 1], (T)0, (T)0);
     }
-    if (kb < nqp) point(a0, a1);
-  }
-  Acc<KERNEL> acc;
-  acc.re = are;
-  if constexpr (KERNEL == BEM_HELMHOLTZ) acc.im = aim;
-  return acc;
+    if constexpr (LIN) {
+      ps.t2r = M::mad(n0, ps.t1r, M::mad(na, txr, nb * tbr));
+      if constexpr (HELM) ps.t2i = M::mad(n0, ps.t1i, M::mad(na, txi, nb * tbi));
+    }
+    T wm = 0;
+    // wy 2 <y - x, n_i>: <X, n_i> is one value on the row triangle's plane
+    if constexpr (LAYER == kBoth) wm = -wy * M::mad(D0, m0, M::mad(D1, m1, D2 * m2));
+    sum.add(ps, wy, wm, cy, sy);
+  });
+  sum.finish(g.sg, HELM && SHORT ? ka * M::kInvK : M::kInv, c0, s0, kappa < 0.0, out);
 }
 
-// The one-pass form of regular_entry_f32 (see regular_entry_both): both
-// layers of entry (rl, cl) and the double layer of the pair (j, i), in
-// coordinates local to the row triangle's first vertex, where <X, n_i> = 0
-// for every x-point, so that DLP(j, i) = sum_b wy_b <Y'_b, n_i> t1_b.
-// h = v_rsq_f32(4 r^2) = 1/(2r): the single layer's k' = 2h, the double
-// layer's radial factor 8 h^3 (the factors 2 and 8 are applied to the sums).
-template <int KERNEL, int XC>
-__device__ __forceinline__ void regular_entry_both_f32(const Lds &l, int TR, int TC, int nqp,
-                                                       int rl, int cl, double kappa,
-                                                       Acc<KERNEL> *gs, Acc<KERNEL> *gd,
-                                                       Acc<KERNEL> *gm) {
-  const double A0 = l.rg[3 * TR + rl], A1 = l.rg[4 * TR + rl], A2 = l.rg[5 * TR + rl];
-  const double B0 = l.rg[6 * TR + rl], B1 = l.rg[7 * TR + rl], B2 = l.rg[8 * TR + rl];
-  const double SG = l.rg[9 * TR + rl];
-  const float d0 = (float)(l.cg[cl] - l.rg[0 * TR + rl]);
-  const float d1 = (float)(l.cg[TC + cl] - l.rg[1 * TR + rl]);
-  const float d2 = (float)(l.cg[2 * TC + cl] - l.rg[2 * TR + rl]);
-  const float n0 = (float)l.cn[cl], n1 = (float)l.cn[TC + cl], n2 = (float)l.cn[2 * TC + cl];
-  const float m0 = (float)l.rn[rl], m1 = (float)l.rn[TR + rl], m2 = (float)l.rn[2 * TR + rl];
-  const float dn = fmaf(d0, n0, fmaf(d1, n1, d2 * n2));  // <D, n_j>
-  const float hk = 0.5f * (float)kappa;
-  const float4 *ycol = reinterpret_cast<const float4 *>(l.ys) + 2 * cl;
-  const int ystride = 2 * TC;
-  float sre = 0.0f, sim = 0.0f, dre = 0.0f, dim = 0.0f, mre = 0.0f, mim = 0.0f;
+// The same for any triangle rule (rule[3][nqp]: s, t, w, padded to a multiple
+// of XC with zero weights): x-points in register chunks of XC, three
+// operations per squared distance.
+template <int KERNEL, int LAYER, int XC, class T, class PTS>
+__device__ __forceinline__ void general_sums(const EntryGeo &g, const double *rule, int nqp,
+                                             double kappa, const PTS &pts, Sums<KERNEL> *out) {
+  typedef Arith<T> M;
+  const T V0 = (T)g.V[0], V1 = (T)g.V[1], V2 = (T)g.V[2];
+  const T A0 = (T)g.A[0], A1 = (T)g.A[1], A2 = (T)g.A[2];
+  const T B0 = (T)g.B[0], B1 = (T)g.B[1], B2 = (T)g.B[2];
+  T m0 = 0, m1 = 0, m2 = 0;
+  if constexpr (LAYER == kBoth) m0 = (T)g.m[0], m1 = (T)g.m[1], m2 = (T)g.m[2];
+  const double n0 = fma(g.V[0], g.n[0], fma(g.V[1], g.n[1], g.V[2] * g.n[2])) - g.yn;
+  const double na = 0.5 * fma(g.A[0], g.n[0], fma(g.A[1], g.n[1], g.A[2] * g.n[2]));
+  const double nb = 0.5 * fma(g.B[0], g.n[0], fma(g.B[1], g.n[1], g.B[2] * g.n[2]));
+  const T kq = (T)(M::kPhase * kappa);
+  EntrySums<KERNEL, LAYER, false, T> sum;
   for (int ch = 0; ch < nqp; ch += XC) {
-    float X0[XC], X1[XC], X2[XC], XX[XC], WX[XC], WN[XC];
+    T s[XC], e[XC], q[XC], W[XC], WN[XC];
 #pragma unroll
     for (int a = 0; a < XC; ++a) {
-      const double u = l.rule[ch + a], t = l.rule[nqp + ch + a], w = l.rule[2 * nqp + ch + a];
-      const float x0 = (float)fma(u, A0, t * B0), x1 = (float)fma(u, A1, t * B1),
-                  x2 = (float)fma(u, A2, t * B2);
-      XX[a] = fmaf(x0, x0, fmaf(x1, x1, x2 * x2));
-      X0[a] = -2.0f * x0;
-      X1[a] = -2.0f * x1;
-      X2[a] = -2.0f * x2;
-      WX[a] = (float)(w * SG);
-      WN[a] = WX[a] * (fmaf(x0, n0, fmaf(x1, n1, x2 * n2)) - dn);  // wx <X - Y', n_j>
+      const double sa = rule[ch + a], wa = rule[2 * nqp + ch + a];
+      const double ea = fma(-0.5, sa, rule[nqp + ch + a]);
+      s[a] = (T)sa;
+      e[a] = (T)ea;
+      q[a] = (T)fma(sa * sa, g.k0, fma(sa * ea, g.c1, ea * ea * g.a22));
+      W[a] = (T)wa;
+      if constexpr (LAYER != BEM_SLP) WN[a] = (T)(wa * fma(sa, na, fma(ea, nb, n0)));
     }
-    auto point = [&](const float4 c0) {
-      const float y0 = d0 + c0.x, y1 = d1 + c0.y, y2 = d2 + c0.z, WY = c0.w;
-      const float YY = fmaf(y0, y0, fmaf(y1, y1, y2 * y2));
-      float sq[XC], h[XC];
+    for_points<KERNEL == BEM_HELMHOLTZ>(pts, nqp, [&](const typename PTS::P &pt) {
+      T y[3], wy;
+      PTS::unpack(pt, y, &wy);
+      const T D0 = V0 - y[0], D1 = V1 - y[1], D2 = V2 - y[2];
+      const T U = M::mad(D0, D0, M::mad(D1, D1, D2 * D2));
+      const T R = M::mad(D0, A0, M::mad(D1, A1, D2 * A2));
+      const T S = M::mad(D0, B0, M::mad(D1, B1, D2 * B2));
+      T sq[XC], h[XC];
 #pragma unroll
-      for (int a = 0; a < XC; ++a)
-        sq[a] = fmaf(X2[a], y2, fmaf(X1[a], y1, fmaf(X0[a], y0, XX[a] + YY)));  // 4 r^2
+      for (int a = 0; a < XC; ++a) sq[a] = M::mad(e[a], S, M::mad(s[a], R, U + q[a]));
 #pragma unroll
-      for (int a = 0; a < XC; ++a) h[a] = __builtin_amdgcn_rsqf(sq[a]);
-      float tsr = 0.0f, tsi = 0.0f, t1r = 0.0f, t1i = 0.0f, t2r = 0.0f, t2i = 0.0f;
+      for (int a = 0; a < XC; ++a) h[a] = M::rsq(sq[a]);
+      PointSums<KERNEL, LAYER, T> ps;
 #pragma unroll
       for (int a = 0; a < XC; ++a) {
-        const float h3 = h[a] * h[a] * h[a];
-        if constexpr (KERNEL == BEM_LAPLACE) {
-          tsr = fmaf(WX[a], h[a], tsr);
-          t1r = fmaf(WX[a], h3, t1r);
-          t2r = fmaf(WN[a], h3, t2r);
-        } else {
-          const float kr = hk * sq[a] * h[a];
-          float sn, cs;
-          sincos_cw_f32(kr, &sn, &cs);
-          const float wz = WX[a] * h[a];
-          tsr = fmaf(wz, cs, tsr);
-          tsi = fmaf(wz, sn, tsi);
-          const float fr = h3 * fmaf(kr, sn, cs), fi = h3 * fmaf(-kr, cs, sn);
-          t1r = fmaf(WX[a], fr, t1r);
-          t1i = fmaf(WX[a], fi, t1i);
-          t2r = fmaf(WN[a], fr, t2r);
-          t2i = fmaf(WN[a], fi, t2i);
+        PairValue<KERNEL, LAYER, false, T> v;
+        v.eval(sq[a], h[a], kq, (T)0);
+        if constexpr (LAYER != BEM_DLP) {
+          ps.sr = M::mad(W[a], v.kr_, ps.sr);
+          if constexpr (KERNEL == BEM_HELMHOLTZ) ps.si = M::mad(W[a], v.ki_, ps.si);
+        }
+        if constexpr (LAYER != BEM_SLP) {
+          const T ar = v.dr();
+          T ai = 0;
+          if constexpr (KERNEL == BEM_HELMHOLTZ) ai = v.di();
+          if constexpr (LAYER == kBoth) ps.t1r = M::mad(W[a], ar, ps.t1r), ps.t1i = M::mad(W[a], ai, ps.t1i);
+          ps.t2r = M::mad(WN[a], ar, ps.t2r);
+          ps.t2i = M::mad(WN[a], ai, ps.t2i);
         }
       }
-      const float wm = WY * fmaf(y0, m0, fmaf(y1, m1, y2 * m2));  // wy <Y', n_i>
-      sre = fmaf(WY, tsr, sre);
-      dre = fmaf(WY, t2r, dre);
-      mre = fmaf(wm, t1r, mre);
-      if constexpr (KERNEL == BEM_HELMHOLTZ) {
-        sim = fmaf(WY, tsi, sim);
-        dim = fmaf(WY, t2i, dim);
-        mim = fmaf(wm, t1i, mim);
-      }
-    };
-    const float4 *yp = ycol;
-    float4 a0 = yp[0];
-    int kb = 0;
-    for (; kb + 2 <= nqp; kb += 2) {
-      const float4 b0 = (yp + ystride)[0];
-      __builtin_amdgcn_sched_barrier(0);
-      point(a0);
-      yp = ycol + (kb + 2 < nqp ? kb + 2 : nqp - 1) * ystride;
-      a0 = yp[0];
-      __builtin_amdgcn_sched_barrier(0);
-      point(b0);
-    }
-    if (kb < nqp) point(a0);
+      T wm = 0;
+      if constexpr (LAYER == kBoth) wm = -wy * M::mad(D0, m0, M::mad(D1, m1, D2 * m2));
+      sum.add(ps, wy, wm, (T)1, (T)0);
+    });
   }
-  // k' factors: 2 for the single layer, 8 for the double layer
-  gs->re = 2.0 * sre;
-  gd->re = 8.0 * dre;
-  gm->re = 8.0 * mre;
-  if constexpr (KERNEL == BEM_HELMHOLTZ) {
-    gs->im = 2.0 * sim;
-    gd->im = 8.0 * dim;
-    gm->im = 8.0 * mim;
+  sum.finish(g.sg, M::kInv, 1.0, 0.0, false, out);
+}
+
+// Rule variants of the kernels: the Duffy orders 2 .. 6, else the general sums
+// in chunks of 4 or 7 x-points.
+constexpr int kRule4 = 14, kRule7 = 17;
+
+// Operands of entry (rl, cl) of the staged sub-tile.
+template <int LAYER, bool MIXED>
+__device__ __forceinline__ EntryGeo entry_geo(const Lds &l, int TR, int TC, int rl, int cl) {
+  EntryGeo g;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    g.V[c] = l.rg[(R_V + c) * TR + rl];
+    if (MIXED) g.V[c] -= l.cg[c * TC + cl];  // relative to the column triangle's first vertex
+    g.A[c] = l.rg[(R_A + c) * TR + rl];
+    g.B[c] = l.rg[(R_B + c) * TR + rl];
+    g.n[c] = LAYER == BEM_SLP ? 0.0 : l.cn[c * TC + cl];
+    g.m[c] = LAYER == kBoth ? l.rn[c * TR + rl] : 0.0;
+    g.cen[c] = l.cc[c * TC + cl];
+    if (MIXED) g.cen[c] -= l.cg[c * TC + cl];
+  }
+  g.yn = LAYER == BEM_SLP || MIXED ? 0.0 : l.cn[3 * TC + cl];
+  g.sg = l.rg[R_SG * TR + rl];
+  g.c1 = l.rg[R_C1 * TR + rl];
+  g.k0 = l.rg[R_K0 * TR + rl];
+  g.a22 = l.rg[R_A22 * TR + rl];
+  return g;
+}
+
+// All sums of regular entry (rl, cl), FP64 or (mixed) FP32.  Helmholtz: the
+// short phases if both triangles allow them (kappa times the distance of a
+// triangle's points from its centroid at most 1/2, see short_phase): a
+// decision of the entry alone, so that its value does not depend on the
+// kernel, sub-tile or wave that computes it.
+template <int KERNEL, int LAYER, int RULE, bool MIXED>
+__device__ __forceinline__ void regular_sums(const Lds &l, int TR, int TC, int nqp, int rl, int cl,
+                                             const double *table, double kappa, Sums<KERNEL> *o) {
+  const EntryGeo g = entry_geo<LAYER, MIXED>(l, TR, TC, rl, cl);
+  typedef typename std::conditional<MIXED, float, double>::type T;
+  typename std::conditional<MIXED, PointsLds32, PointsLds64>::type pts;
+  if constexpr (MIXED) {
+    pts.p = reinterpret_cast<const float4 *>(l.ys) + cl;
+    pts.stride = TC;
+  } else {
+    pts.p = reinterpret_cast<const double2 *>(l.ys) + 2 * cl;
+    pts.stride = 2 * TC;
+  }
+  if constexpr (RULE >= kRule4) {
+    general_sums<KERNEL, LAYER, RULE - 10, T>(g, l.rule, nqp, kappa, pts, o);
+  } else if constexpr (KERNEL == BEM_LAPLACE) {
+    duffy_sums<KERNEL, LAYER, RULE, false, T>(g, table, kappa, pts, o);
+  } else {
+    if (l.rs[rl] & l.cs[cl]) duffy_sums<KERNEL, LAYER, RULE, true, T>(g, table, kappa, pts, o);
+    else duffy_sums<KERNEL, LAYER, RULE, false, T>(g, table, kappa, pts, o);
   }
 }
 

@@ -1,0 +1,4 @@
+// Block kernels: Helmholtz, plain FP64.
+#include "bem_block_kernels.h"
+
+template struct bem::BlockLaunch<BEM_HELMHOLTZ, false>;

@@ -101,6 +101,39 @@ __device__ __forceinline__ void sincos_cw_f32(float x, float *s, float *c) {
   *c = __int_as_float(__float_as_int(cr) ^ sgn);
 }
 
+// Sine and cosine of a phase |x| <= 1/2 relative to a reference distance, no
+// reduction: sin x = x + x^3 P(x^2), cos x = 1 - x^2 / 2 + x^4 Q(x^2), P and Q
+// from the same construction on [0, 1/4] (below 2.5e-17 relative and 2.6e-19
+// absolute; FP32 5.4e-10 and 2.0e-9): 13 instructions (FP32 8) where the
+// reduction by pi and its polynomials take 28 (20).
+__device__ __forceinline__ void short_phase(double x, double *s, double *c) {
+  const double r2 = x * x;
+  double ps = -0x1.ac5c1605a3a89p-26;
+  ps = fma(ps, r2, 0x1.71dd1cae1263ap-19);
+  ps = fma(ps, r2, -0x1.a01a011194a79p-13);
+  ps = fma(ps, r2, 0x1.11111110f201bp-7);
+  ps = fma(ps, r2, -0x1.55555555554c8p-3);
+  *s = fma(x * r2, ps, x);
+  double pc = 0x1.1da5f6afdc0e5p-29;
+  pc = fma(pc, r2, -0x1.27e4301a437b0p-22);
+  pc = fma(pc, r2, 0x1.a01a0128eddeap-16);
+  pc = fma(pc, r2, -0x1.6c16c16bf658fp-10);
+  pc = fma(pc, r2, 0x1.55555555554efp-5);
+  pc = fma(pc, r2, -0.5);
+  *c = fma(r2, pc, 1.0);
+}
+__device__ __forceinline__ void short_phase_f32(float x, float *s, float *c) {
+  const float r2 = x * x;
+  float ps = -0x1.9d5406p-13f;
+  ps = fmaf(ps, r2, 0x1.110f74p-7f);
+  ps = fmaf(ps, r2, -0x1.555554p-3f);
+  *s = fmaf(x * r2, ps, x);
+  float pc = -0x1.699072p-10f;
+  pc = fmaf(pc, r2, 0x1.555376p-5f);
+  pc = fmaf(pc, r2, -0.5f);
+  *c = fmaf(r2, pc, 1.0f);
+}
+
 template <int KERNEL>
 struct Acc;
 template <>

@@ -25,6 +25,8 @@ struct TriRule {
   std::vector<double> s, t, w;
 };
 TriRule triangle_rule(int rule, int q);
+// Constants of the Duffy rule of order q in the block kernels' layout (DuffyAt).
+std::vector<double> duffy_table(int q);
 
 // Sauter-Schwab rule of one singular class, factored as (x^, y^) = xi g(eta):
 // per region and (eta1, eta2, eta3) Gauss triple the map g at xi = 1
@@ -76,6 +78,8 @@ struct DevRules {
   double *mem = nullptr;
   int nq = 0;                   // points per triangle (regular rule)
   const double *tri = nullptr;  // [3][nq]: s, t, w
+  // Duffy rules of orders 2 .. 6: duffy_table in double and in float (else null)
+  const double *duffy = nullptr, *duffy32 = nullptr;
   // Sauter-Schwab eta tables per class 1..3 (piecewise-linear bases)
   int np[4] = {0, 0, 0, 0};
   const double *ss[4] = {nullptr, nullptr, nullptr, nullptr};  // [5][np]: xs, xt, ys, yt, w
@@ -120,6 +124,7 @@ struct BlockArgs {
   void *out2;          // both layers in one pass: the double layer's output
   int64_t out_len;
   const double *rule;  // [3][nq]
+  const double *duffy;  // DevRules::duffy, mixed form duffy32 (float)
   int32_t nq, nq_pad;
   int32_t tr, tc;      // sub-tile rows / columns
   SSArgs ss;
@@ -304,6 +309,7 @@ struct SelectArgs {
 // 2 .. q_max (index = order) and the order map (one byte per output entry).
 struct OrderRules {
   const double *rule[BEM_MAX_ORDER + 1];
+  const double *duffy[BEM_MAX_ORDER + 1];
   int32_t nq[BEM_MAX_ORDER + 1];
   const int8_t *orders;
   int32_t q_max;
@@ -324,15 +330,12 @@ hipError_t launch_mlp_forward(bool f16, int n_out, const float *P, const void *p
                               const float *x, float *y, hipStream_t s);
 hipError_t launch_selector_samples(int kernel, int layer, const SampleArgs &a, hipStream_t s);
 hipError_t launch_select_orders(const SelectArgs &a, int grid, hipStream_t s);
-// x-points per register chunk of the learned kernel for order q
-int learned_chunk(int q, int kernel);
 hipError_t launch_blocks_learned(int kernel, int layer, const BlockArgs &a, const OrderRules &o,
                                  size_t lds_bytes, hipStream_t s);
 
-// xc: x-points per register chunk (4, 5, 7, 8 or 9; nq_pad of every batch
-// entry is nq rounded up to a multiple of it); the layer of each entry is in
+// rule: rule_variant of the plan's rule; the layer of each entry is in
 // PersistentArgs::mode, its sub-tile shape in its BlockArgs
-hipError_t launch_persistent(int kernel, bool mixed, int xc, const PersistentArgs &p,
+hipError_t launch_persistent(int kernel, bool mixed, int rule, const PersistentArgs &p,
                              size_t lds_bytes, hipStream_t s);
 hipError_t launch_reset_counter(int32_t *counter, hipStream_t s);
 
@@ -346,12 +349,10 @@ hipError_t launch_pivot_inverse(bool cplx, const PivInvArgs &a, hipStream_t s);
 hipError_t noalloc_scratch(int device, double **ptr);
 hipError_t launch_geometry(const bem_mesh &m, double *geo, int64_t ldg, unsigned *flags,
                            hipStream_t s);
-hipError_t launch_blocks(int kernel, int layer, bool coupling, bool mixed, const BlockArgs &a,
-                         size_t lds_bytes, hipStream_t s);
-// near field of the single and the double layer in one pass (a.out: single
-// layer, a.out2: double layer; plain FP64 or the mixed form)
-hipError_t launch_blocks_both(int kernel, bool mixed, const BlockArgs &a, size_t lds_bytes,
-                              hipStream_t s);
+// layer: BEM_SLP, BEM_DLP or 2, the near field of both layers in one pass
+// (a.out: single layer, a.out2: double layer); rule: rule_variant
+hipError_t launch_blocks(int kernel, int layer, int rule, bool coupling, bool mixed,
+                         const BlockArgs &a, size_t lds_bytes, hipStream_t s);
 hipError_t launch_entries(int kernel, int layer, bool mixed, const EntryArgs &a, hipStream_t s);
 // sub-tile shape (rows, columns) and LDS bytes of the block kernel for a
 // padded rule size within an LDS budget; false if nothing fits
@@ -359,7 +360,10 @@ bool block_tile_shape(int nq_pad, bool mixed, size_t lds_budget, int *tr, int *t
                       size_t *lds_bytes, bool coupling = false, bool both = false);
 size_t block_lds_bytes(int nq_pad, int tr, int tc, bool mixed, bool lists = true,
                        bool both = false);
-int rule_chunk(int nq, int kernel);  // x-points per register chunk
+int rule_chunk(int nq, int kernel);
+// kernel variant of a rule (regular_rule, order, points) and its padded points
+int rule_variant(int regular_rule, int q, int nq);
+int rule_pad(int variant, int nq);
 
 }  // namespace bem
 

@@ -265,7 +265,7 @@ int bem_assemble_nearfield_learned(bem_ctx *ctx, const bem_mesh *mesh, const bem
   hipError_t e = launch_geometry(*mesh, ctx->geo, ldg, ctx->flags, s);
   if (e != hipSuccess) return hip_fail(ctx, e, "geometry kernel launch");
   OrderRules o{};
-  for (int q = 2; q <= op->q_regular; ++q) o.rule[q] = r[q]->tri, o.nq[q] = r[q]->nq;
+  for (int q = 2; q <= op->q_regular; ++q) o.rule[q] = r[q]->tri, o.duffy[q] = r[q]->duffy, o.nq[q] = r[q]->nq;
   o.orders = orders;
   o.q_max = op->q_regular;
   const DevRules *plain = r[op->q_regular];
@@ -288,9 +288,7 @@ int bem_assemble_nearfield_learned(bem_ctx *ctx, const bem_mesh *mesh, const bem
   a.out_len = out_len;
   a.rule = plain->tri;
   a.nq = plain->nq;
-  // LDS sized for the largest order (q^2 points are a multiple of its chunk)
-  const int xc = learned_chunk(op->q_regular, op->kernel);
-  a.nq_pad = (plain->nq + xc - 1) / xc * xc;
+  a.nq_pad = plain->nq;  // LDS sized for the largest order
   size_t lds;
   if (!block_tile_shape(a.nq_pad, false, ctx->lds_budget, &a.tr, &a.tc, &lds))
     return fail(ctx, BEM_EUNSUPPORTED, "quadrature order too high for the LDS budget");

@@ -1,0 +1,4 @@
+// Persistent batched kernel: Laplace, plain FP64.
+#include "bem_block_kernels.h"
+
+template struct bem::PersistentLaunch<BEM_LAPLACE, false>;

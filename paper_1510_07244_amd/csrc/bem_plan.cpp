@@ -33,6 +33,7 @@ struct bem_plan {
   int kernel = 0;
   bool mixed = false;
   int32_t nq = 0;
+  int rule = 0;  // kernel variant of the rule (rule_variant)
   size_t lds = 0;
   bem_tune cfg{};
   int32_t nbatch = 0;
@@ -80,8 +81,8 @@ hipError_t d2h(std::vector<T> *dst, const T *src, int64_t n) {
 // 8 k q_s^3 (measured on the near field of the 8192-triangle sphere, the
 // singular pass takes about 1/6 of the launch for 1/40 of its flops).  The
 // other layers scale the regular part by their issue slots per point pair
-// over the single layer's (Laplace 12 : 14 : 16 for single, double, both in
-// one pass; Helmholtz, with the sine and cosine, about 36 : 41 : 46) and the
+// over the single layer's (Laplace 10.3 : 12.8 : 15.2 for single, double, both
+// in one pass; Helmholtz, with the sine and cosine, about 28 : 34 : 43) and the
 // singular part by the Sauter-Schwab evaluations per pair (1, 1, 2.5: both
 // layers of (i, j), the double layer of (j, i)).
 struct CostModel {
@@ -91,8 +92,8 @@ struct CostModel {
 };
 
 void layer_weights(int kernel, int layer, double *reg_w, double *sing_w) {
-  static const double lap[3] = {1.0, 14.0 / 12.0, 16.0 / 12.0};
-  static const double hel[3] = {1.0, 41.0 / 36.0, 46.0 / 36.0};
+  static const double lap[3] = {1.0, 12.8 / 10.3, 15.2 / 10.3};
+  static const double hel[3] = {1.0, 34.0 / 28.0, 43.0 / 28.0};
   *reg_w = (kernel == BEM_LAPLACE ? lap : hel)[layer];
   *sing_w = layer == kLayerBoth ? 2.5 : 1.0;
 }
@@ -368,6 +369,7 @@ int bem_plan_batched(bem_ctx *ctx, const bem_op *op, int32_t nbatch, const bem_b
     }
     if ((rc = get_rules(ctx, op, &rules))) return bail(rc);
     p->nq = rules->nq;
+    p->rule = rule_variant(op->regular_rule, op->q_regular, p->nq);
     // geometry slices
     int64_t total = 0;
     for (const bem_mesh &m : p->meshes) {
@@ -400,16 +402,9 @@ int bem_plan_batched(bem_ctx *ctx, const bem_op *op, int32_t nbatch, const bem_b
   if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess ||
       ncu <= 0)
     ncu = 256;
-  const int def_xc = rule_chunk(p->nq, p->kernel);
-  std::vector<int> xcs;
-  if (want.x_chunk) {
-    xcs.push_back(want.x_chunk);
-  } else {
-    xcs.push_back(def_xc);
-    if (want.autotune)
-      for (int x : {8, 9, 7, 5, 4})
-        if (x != def_xc && p->nq % x == 0) xcs.push_back(x);
-  }
+  // the kernels choose their own register chunk: the field is only reported
+  const int xc = want.x_chunk ? want.x_chunk : rule_chunk(p->nq, p->kernel);
+  const int nqp = rule_pad(p->rule, p->nq);
   // sub-tiles: the lists with pair lists (near field; all in the mixed form)
   // take the candidate's shape, plain coupling lists the coupling kernel's
   bool any_lists = false, any_plain_coupling = false;
@@ -421,7 +416,6 @@ int bem_plan_batched(bem_ctx *ctx, const bem_op *op, int32_t nbatch, const bem_b
   auto make_cand = [&](int grid, int tr, int tc, int xc, bool whole) {
     Candidate c{grid, tr, tc, xc, whole, 0, 0};
     if (any_plain_coupling) {
-      const int nqp = (p->nq + xc - 1) / xc * xc;
       size_t lds;
       if (!block_tile_shape(nqp, false, ctx->lds_budget, &c.ctr, &c.ctc, &lds, true, false))
         c.ctr = c.ctc = 0;
@@ -436,7 +430,6 @@ int bem_plan_batched(bem_ctx *ctx, const bem_op *op, int32_t nbatch, const bem_b
   };
   // LDS of the launch: the largest layout of its batch entries (0: no entry)
   auto plan_lds = [&](const Candidate &c) -> size_t {
-    const int nqp = (p->nq + c.xc - 1) / c.xc * c.xc;
     size_t m = 0;
     for (const HostBatch &hb : hbs) {
       const bool l = has_lists(hb);
@@ -451,8 +444,7 @@ int bem_plan_batched(bem_ctx *ctx, const bem_op *op, int32_t nbatch, const bem_b
   bool any_both = false;
   for (const HostBatch &hb : hbs) any_both = any_both || hb.layer == kLayerBoth;
   std::vector<Candidate> cands;
-  for (int xc : xcs) {
-    const int nqp = (p->nq + xc - 1) / xc * xc;
+  {
     std::vector<std::pair<int, int>> shapes;
     if (want.tile_rows && want.tile_cols) {
       shapes.push_back({want.tile_rows, want.tile_cols});
@@ -497,7 +489,6 @@ int bem_plan_batched(bem_ctx *ctx, const bem_op *op, int32_t nbatch, const bem_b
     auto key = std::make_tuple(c.tr, c.tc, c.whole, c.ctr, c.ctc);
     auto it = tile_sets.find(key);
     if (it == tile_sets.end()) {
-      const int nqp = (p->nq + def_xc - 1) / def_xc * def_xc;
       it = tile_sets.emplace(key, build_tiles(hbs, tris, p->meshes, shapes_of(c), p->kernel, nqp,
                                               op->q_singular, c.whole)).first;
     }
@@ -546,7 +537,8 @@ int bem_plan_batched(bem_ctx *ctx, const bem_op *op, int32_t nbatch, const bem_b
       a.out_len = hb.out_len;
       a.rule = rules->tri;
       a.nq = rules->nq;
-      a.nq_pad = (rules->nq + c.xc - 1) / c.xc * c.xc;
+      a.duffy = p->mixed ? rules->duffy32 : rules->duffy;
+      a.nq_pad = nqp;
       a.tr = sh[k].first;
       a.tc = sh[k].second;
       a.ss = ss_args(*rules);
@@ -569,9 +561,9 @@ int bem_plan_batched(bem_ctx *ctx, const bem_op *op, int32_t nbatch, const bem_b
     p->lds = plan_lds(c);
     return BEM_OK;
   };
-  auto enqueue = [&](const PersistentArgs &pa, int xc, hipStream_t st) -> hipError_t {
+  auto enqueue = [&](const PersistentArgs &pa, hipStream_t st) -> hipError_t {
     hipError_t e = launch_reset_counter(p->counter, st);
-    if (e == hipSuccess) e = launch_persistent(p->kernel, p->mixed, xc, pa, p->lds, st);
+    if (e == hipSuccess) e = launch_persistent(p->kernel, p->mixed, p->rule, pa, p->lds, st);
     return e;
   };
 
@@ -602,8 +594,7 @@ int bem_plan_batched(bem_ctx *ctx, const bem_op *op, int32_t nbatch, const bem_b
   bem_tune cached{};
   bool hit = want.autotune && cache_lookup(cache_path, key, &cached);
   if (hit) {
-    const int nqp = valid_chunk(cached.x_chunk) ? (p->nq + cached.x_chunk - 1) / cached.x_chunk * cached.x_chunk : 0;
-    hit = nqp > 0 && p->nq % cached.x_chunk == 0 && cached.grid > 0 && cached.tile_rows >= 1 &&
+    hit = valid_chunk(cached.x_chunk) && p->nq % cached.x_chunk == 0 && cached.grid > 0 && cached.tile_rows >= 1 &&
           cached.tile_rows <= 64 && cached.tile_cols >= 1 && cached.tile_cols <= 64;
     hit = hit && (cached.granularity == 1 || cached.granularity == 2) &&
           (want.granularity == 0 || want.granularity == cached.granularity);
@@ -625,11 +616,11 @@ int bem_plan_batched(bem_ctx *ctx, const bem_op *op, int32_t nbatch, const bem_b
       PersistentArgs pa{};
       int r0 = stage(c, &pa);
       if (r0) return r0;
-      hipError_t e = warm ? enqueue(pa, c.xc, s) : hipSuccess;
+      hipError_t e = warm ? enqueue(pa, s) : hipSuccess;
       float ms = 0.f, mn = 1e30f;
       for (int r = 0; r < reps && e == hipSuccess; ++r) {
         e = hipEventRecord(t0, s);
-        if (e == hipSuccess) e = enqueue(pa, c.xc, s);
+        if (e == hipSuccess) e = enqueue(pa, s);
         if (e == hipSuccess) e = hipEventRecord(t1, s);
         if (e == hipSuccess) e = hipEventSynchronize(t1);
         if (e == hipSuccess) e = hipEventElapsedTime(&ms, t0, t1);
@@ -688,7 +679,7 @@ int bem_plan_batched(bem_ctx *ctx, const bem_op *op, int32_t nbatch, const bem_b
   for (size_t q = 0; q < p->meshes.size() && le == hipSuccess; ++q)
     le = launch_geometry(p->meshes[q], p->geo + p->geo_off[q], p->geo_ld[q], ctx->flags, p->cap);
   if (le == hipSuccess)
-    le = launch_persistent(p->kernel, p->mixed, best.xc, pa, p->lds, p->cap);
+    le = launch_persistent(p->kernel, p->mixed, p->rule, pa, p->lds, p->cap);
   e = hipStreamEndCapture(p->cap, &p->graph);
   if (le != hipSuccess) return bail(hip_fail(ctx, le, "kernel launch under capture"));
   if (e != hipSuccess) return bail(hip_fail(ctx, e, "hipStreamEndCapture"));

@@ -81,6 +81,25 @@ TriRule triangle_rule(int rule, int q) {
   return r;
 }
 
+std::vector<double> duffy_table(int q) {
+  std::vector<double> x(q), w(q), t;
+  gauss_legendre01(q, x.data(), w.data());
+  const int H = q / 2, HC = (q + 1) / 2;
+  // eta pairs 1/2 +- delta from the outermost, then the centre
+  auto delta = [&](int k) { return 0.5 * (x[q - 1 - k] - x[k]); };
+  for (int j = 0; j < q; ++j)
+    t.insert(t.end(), {x[j], x[j] * x[j], w[j] * x[j], w[j] * x[j] * x[j]});
+  for (int k = 0; k < H; ++k) t.push_back(delta(k));
+  for (int k = 0; k < H; ++k) t.push_back(delta(k) * delta(k));
+  for (int k = 0; k < HC; ++k) t.push_back(w[k]);
+  for (int k = 0; k < H; ++k) t.push_back(w[k] * delta(k));
+  for (int j = 0; j < q; ++j)
+    for (int k = 0; k < H; ++k) t.push_back(x[j] * delta(k));
+  for (int j = 0; j < q; ++j)
+    for (int k = 0; k < HC; ++k) t.push_back(w[j] * x[j] * w[k]);
+  return t;
+}
+
 // One point of a Sauter-Schwab region: returns (x^1, x^2, y^1, y^2) and the
 // Jacobian of the region map at (xi, h1, h2, h3) in [0,1]^4.  The maps send
 // [0,1]^4 onto a piece of {0 <= x2 <= x1 <= 1}^2 such that the pieces of one

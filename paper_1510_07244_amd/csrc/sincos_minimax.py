@@ -19,11 +19,16 @@ for quantities of the size of the error, not of the coefficients -- on t in
 script to print the coefficients as hexadecimal floats;
 tests/test_host_sincos.py checks the header's against this construction's
 error bounds.
+
+short_phase (|r| <= 1/2, no reduction: phases relative to a reference
+distance) has its own polynomials, T = 1/4: FP64 P and Q of degree 4, FP32 P
+of degree 2 and Q of degree 1.
 """
 import numpy as np
 
 L = np.longdouble
 T = L(np.pi / 2) ** 2
+T_SHORT = L(0.25)
 
 
 def _fact(n):
@@ -118,7 +123,7 @@ def _remez(fun, weight, a, b, deg, iters=25, npts=20001):
     return c, abs(float(E))
 
 
-def coefficients(kind, deg):
+def coefficients(kind, deg, T=T):
     """Long-double coefficients (lowest first) of P (kind 'sin') or Q
     ('cos') of degree deg, and the levelled weighted error."""
     if kind == "sin":
@@ -133,7 +138,7 @@ def coefficients(kind, deg):
     return [a + b for a, b in zip(taylor, d)], E
 
 
-def max_rel_error(kind, coefs, npts=200001):
+def max_rel_error(kind, coefs, npts=200001, T=T):
     """Largest error over t in [0, T] of the polynomial with the given
     (rounded) coefficients, in long double: relative to sin r for the sine,
     absolute for the cosine."""
@@ -147,9 +152,11 @@ def max_rel_error(kind, coefs, npts=200001):
 
 
 if __name__ == "__main__":
-    for kind, deg, typ in (("sin", 7, np.float64), ("cos", 6, np.float64),
-                           ("sin", 3, np.float32), ("cos", 3, np.float32)):
-        c, E = coefficients(kind, deg)
+    for kind, deg, typ, lim in (("sin", 7, np.float64, T), ("cos", 6, np.float64, T),
+                                ("sin", 3, np.float32, T), ("cos", 3, np.float32, T),
+                                ("sin", 4, np.float64, T_SHORT), ("cos", 4, np.float64, T_SHORT),
+                                ("sin", 2, np.float32, T_SHORT), ("cos", 1, np.float32, T_SHORT)):
+        c, E = coefficients(kind, deg, lim)
         r = [typ(x) for x in c]
-        print(kind, typ.__name__, "levelled", E, "rounded", max_rel_error(kind, r))
+        print(kind, typ.__name__, float(lim), "levelled", E, "rounded", max_rel_error(kind, r, T=lim))
         print("   ", [float(x).hex() for x in r])
