@@ -40,11 +40,7 @@ struct Num<false> {
   __device__ static Num load(const double *p, int64_t k) { Num r; r.v = p[k]; return r; }
   __device__ void add_to(double *p, int64_t k) const { p[k] += v; }
   __device__ void add(const Num &o) { v += o.v; }
-  __device__ Num shfl_down_sum() const {
-    Num r = *this;
-    for (int o = kWave / 2; o >= 1; o >>= 1) r.v += __shfl_xor(r.v, o, kWave);
-    return r;
-  }
+  __device__ Num xor_lane(int o) const { Num r; r.v = __shfl_xor(v, o, kWave); return r; }
   // the value of lane k (k uniform across the wave)
   __device__ Num lane(int k) const { Num r; r.v = read_lane(v, k); return r; }
 };
@@ -69,12 +65,10 @@ struct Num<true> {
     p[2 * k + 1] += im;
   }
   __device__ void add(const Num &o) { re += o.re, im += o.im; }
-  __device__ Num shfl_down_sum() const {
-    Num r = *this;
-    for (int o = kWave / 2; o >= 1; o >>= 1) {
-      r.re += __shfl_xor(r.re, o, kWave);
-      r.im += __shfl_xor(r.im, o, kWave);
-    }
+  __device__ Num xor_lane(int o) const {
+    Num r;
+    r.re = __shfl_xor(re, o, kWave);
+    r.im = __shfl_xor(im, o, kWave);
     return r;
   }
   __device__ Num lane(int k) const {
@@ -87,188 +81,213 @@ struct Num<true> {
 
 // Group g: y[out_idx[out_ptr[g] ..]] += sum_{b in group g} op(A_b) x[in_idx[in_ptr[b] ..]],
 // op(A) = A (TRANS false; A is m_out x n_in) or A^T (TRANS true; A is
-// n_in x m_out), column-major with the row count as leading dimension.  One
-// workgroup of eight waves per group.  The group's work is cut into panels
-// -- kPanel input columns of a block (TRANS false) or kPanel output columns
-// (TRANS true), 16 real or 8 complex -- dealt to the waves in turn, so that a
-// group of one small block still keeps every wave busy; a wave issues the
-// loads of a panel before it uses them, since a product reads every matrix
-// entry once and waits on memory.  TRANS false: lane l takes output rows
-// l + 64 c of R consecutive chunks c in one pass (R = 2 when the group has
-// more than 64 outputs: a coupling block of rank 65 .. 128 is one pass of
-// 2 kPanel loads in flight per wave, not two passes of which the second
-// runs with a few lanes); the panel's inputs are gathered one per lane and
-// broadcast.  TRANS true: lane l takes input row l + 64 c, runs along the
-// panel's columns and the wave adds each column's products up.  The waves'
-// partial sums are added in wave order at the end: every sum runs in a
-// fixed order, so results are reproducible bit for bit.
-constexpr int kGemvThreads = 512;  // eight waves per group: more loads in flight
+// n_in x m_out), column-major with the row count as leading dimension.
+//
+// A level of the nested basis has few groups of small blocks (13 to 182 for
+// 8192 triangles), so a launch is bound by the latency of one workgroup's
+// chain (offsets -> indices -> inputs, matrix entries) and by how many
+// workgroups share the matrices, not by bandwidth.  A group's outputs are
+// therefore spread over gridDim.y workgroups, which need nothing from each
+// other: 64 output rows each (TRANS false, one line of 512 bytes per column) or one panel of kPanel
+// output columns (TRANS true).  Within a
+// workgroup the waves take the group's work in turn -- panels of kPanel input
+// columns, resp. 64-row pieces of the blocks -- each issuing a panel's loads
+// before it uses them, and their partial sums are added in wave order: every
+// sum runs in a fixed order, so results are reproducible bit for bit.
+// One product of the 8192-triangle single layer (224 MB, graph replay, every
+// matrix from HBM): 230 us with one workgroup per group, its rows in two passes
+// and six shuffles per column -> 157 us; the transposed levels 10 .. 13 -> 6 ..
+// 9 us each, the coupling 56 -> 43 us (3.2 TB/s).  Tried: pieces of 32 rows or
+// of 128 with 16-byte loads (coupling 62 and 53 us), eight waves (164 us),
+// the blocks' list entries loaded 64 at a time (159 us).
+constexpr int kGemvThreads = 1024;
+constexpr int kGemvWaves = kGemvThreads / kWave;
+template <bool CPLX>
+constexpr int kPanel = CPLX ? 8 : 16;
 
-// TRANS false: this wave's panels of the group's blocks for the output rows
-// of chunks c0 .. c0 + R - 1, into pw (the wave's row of partial sums).
-template <bool CPLX, int R>
-__device__ __forceinline__ void gemv_rows(const GemvArgs &a, int64_t m, int64_t b0, int64_t b1,
-                                          int c0, int wave, int lane, Num<CPLX> *pw) {
-  using T = Num<CPLX>;
-  constexpr int kPanel = CPLX ? 8 : 16;
-  constexpr int W = kGemvThreads / kWave;
-  const double *A = static_cast<const double *>(a.A);
-  const double *x = static_cast<const double *>(a.x);
-  T acc[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) acc[r] = T::zero();
-  int64_t task = 0;  // panels of the group's blocks so far
-  for (int64_t b = b0; b < b1; ++b) {
-    const int64_t i0 = a.in_ptr[b], i1 = a.in_ptr[b + 1], off = a.a_off[b];
-    const int64_t n = i1 - i0;
-    const int64_t np = (n + kPanel - 1) / kPanel;
-    int64_t p = ((wave - task) % W + W) % W;  // this wave's first panel of block b
-    task += np;
-    if (p >= np) continue;
-    if (!(i0 >= 0 && i0 <= i1 && i1 <= a.in_len && n <= kMaxVec && off >= 0 && off <= a.a_len &&
-          (m == 0 || n <= (a.a_len - off) / m))) {
-      if (lane == 0 && c0 == 0) atomicOr(a.flags, FLAG_EINVAL);
-      continue;  // uniform in the wave
-    }
-    // the panel's inputs, one per lane (gathered one panel ahead, so that
-    // the gather overlaps the current panel's matrix loads)
-    auto gather = [&](int64_t q) {
-      T v = T::zero();
-      const int64_t j = q * kPanel + lane;
-      if (lane < kPanel && j < n) {
-        const int id = a.in_idx[i0 + j];
-        if (id >= 0 && id < a.x_len) v = T::load(x, id);
-        else if (c0 == 0) atomicOr(a.flags, FLAG_EINVAL);
-      }
-      return v;
-    };
-    T xl = gather(p);
-    for (; p < np; p += W) {
-      const int64_t j0 = p * kPanel;
-      const int jn = (int)min((int64_t)kPanel, n - j0);
-      // the panel's first column at a uniform address, the rest by 32-bit
-      // offsets (m, n <= 512)
-      const double *P = A + (CPLX ? 2 : 1) * (off + m * j0);
-      const int mi = (int)m;
-      T av[R][kPanel];
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int i = lane + kWave * (c0 + r);
-        const bool in = i < mi;
-#pragma unroll
-        for (int u = 0; u < kPanel; ++u)
-          av[r][u] = in && u < jn ? T::load(P, i + mi * u) : T::zero();
-      }
-      const T xn = p + W < np ? gather(p + W) : T::zero();
-#pragma unroll
-      for (int u = 0; u < kPanel; ++u) {
-        const T xu = xl.lane(u);
-#pragma unroll
-        for (int r = 0; r < R; ++r) acc[r].fma(av[r][u], xu);
-      }
-      xl = xn;
-    }
+// element k of a list the kernel only reads, k uniform: a scalar load
+__device__ __forceinline__ int64_t list_at(const int32_t *p, int64_t k) {
+  return ((const int32_t __attribute__((address_space(4))) *)p)[k];
+}
+__device__ __forceinline__ int64_t list_at(const int64_t *p, int64_t k) {
+  return ((const int64_t __attribute__((address_space(4))) *)p)[k];
+}
+
+struct GemvGroup {
+  int64_t o0, b0, b1;
+  int m;
+};
+
+// Offsets of group g; false (and the flag) if they are invalid.  Uniform.
+__device__ __forceinline__ bool gemv_group(const GemvArgs &a, int g, GemvGroup *r) {
+  const int64_t o0 = list_at(a.out_ptr, g), o1 = list_at(a.out_ptr, g + 1);
+  r->o0 = o0;
+  r->b0 = list_at(a.grp_ptr, g), r->b1 = list_at(a.grp_ptr, g + 1);
+  if (o0 >= 0 && o0 <= o1 && o1 <= a.out_len && o1 - o0 <= kMaxVec && r->b0 >= 0 &&
+      r->b0 <= r->b1 && r->b1 <= a.nblocks) {
+    r->m = (int)(o1 - o0);
+    return true;
   }
+  if (threadIdx.x == 0) atomicOr(a.flags, FLAG_EINVAL);
+  return false;
+}
+
+// Input range and matrix of block b with m output rows / columns; false (and
+// the flag) if they are invalid.  Uniform in a wave.
+struct GemvBlock {
+  int64_t i0, off;
+  int n;
+};
+__device__ __forceinline__ bool gemv_block(const GemvArgs &a, int64_t b, int m, int lane,
+                                           GemvBlock *r) {
+  const int64_t i0 = list_at(a.in_ptr, b), i1 = list_at(a.in_ptr, b + 1), off = list_at(a.a_off, b);
+  const int64_t n = i1 - i0;
+  r->i0 = i0, r->off = off;
+  if (i0 >= 0 && i0 <= i1 && i1 <= a.in_len && n <= kMaxVec && off >= 0 && off <= a.a_len &&
+      (m == 0 || n <= (a.a_len - off) / m)) {
+    r->n = (int)n;
+    return true;
+  }
+  if (lane == 0) atomicOr(a.flags, FLAG_EINVAL);
+  return false;
+}
+
+template <bool CPLX>
+__device__ __forceinline__ Num<CPLX> gemv_input(const GemvArgs &a, int64_t k, bool in) {
+  Num<CPLX> v = Num<CPLX>::zero();
+  if (in) {
+    const int id = a.in_idx[k];
+    if (id >= 0 && id < a.x_len) v = Num<CPLX>::load(static_cast<const double *>(a.x), id);
+    else atomicOr(a.flags, FLAG_EINVAL);
+  }
+  return v;
+}
+
+// entry k of the matrix at the wave-uniform address base: scalar base and a
+// 32-bit byte offset (m, n <= 512), half the address registers of 64-bit ones
+template <bool CPLX>
+__device__ __forceinline__ Num<CPLX> load_entry(const double *base, int k) {
+  const uint32_t off = (uint32_t)k * (CPLX ? 16u : 8u);
+  return Num<CPLX>::load(reinterpret_cast<const double *>(reinterpret_cast<const char *>(base) + off), 0);
+}
+
+template <bool CPLX>
+__device__ __forceinline__ void gemv_add(const GemvArgs &a, int64_t k, const Num<CPLX> &v) {
+  const int id = a.out_idx[k];
+  if (id < 0 || id >= a.y_len) atomicOr(a.flags, FLAG_EINVAL);
+  else v.add_to(static_cast<double *>(a.y), id);
+}
+
+// TRANS false: lane l takes output row l of a 64-row piece; the inputs of a
+// panel are gathered one per lane, one panel ahead, and broadcast.
+template <bool CPLX>
+__global__ __launch_bounds__(kGemvThreads) void k_gemv(const GemvArgs a) {
+  using T = Num<CPLX>;
+  constexpr int P = kPanel<CPLX>;
+  __shared__ T part[kGemvWaves][kWave];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  GemvGroup gr;
+  if (!gemv_group(a, blockIdx.x, &gr)) return;
+  const int m = gr.m;
+  for (int r0 = blockIdx.y * kWave; r0 < m; r0 += gridDim.y * kWave) {  // uniform
+    const int row = r0 + lane;
+    T acc = T::zero();
+    int64_t task = 0;  // panels of the group's blocks so far
+    for (int64_t b = gr.b0; b < gr.b1; ++b) {
+      GemvBlock bl;
+      const int64_t len = list_at(a.in_ptr, b + 1) - list_at(a.in_ptr, b);
+      const int64_t np = (len + P - 1) / P;
+      int64_t p = ((wave - task) % kGemvWaves + kGemvWaves) % kGemvWaves;  // first panel of block b
+      task += np;
+      if (p >= np || !gemv_block(a, b, m, lane, &bl)) continue;  // uniform in the wave
+      T xl = gemv_input<CPLX>(a, bl.i0 + p * P + lane, lane < P && p * P + lane < bl.n);
+      for (; p < np; p += kGemvWaves) {
+        const int jn = min(P, bl.n - (int)p * P);
+        const double *C = static_cast<const double *>(a.A) + (CPLX ? 2 : 1) * (bl.off + (int64_t)m * (p * P));
+        T av[P];
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int64_t i = lane + kWave * (int64_t)(c0 + r);
-    if (i < m) pw[i] = acc[r];
+        for (int u = 0; u < P; ++u) av[u] = row < m && u < jn ? load_entry<CPLX>(C, row + m * u) : T::zero();
+        const int64_t pn = p + kGemvWaves;
+        const T xn = gemv_input<CPLX>(a, bl.i0 + pn * P + lane, lane < P && pn * P + lane < bl.n);
+#pragma unroll
+        for (int u = 0; u < P; ++u) acc.fma(av[u], xl.lane(u));
+        xl = xn;
+      }
+    }
+    part[wave][lane] = acc;
+    __syncthreads();
+    if (tid < kWave && row < m) {
+      T s = part[0][tid];
+      for (int w = 1; w < kGemvWaves; ++w) s.add(part[w][tid]);
+      gemv_add<CPLX>(a, gr.o0 + row, s);
+    }
+    __syncthreads();  // part is reused by the next rows
   }
 }
 
-template <bool CPLX, bool TRANS>
-__global__ __launch_bounds__(kGemvThreads, 1) void k_gemv(const GemvArgs a) {
+// TRANS true: lane l takes input row l of a 64-row piece of a block and runs
+// along the workgroup's panel of columns; the columns' sums over the lanes
+// are formed by exchanging halves (after the first four, resp. three, steps
+// a lane holds one column).
+template <bool CPLX>
+__global__ __launch_bounds__(kThreads, 4) void k_gemv_trans(const GemvArgs a) {
   using T = Num<CPLX>;
-  constexpr int kPanel = CPLX ? 8 : 16;
-  __shared__ T part[kGemvThreads / kWave][kMaxVec];
-  __shared__ T xw[TRANS ? kGemvThreads / kWave : 1][TRANS ? kMaxVec : 1];  // gathered inputs
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  constexpr int W = kGemvThreads / kWave;
+  constexpr int P = kPanel<CPLX>, W = kThreads / kWave;
+  __shared__ T part[W][P];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const double *A = static_cast<const double *>(a.A);
-  const double *x = static_cast<const double *>(a.x);
-  double *y = static_cast<double *>(a.y);
-  for (int g = blockIdx.x; g < a.ngroups; g += gridDim.x) {
-    const int64_t o0 = a.out_ptr[g], o1 = a.out_ptr[g + 1];
-    const int64_t b0 = a.grp_ptr[g], b1 = a.grp_ptr[g + 1];
-    const int64_t m = o1 - o0;
-    if (!(o0 >= 0 && o0 <= o1 && o1 <= a.out_len && m <= kMaxVec && b0 >= 0 && b0 <= b1 &&
-          b1 <= a.nblocks)) {
-      if (tid == 0) atomicOr(a.flags, FLAG_EINVAL);
-      continue;  // uniform
-    }
-    for (int64_t i = lane; i < m; i += kWave) part[wave][i] = T::zero();
-    if (!TRANS) {
-      // passes of two chunks of 64 output rows (one chunk if that is all)
-      const int nchunks = (int)((m + kWave - 1) / kWave);
-      if (nchunks <= 1) {
-        gemv_rows<CPLX, 1>(a, m, b0, b1, 0, wave, lane, part[wave]);
-      } else {
-        for (int c0 = 0; c0 < nchunks; c0 += 2)
-          gemv_rows<CPLX, 2>(a, m, b0, b1, c0, wave, lane, part[wave]);
-      }
-    } else {
-      int64_t task = 0;  // panels of the group's blocks so far
-      for (int64_t b = b0; b < b1; ++b) {
-        const int64_t i0 = a.in_ptr[b], i1 = a.in_ptr[b + 1], off = a.a_off[b];
-        const int64_t n = i1 - i0;
-        const int64_t np = (m + kPanel - 1) / kPanel;
-        int64_t p = ((wave - task) % W + W) % W;  // this wave's first panel of block b
-        task += np;
-        if (p >= np) continue;
-        if (!(i0 >= 0 && i0 <= i1 && i1 <= a.in_len && n <= kMaxVec && off >= 0 &&
-              off <= a.a_len && (m == 0 || n <= (a.a_len - off) / m))) {
-          if (lane == 0) atomicOr(a.flags, FLAG_EINVAL);
-          continue;  // uniform in the wave
-        }
-        // the block's inputs, gathered once for all of this wave's panels
-        // into the wave's row of xw (each lane reads back only the rows it
-        // wrote: no barrier)
-        const int ni = (int)n;
-        for (int i = lane; i < ni; i += kWave) {
-          T v = T::zero();
-          const int id = a.in_idx[i0 + i];
-          if (id >= 0 && id < a.x_len) v = T::load(x, id);
-          else atomicOr(a.flags, FLAG_EINVAL);
-          xw[wave][i] = v;
-        }
-        for (; p < np; p += W) {
-          const int64_t j0 = p * kPanel;
-          const int jn = (int)min((int64_t)kPanel, m - j0);
-          T s[kPanel];
+  GemvGroup gr;
+  if (!gemv_group(a, blockIdx.x, &gr)) return;
+  const int m = gr.m;
+  for (int j0 = blockIdx.y * P; j0 < m; j0 += gridDim.y * P) {  // uniform
+    const int jn = min(P, m - j0);
+    T s[P];
 #pragma unroll
-          for (int u = 0; u < kPanel; ++u) s[u] = T::zero();
-          const double *P = A + (CPLX ? 2 : 1) * (off + n * j0);
-#pragma unroll 1
-          for (int i = lane; i - lane < ni; i += kWave) {  // uniform trip count
-            const T xi = i < ni ? xw[wave][i] : T::zero();
-            T av[kPanel];
+    for (int u = 0; u < P; ++u) s[u] = T::zero();
+    int64_t task = 0;  // 64-row pieces of the group's blocks so far
+    for (int64_t b = gr.b0; b < gr.b1; ++b) {
+      GemvBlock bl;
+      const int64_t len = list_at(a.in_ptr, b + 1) - list_at(a.in_ptr, b);
+      const int64_t np = (len + kWave - 1) / kWave;
+      int64_t p = ((wave - task) % W + W) % W;  // this wave's first piece of block b
+      // (an empty block's range is checked too)
+      task += max(np, (int64_t)0);
+      if ((p >= np && len > 0) || !gemv_block(a, b, m, lane, &bl)) continue;  // uniform in the wave
+      const double *C = A + (CPLX ? 2 : 1) * (bl.off + (int64_t)bl.n * j0);
+      for (; p < np; p += W) {
+        const int row = (int)p * kWave + lane;
+        const bool in = row < bl.n;
+        T av[P];
 #pragma unroll
-            for (int u = 0; u < kPanel; ++u)
-              av[u] = i < ni && u < jn ? T::load(P, i + ni * u) : T::zero();
+        for (int u = 0; u < P; ++u) av[u] = in && u < jn ? load_entry<CPLX>(C, row + bl.n * u) : T::zero();
+        const T xi = gemv_input<CPLX>(a, bl.i0 + row, in);
 #pragma unroll
-            for (int u = 0; u < kPanel; ++u) s[u].fma(av[u], xi);
-          }
-          // butterfly sums leave every column's total in every lane; lane
-          // u adds output j0 + u
-          T mine = T::zero();
-#pragma unroll
-          for (int u = 0; u < kPanel; ++u) {
-            const T t = s[u].shfl_down_sum();
-            if (lane == u) mine = t;
-          }
-          if (lane < jn) part[wave][j0 + lane].add(mine);
-        }
+        for (int u = 0; u < P; ++u) s[u].fma(av[u], xi);
       }
     }
+    int mask = kWave / 2;
+#pragma unroll
+    for (int h = P / 2; h >= 1; h /= 2, mask /= 2) {
+      const bool up = lane & mask;
+#pragma unroll
+      for (int u = 0; u < h; ++u) {
+        T keep = up ? s[u + h] : s[u];
+        keep.add((up ? s[u] : s[u + h]).xor_lane(mask));
+        s[u] = keep;
+      }
+    }
+    for (; mask >= 1; mask /= 2) s[0].add(s[0].xor_lane(mask));
+    constexpr int kLanes = kWave / P;  // lanes that hold one column
+    if (lane % kLanes == 0) part[wave][lane / kLanes] = s[0];
     __syncthreads();
-    for (int64_t k = tid; k < m; k += kGemvThreads) {
-      T s = part[0][k];
-      for (int w = 1; w < W; ++w) s.add(part[w][k]);
-      const int id = a.out_idx[o0 + k];
-      if (id < 0 || id >= a.y_len) atomicOr(a.flags, FLAG_EINVAL);
-      else s.add_to(y, id);
+    if (tid < jn) {
+      T t = part[0][tid];
+      for (int w = 1; w < W; ++w) t.add(part[w][tid]);
+      gemv_add<CPLX>(a, gr.o0 + j0 + tid, t);
     }
-    __syncthreads();  // part is reused by the next group
+    __syncthreads();  // part is reused by the next panel
   }
 }
 
@@ -418,13 +437,20 @@ hipError_t launch_cg_step(int64_t n, double *state, double *x, double *r, double
 
 hipError_t launch_gemv(bool cplx, bool trans, const GemvArgs &a, hipStream_t s) {
   if (a.ngroups == 0) return hipSuccess;
-  const dim3 grid((unsigned)std::min<int64_t>(a.ngroups, 4096)), block(kGemvThreads);
+  // workgroups per group from the mean number of outputs (the lengths
+  // themselves are device memory): pieces of rows of twice the mean (the
+  // coupling's groups have 40 to 125 rows of mean 51), resp. panels of a quarter more than the mean; one
+  // without work ends at once, one with more loops, so any number is correct
+  const int64_t mean = std::max<int64_t>((a.out_len + a.ngroups - 1) / a.ngroups, 1);
+  const int panel = cplx ? kPanel<true> : kPanel<false>;
+  const int64_t want = trans ? (5 * mean / 4 + panel - 1) / panel : (2 * mean + kWave - 1) / kWave;
+  const dim3 grid((unsigned)a.ngroups, (unsigned)std::min<int64_t>(std::max<int64_t>(want, 1), kMaxVec / panel));
   if (cplx) {
-    if (trans) hipLaunchKernelGGL((k_gemv<true, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_gemv<true, false>), grid, block, 0, s, a);
+    if (trans) hipLaunchKernelGGL(k_gemv_trans<true>, grid, dim3(kThreads), 0, s, a);
+    else hipLaunchKernelGGL(k_gemv<true>, grid, dim3(kGemvThreads), 0, s, a);
   } else {
-    if (trans) hipLaunchKernelGGL((k_gemv<false, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_gemv<false, false>), grid, block, 0, s, a);
+    if (trans) hipLaunchKernelGGL(k_gemv_trans<false>, grid, dim3(kThreads), 0, s, a);
+    else hipLaunchKernelGGL(k_gemv<false>, grid, dim3(kGemvThreads), 0, s, a);
   }
   return hipGetLastError();
 }

@@ -88,8 +88,9 @@ class H2Matrix:
             off[1:] = np.cumsum(B.rank)
             return off
         self.cw, self.cv = slots(col_basis), slots(row_basis)
-        self.xh = torch.zeros(int(self.cw[-1]), dtype=self.dtype, device="cuda")
-        self.yh = torch.zeros(int(self.cv[-1]), dtype=self.dtype, device="cuda")
+        # (one allocation, cleared by one launch per product)
+        self._coef = torch.zeros(int(self.cw[-1] + self.cv[-1]), dtype=self.dtype, device="cuda")
+        self.xh, self.yh = self._coef[:int(self.cw[-1])], self._coef[int(self.cw[-1]):]
         rng = lambda off, c: np.arange(off[c], off[c] + (off[c + 1] - off[c]))
         # near field, grouped by row cluster; a block is inadmissible when
         # either cluster is a leaf, so a row cluster may be a father whose
@@ -171,8 +172,7 @@ class H2Matrix:
                     y.zero_()
                 for c in self.near_calls:
                     self._run(c, bufs, None)
-            self.xh.zero_()
-            self.yh.zero_()
+            self._coef.zero_()
             for c in self.fwd:
                 self._run(c, bufs, None)
             self._run(self.coupling_call, bufs, None)
