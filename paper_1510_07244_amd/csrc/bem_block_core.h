@@ -45,8 +45,7 @@ enum RowField {
 //   cc[3][TC]      column centroids, doubled (Helmholtz phases)
 //   both layers:   rn[3][TR] row normals
 //   mixed only:    cg[3][TC] = 2 (v0_j - c); rb[6][TR], cb[6][TC] boxes
-//   ints           rid[TR], rv[3][TR], rs[TR], cid[TC], cv[3][TC], cs[TC] (rs, cs: short phases),
-//                  count, bad, rcount, pad, per-group counts[16] and
+//   ints           rid[TR], rv[3][TR], cid[TC], cv[3][TC], count, bad, rcount, pad, per-group counts[16] and
 //                  cursors[16] (classes at 0 .. 3, orders q at 8 + q)
 //   list[TR*TC]    uint16 codes (row | col << 6 | group << 12, kSwapped) of the pairs
 //                  left to the FP64 pass (singular; near-singular if mixed),
@@ -56,7 +55,7 @@ enum RowField {
 //                  group padded to a multiple of 64 with kNoPair
 struct Lds {
   double *ys, *rg, *rule, *cn, *cc, *rn, *cg, *rb, *cb;
-  int *rid, *rv, *rs, *cid, *cv, *cs, *count, *bad, *rcount, *ccount, *cursor;
+  int *rid, *rv, *cid, *cv, *count, *bad, *rcount, *ccount, *cursor;
   uint16_t *list, *sorted;
 };
 
@@ -77,11 +76,9 @@ __device__ __forceinline__ Lds carve(double *base, int nqp, int TR, int TC, bool
   int *ib = reinterpret_cast<int *>(l.cb + (MIXED ? 6 * TC : 0));
   l.rid = ib;
   l.rv = l.rid + TR;
-  l.rs = l.rv + 3 * TR;
-  l.cid = l.rs + TR;
+  l.cid = l.rv + 3 * TR;
   l.cv = l.cid + TC;
-  l.cs = l.cv + 3 * TC;
-  l.count = l.cs + TC;
+  l.count = l.cv + 3 * TC;
   l.bad = l.count + 1;
   l.rcount = l.bad + 1;
   l.ccount = l.rcount + 2;
@@ -199,7 +196,7 @@ __device__ __forceinline__ void for_points(const PTS &pts, int n, F &&point) {
 //   both layers   t1 = sum w k3, t2 = sum wn k3 and the single layer's sum,
 // with k = 1/r, k3 = 1/r^3, times e^{i kappa r} resp. e^{i kappa r} (1 - i
 // kappa r) for Helmholtz.  SHORT: phases relative to kr0 (kappa r - kr0 in
-// [-1/2, 1/2]), the common factor e^{i kr0} left to the caller.
+// [-3/4, 3/4]), the common factor e^{i kr0} left to the caller.
 template <int KERNEL, int LAYER, class T>
 struct PointSums {
   T sr = 0, si = 0, t1r = 0, t1i = 0, t2r = 0, t2i = 0;
@@ -644,14 +641,11 @@ __device__ __forceinline__ EntryGeo entry_geo(const Lds &l, int TR, int TC, int 
   return g;
 }
 
-// All sums of regular entry (rl, cl), FP64 or (mixed) FP32.  Helmholtz: the
-// short phases if both triangles allow them (kappa times the distance of a
-// triangle's points from its centroid at most 1/2, see short_phase): a
-// decision of the entry alone, so that its value does not depend on the
-// kernel, sub-tile or wave that computes it.
+// All sums of regular entry (rl, cl), FP64 or (mixed) FP32.  brief: Helmholtz
+// with short phases, uniform in the workgroup (block_is_brief).
 template <int KERNEL, int LAYER, int RULE, bool MIXED>
 __device__ __forceinline__ void regular_sums(const Lds &l, int TR, int TC, int nqp, int rl, int cl,
-                                             const double *table, double kappa, Sums<KERNEL> *o) {
+                                             const double *table, double kappa, bool brief, Sums<KERNEL> *o) {
   const EntryGeo g = entry_geo<LAYER, MIXED>(l, TR, TC, rl, cl);
   typedef typename std::conditional<MIXED, float, double>::type T;
   typename std::conditional<MIXED, PointsLds32, PointsLds64>::type pts;
@@ -667,7 +661,7 @@ __device__ __forceinline__ void regular_sums(const Lds &l, int TR, int TC, int n
   } else if constexpr (KERNEL == BEM_LAPLACE) {
     duffy_sums<KERNEL, LAYER, RULE, false, T>(g, table, kappa, pts, o);
   } else {
-    if (l.rs[rl] & l.cs[cl]) duffy_sums<KERNEL, LAYER, RULE, true, T>(g, table, kappa, pts, o);
+    if (brief) duffy_sums<KERNEL, LAYER, RULE, true, T>(g, table, kappa, pts, o);
     else duffy_sums<KERNEL, LAYER, RULE, false, T>(g, table, kappa, pts, o);
   }
 }

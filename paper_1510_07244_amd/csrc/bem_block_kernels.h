@@ -37,6 +37,7 @@ struct BlockHdr {
   int64_t moff;       // transposed copy (coupling of a single layer), -1: none
   bool diag;          // its own mirror (moff == off): a block on the diagonal,
                       // only its entries with row >= column are evaluated
+  bool brief;         // block_is_brief
   double cx, cy, cz;  // block-local origin: first vertex of the first row triangle
 };
 
@@ -79,6 +80,36 @@ __device__ __forceinline__ bool block_header(const BlockArgs &a, int b, BlockHdr
   return true;
 }
 
+// Whether block h may take its Helmholtz phases relative to the centroids'
+// distance: kappa times the largest distance of a point from its centroid at
+// most 3/4 (short_phase) for every triangle of its rows and columns (and at
+// least 1e-10: coordinates are scaled by kappa then).  A property of the block
+// alone, so that its entries do not depend on the kernel or the sub-tiles that
+// compute them, and one for all its entries: with a decision per entry, waves
+// that held both kinds ran both sums (0.64x on a coarse mesh).  Uniform; starts
+// and ends with a barrier.
+template <int KERNEL>
+__device__ bool block_is_brief(const BlockArgs &a, const Lds &l, const BlockHdr &h) {
+  if constexpr (KERNEL == BEM_LAPLACE) {
+    return false;
+  } else {
+    const int tid = thread_id();
+    __syncthreads();
+    if (tid == 0) *l.bad = 0;
+    __syncthreads();
+    const double k2 = a.kappa * a.kappa;
+    for (int64_t k = tid; k < h.nr + h.nc; k += kThreads) {
+      const int id = k < h.nr ? a.row_idx[h.rp0 + k] : a.col_idx[h.cp0 + (k - h.nr)];
+      const double x = id >= 0 && id < a.nt ? k2 * a.geo[G_R2 * a.ldg + id] : 0.0;
+      if (!(x <= kShortPhase * kShortPhase && x >= 1e-20)) *l.bad = 1;
+    }
+    __syncthreads();
+    const bool brief = *l.bad == 0;
+    __syncthreads();
+    return brief;
+  }
+}
+
 // The quadrature rule into LDS (padded with zero weights to nqp points).
 __device__ __forceinline__ void load_rule(const BlockArgs &a, const Lds &l) {
   const int nqp = a.nq_pad, nq = a.nq;
@@ -112,21 +143,13 @@ __device__ bool stage_tile(const BlockArgs &a, const Lds &l, const BlockHdr &h, 
       *l.bad = 1;
       continue;
     }
-    // kappa times the largest distance of a point of the triangle from its
-    // centroid at most 1/2: its phases may be taken relative to the centroid's
-    // (and at least 1e-10: coordinates are scaled by kappa then)
-    double e1[3], e2[3], g0 = 0.0, g1 = 0.0, g2 = 0.0;
+    double e1[3], e2[3];
     for (int m = 0; m < 3; ++m) {
       e1[m] = a.geo[(G_E1X + m) * L + id];
       e2[m] = a.geo[(G_E2X + m) * L + id];
-      const double p = 2.0 * e1[m] + e2[m], q = e1[m] - e2[m], r = e1[m] + 2.0 * e2[m];
-      g0 = fma(p, p, g0), g1 = fma(q, q, g1), g2 = fma(r, r, g2);
     }
-    const double kr2 = a.kappa * a.kappa * fmax(g0, fmax(g1, g2)) * (1.0 / 9.0);
-    const int brief = kr2 <= 0.25 && kr2 >= 1e-20;
     if (isrow) {
       l.rid[k] = id;
-      l.rs[k] = brief;
       for (int m = 0; m < 3; ++m) l.rv[m * TR + k] = a.tri[3 * (int64_t)id + m];
       l.rg[(R_V + 0) * TR + k] = 2.0 * (a.geo[G_V0X * L + id] - cx);
       l.rg[(R_V + 1) * TR + k] = 2.0 * (a.geo[G_V0Y * L + id] - cy);
@@ -152,7 +175,6 @@ __device__ bool stage_tile(const BlockArgs &a, const Lds &l, const BlockHdr &h, 
     } else {
       const int cl = k - tr;
       l.cid[cl] = id;
-      l.cs[cl] = brief;
       for (int m = 0; m < 3; ++m) l.cv[m * TC + cl] = a.tri[3 * (int64_t)id + m];
       double yn = 0.0;
       for (int m = 0; m < 3; ++m) {
@@ -293,7 +315,7 @@ __device__ __forceinline__ void singular_chunk(const BlockArgs &a, const Lds &l,
 // listed code in both layers and, if the block has a mirror, the transposed
 // pair (j, i): an edge pair evaluated as (j, i) (that rule is not symmetric);
 // else its single layer copied and its double layer summed over the same
-// directions (vertex pairs) or evaluated as (j, i) (near-singular pairs).  The class is uniform
+// directions (vertex pairs) or point pairs (near-singular pairs).  The class is uniform
 // across the chunk.
 template <int KERNEL, bool MIXED>
 __device__ __forceinline__ void singular_chunk_both(const BlockArgs &a, const Lds &l,
@@ -311,12 +333,11 @@ __device__ __forceinline__ void singular_chunk_both(const BlockArgs &a, const Ld
   if (cls == kNearSingular) {  // mixed form: a regular pair summed in FP64
     if (!active) return;
     const int i = l.rid[rl], j = l.cid[cl];
-    const Acc<KERNEL> vs = regular_pair_fp64<KERNEL, BEM_SLP>(a.geo, a.ldg, a.rule, a.nq, a.kappa, i, j);
-    const Acc<KERNEL> vd = regular_pair_fp64<KERNEL, BEM_DLP>(a.geo, a.ldg, a.rule, a.nq, a.kappa, i, j);
+    Acc<KERNEL> vs, vd, md;
+    regular_pair_both_fp64<KERNEL>(a.geo, a.ldg, a.rule, a.nq, a.kappa, i, j, &vs, &vd, &md);
     store_as<KERNEL, MIXED>(a.out, dst, vs, a.flags);
     store_as<KERNEL, MIXED>(a.out2, dst, vd, a.flags);
     if (h.moff >= 0) {
-      const Acc<KERNEL> md = regular_pair_fp64<KERNEL, BEM_DLP>(a.geo, a.ldg, a.rule, a.nq, a.kappa, j, i);
       store_as<KERNEL, MIXED>(a.out, mdst, vs, a.flags);
       store_as<KERNEL, MIXED>(a.out2, mdst, md, a.flags);
     }
@@ -496,7 +517,7 @@ __device__ void subtile(const BlockArgs &a, const Lds &l, const BlockHdr &h, int
     int cls;
     if (fp64_pair<MIXED>(l, TR, TC, rl, cl, ratio, &cls)) continue;
     Sums<KERNEL> o;
-    regular_sums<KERNEL, LAYER, RULE, MIXED>(l, TR, TC, nqp, rl, cl, a.duffy, a.kappa, &o);
+    regular_sums<KERNEL, LAYER, RULE, MIXED>(l, TR, TC, nqp, rl, cl, a.duffy, a.kappa, h.brief, &o);
     scale_sums(&o);
     const int64_t dst = off + (r0 + rl) + nr * (c0 + cl);
     const int64_t mdst = h.moff + (c0 + cl) + h.nc * (r0 + rl);
@@ -511,13 +532,14 @@ __device__ void subtile(const BlockArgs &a, const Lds &l, const BlockHdr &h, int
 
 template <int KERNEL, int LAYER>
 __device__ __forceinline__ void regular_sums_q(int q, const Lds &l, int TR, int TC, int rl, int cl,
-                                               const double *table, double kappa, Sums<KERNEL> *o) {
+                                               const double *table, double kappa, bool brief,
+                                               Sums<KERNEL> *o) {
   switch (q) {
-    case 2: return regular_sums<KERNEL, LAYER, 2, false>(l, TR, TC, 4, rl, cl, table, kappa, o);
-    case 3: return regular_sums<KERNEL, LAYER, 3, false>(l, TR, TC, 9, rl, cl, table, kappa, o);
-    case 4: return regular_sums<KERNEL, LAYER, 4, false>(l, TR, TC, 16, rl, cl, table, kappa, o);
-    case 5: return regular_sums<KERNEL, LAYER, 5, false>(l, TR, TC, 25, rl, cl, table, kappa, o);
-    default: return regular_sums<KERNEL, LAYER, 6, false>(l, TR, TC, 36, rl, cl, table, kappa, o);
+    case 2: return regular_sums<KERNEL, LAYER, 2, false>(l, TR, TC, 4, rl, cl, table, kappa, brief, o);
+    case 3: return regular_sums<KERNEL, LAYER, 3, false>(l, TR, TC, 9, rl, cl, table, kappa, brief, o);
+    case 4: return regular_sums<KERNEL, LAYER, 4, false>(l, TR, TC, 16, rl, cl, table, kappa, brief, o);
+    case 5: return regular_sums<KERNEL, LAYER, 5, false>(l, TR, TC, 25, rl, cl, table, kappa, brief, o);
+    default: return regular_sums<KERNEL, LAYER, 6, false>(l, TR, TC, 36, rl, cl, table, kappa, brief, o);
   }
 }
 
@@ -598,7 +620,7 @@ __device__ void subtile_learned(const BlockArgs &a, const OrderRules &o, const L
       if (code == kNoPair) continue;
       const int rl = code & 63, cl = (code >> 6) & 63;
       Sums<KERNEL> v;
-      regular_sums_q<KERNEL, LAYER>(q, l, TR, TC, rl, cl, o.duffy[q], a.kappa, &v);
+      regular_sums_q<KERNEL, LAYER>(q, l, TR, TC, rl, cl, o.duffy[q], a.kappa, h.brief, &v);
       scale_sums(&v);
       store_as<KERNEL, false>(a.out, off + (r0 + rl) + nr * (c0 + cl), LAYER == BEM_DLP ? v.d : v.s,
                               a.flags);
@@ -615,6 +637,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_blocks_learned(const BlockArgs 
   BlockHdr h;
   if (!block_header(a, blockIdx.x, &h) || h.nr == 0 || h.nc == 0) return;
   const Lds l = carve<false>(lds_raw, a.nq_pad, a.tr, a.tc);
+  h.brief = block_is_brief<KERNEL>(a, l, h);
   for (int64_t r0 = 0; r0 < h.nr; r0 += a.tr)
     for (int64_t c0 = 0; c0 < h.nc; c0 += a.tc) subtile_learned<KERNEL, LAYER>(a, o, l, h, r0, c0);
 }
@@ -625,6 +648,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_blocks(const BlockArgs a, const
   BlockHdr h;
   if (!block_header(a, blockIdx.x, &h) || h.nr == 0 || h.nc == 0) return;
   const Lds l = carve<MIXED>(lds_raw, a.nq_pad, a.tr, a.tc, LAYER == kBoth);
+  h.brief = block_is_brief<KERNEL>(a, l, h);
   load_rule(a, l);
   for (int64_t r0 = 0; r0 < h.nr; r0 += a.tr)
     for (int64_t c0 = 0; c0 < h.nc; c0 += a.tc)
@@ -680,6 +704,7 @@ __device__ __forceinline__ void persistent_item(const BlockArgs *__restrict__ ba
     load_rule(a, l);
     *carved = shape;
   }
+  h.brief = block_is_brief<KERNEL>(a, l, h);
   if (whole) {  // the whole block, sub-tile by sub-tile
     for (int64_t r0 = 0; r0 < h.nr; r0 += a.tr)
       for (int64_t c0 = 0; c0 < h.nc; c0 += a.tc) subtile<KERNEL, LAYER, RULE, MIXED>(a, l, h, r0, c0, cp);

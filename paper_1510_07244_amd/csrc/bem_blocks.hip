@@ -43,7 +43,7 @@ size_t block_lds_bytes(int nq_pad, int tr, int tc, bool mixed, bool lists, bool 
   size_t dbl = (size_t)blk::ypoint_doubles(mixed) * nq_pad * tc + blk::ROW_NF * (size_t)tr +
                3 * (size_t)nq_pad + 7 * (size_t)tc + (both ? 3 * (size_t)tr : 0);
   if (mixed) dbl += 3 * (size_t)tc + 6 * (size_t)tr + 6 * (size_t)tc;
-  const size_t ints = (size_t)5 * tr + 5 * (size_t)tc + 36;
+  const size_t ints = (size_t)4 * tr + 4 * (size_t)tc + 36;
   return dbl * 8 + ints * 4 + (lists ? (size_t)2 * (2 * (size_t)tr * tc + blk::kSortPad) : 0);
 }
 

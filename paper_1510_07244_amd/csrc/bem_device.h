@@ -101,35 +101,38 @@ __device__ __forceinline__ void sincos_cw_f32(float x, float *s, float *c) {
   *c = __int_as_float(__float_as_int(cr) ^ sgn);
 }
 
-// Sine and cosine of a phase |x| <= 1/2 relative to a reference distance, no
+// Sine and cosine of a phase |x| <= 3/4 relative to a reference distance, no
 // reduction: sin x = x + x^3 P(x^2), cos x = 1 - x^2 / 2 + x^4 Q(x^2), P and Q
-// from the same construction on [0, 1/4] (below 2.5e-17 relative and 2.6e-19
-// absolute; FP32 5.4e-10 and 2.0e-9): 13 instructions (FP32 8) where the
+// from the same construction on [0, 9/16] (below 3.3e-18 relative and 4.1e-17
+// absolute; FP32 6.9e-9 and 5.0e-10): 14 instructions (FP32 9) where the
 // reduction by pi and its polynomials take 28 (20).
+constexpr double kShortPhase = 0.75;
 __device__ __forceinline__ void short_phase(double x, double *s, double *c) {
   const double r2 = x * x;
-  double ps = -0x1.ac5c1605a3a89p-26;
-  ps = fma(ps, r2, 0x1.71dd1cae1263ap-19);
-  ps = fma(ps, r2, -0x1.a01a011194a79p-13);
-  ps = fma(ps, r2, 0x1.11111110f201bp-7);
-  ps = fma(ps, r2, -0x1.55555555554c8p-3);
+  double ps = 0x1.5de07ede42fd2p-33;
+  ps = fma(ps, r2, -0x1.ae5f5cd1da528p-26);
+  ps = fma(ps, r2, 0x1.71de36994cee9p-19);
+  ps = fma(ps, r2, -0x1.a01a019d434f0p-13);
+  ps = fma(ps, r2, 0x1.111111111012cp-7);
+  ps = fma(ps, r2, -0x1.555555555554ep-3);
   *s = fma(x * r2, ps, x);
-  double pc = 0x1.1da5f6afdc0e5p-29;
-  pc = fma(pc, r2, -0x1.27e4301a437b0p-22);
-  pc = fma(pc, r2, 0x1.a01a0128eddeap-16);
-  pc = fma(pc, r2, -0x1.6c16c16bf658fp-10);
-  pc = fma(pc, r2, 0x1.55555555554efp-5);
+  double pc = 0x1.1c0e6d71989eep-29;
+  pc = fma(pc, r2, -0x1.27e0f9998bd9dp-22);
+  pc = fma(pc, r2, 0x1.a019fc581f756p-16);
+  pc = fma(pc, r2, -0x1.6c16c168dbc4bp-10);
+  pc = fma(pc, r2, 0x1.5555555553e74p-5);
   pc = fma(pc, r2, -0.5);
   *c = fma(r2, pc, 1.0);
 }
 __device__ __forceinline__ void short_phase_f32(float x, float *s, float *c) {
   const float r2 = x * x;
-  float ps = -0x1.9d5406p-13f;
-  ps = fmaf(ps, r2, 0x1.110f74p-7f);
-  ps = fmaf(ps, r2, -0x1.555554p-3f);
+  float ps = -0x1.99dddcp-13f;
+  ps = fmaf(ps, r2, 0x1.1108e4p-7f);
+  ps = fmaf(ps, r2, -0x1.55554ap-3f);
   *s = fmaf(x * r2, ps, x);
-  float pc = -0x1.699072p-10f;
-  pc = fmaf(pc, r2, 0x1.555376p-5f);
+  float pc = 0x1.9a8ae2p-16f;
+  pc = fmaf(pc, r2, -0x1.6c0e42p-10f);
+  pc = fmaf(pc, r2, 0x1.55554ep-5f);
   pc = fmaf(pc, r2, -0.5f);
   *c = fmaf(r2, pc, 1.0f);
 }
@@ -180,57 +183,178 @@ __device__ __forceinline__ void store_as(void *out, int64_t k, const Acc<KERNEL>
   }
 }
 
-// One regular (disjoint) pair in FP64 with its rule points computed on the
-// fly from the geometry arrays: sqrt(g_i g_j) sum_a w_a sum_b w_b k(x_a, y_b).
-template <int KERNEL, int LAYER>
-__device__ __forceinline__ Acc<KERNEL> regular_pair_fp64(const double *g, int64_t L,
-                                                         const double *R, int nq, double kappa,
-                                                         int i, int j) {
-  double D[3], E1i[3], E2i[3], E1j[3], E2j[3];
+typedef const double __attribute__((address_space(4))) *uniform_ptr;
+
+constexpr int kSS = 2;  // layer value: both layers
+
+// Sums over the column points y_b of one x-point (lane's own), without the
+// x-point's weight: single layer s, double layer d, and with P1 the same
+// kernel values times the column triangle's barycentric coordinates.
+struct RowSum {
+  double sr[3], si[3], dr[3], di[3];
+};
+
+// One regular (disjoint) pair (i, j) in FP64 with its rule points formed from
+// the geometry arrays, XC x-points at a time: the chunks sub, sub + G, ... of
+// the rule's nq points (G lanes share a pair; each returns its part).  On the
+// column triangle the squared distance from an x-point is a quadratic
+// polynomial: |X|^2 - 2 u <X, e1> - 2 v <X, e2> + |u e1 + v e2|^2 with X = x -
+// v0_j, three operations per point pair beyond the term all x-points share;
+// <x - y, n_j> is one value per x-point.  The rule is read by scalar loads.
+// row(k, w, sums) is called for every x-point k with its weight (zero and a
+// repeated point past the last one); with MIRROR *mr, *mi receive the double
+// layer of (j, i), which needs the row's weights inside.
+template <int KERNEL, int LAYER, bool MIRROR, bool P1, int XC, class F>
+__device__ __forceinline__ void regular_rows(const double *g, int64_t L, const double *rule, int nq,
+                                             double kappa, int i, int j, int sub, int G, F &&row,
+                                             double *mr = nullptr, double *mi = nullptr) {
+  constexpr int NB = P1 ? 3 : 1;
+  constexpr bool S = LAYER != BEM_DLP, D = LAYER != BEM_SLP;
+  const uniform_ptr R = (uniform_ptr)rule;
+  double X0[3], e1i[3], e2i[3], e1j[3], e2j[3], n[3] = {0, 0, 0}, ni[3] = {0, 0, 0};
+#pragma unroll
   for (int c = 0; c < 3; ++c) {
-    D[c] = g[(G_V0X + c) * L + i] - g[(G_V0X + c) * L + j];
-    E1i[c] = g[(G_E1X + c) * L + i];
-    E2i[c] = g[(G_E2X + c) * L + i];
-    E1j[c] = g[(G_E1X + c) * L + j];
-    E2j[c] = g[(G_E2X + c) * L + j];
+    X0[c] = g[(G_V0X + c) * L + i] - g[(G_V0X + c) * L + j];
+    e1i[c] = g[(G_E1X + c) * L + i];
+    e2i[c] = g[(G_E2X + c) * L + i];
+    e1j[c] = g[(G_E1X + c) * L + j];
+    e2j[c] = g[(G_E2X + c) * L + j];
+    if (D) n[c] = g[(G_NX + c) * L + j];
+    if (MIRROR) ni[c] = g[(G_NX + c) * L + i];
   }
-  const double nx = g[G_NX * L + j], ny = g[G_NY * L + j], nz = g[G_NZ * L + j];
-  double are = 0.0, aim = 0.0;
-  for (int qa = 0; qa < nq; ++qa) {
-    double x[3];
-    for (int c = 0; c < 3; ++c) x[c] = fma(R[qa], E1i[c], fma(R[nq + qa], E2i[c], D[c]));
-    double ire = 0.0, iim = 0.0;
-    for (int qb = 0; qb < nq; ++qb) {
-      double d[3];
-      for (int c = 0; c < 3; ++c) d[c] = fma(-R[qb], E1j[c], fma(-R[nq + qb], E2j[c], x[c]));
-      const double r2 = fma(d[0], d[0], fma(d[1], d[1], d[2] * d[2]));
-      const double z = rsqrt_newton(r2);
-      double k = z;
-      if constexpr (LAYER == BEM_DLP) k = fma(d[0], nx, fma(d[1], ny, d[2] * nz)) * z * z * z;
-      const double w = R[2 * nq + qb];
-      if constexpr (KERNEL == BEM_LAPLACE) {
-        ire = fma(w, k, ire);
-      } else {
-        const double kr = kappa * r2 * z;
-        double sn, cs;
-        sincos_cw(kr, &sn, &cs);
-        if constexpr (LAYER == BEM_SLP) {
-          ire = fma(w * k, cs, ire);
-          iim = fma(w * k, sn, iim);
-        } else {
-          ire = fma(w * k, fma(kr, sn, cs), ire);
-          iim = fma(w * k, fma(-kr, cs, sn), iim);
+  auto dot = [](const double *a, const double *b) { return fma(a[0], b[0], fma(a[1], b[1], a[2] * b[2])); };
+  const double a11 = dot(e1j, e1j), a12 = 2.0 * dot(e1j, e2j), a22 = dot(e2j, e2j);
+  // <y - x, n_i> = m1 u + m2 v - m0
+  const double m0 = dot(X0, ni), m1 = dot(e1j, ni), m2 = dot(e2j, ni);
+  for (int a0 = sub * XC; a0 < nq; a0 += G * XC) {
+    double c[XC], p[XC], q[XC], dn[XC], w[XC];
+    RowSum acc[XC];
+#pragma unroll
+    for (int a = 0; a < XC; ++a) {
+      const int k = min(a0 + a, nq - 1);
+      // lanes of a pair take different x-points: per-lane loads
+      const double s = rule[k], t = rule[nq + k];
+      w[a] = a0 + a < nq ? rule[2 * nq + k] : 0.0;
+      double X[3];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) X[d] = fma(s, e1i[d], fma(t, e2i[d], X0[d]));
+      c[a] = dot(X, X);
+      p[a] = -2.0 * dot(X, e1j);
+      q[a] = -2.0 * dot(X, e2j);
+      dn[a] = dot(X, n);
+#pragma unroll
+      for (int b = 0; b < NB; ++b) acc[a].sr[b] = acc[a].si[b] = acc[a].dr[b] = acc[a].di[b] = 0.0;
+    }
+    constexpr int U = XC == 1 ? 4 : 1;  // column points per step
+    auto step = [&](int b0, int nu) {
+      double u[U], v[U], wb[U], r2[U][XC], h[U][XC];
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const int b = U == 1 ? b0 : min(b0 + k, nq - 1);
+        u[k] = R[b];
+        v[k] = R[nq + b];
+        wb[k] = k < nu ? R[2 * nq + b] : 0.0;
+        const double gb = fma(u[k], fma(u[k], a11, v[k] * a12), v[k] * v[k] * a22);
+#pragma unroll
+        for (int a = 0; a < XC; ++a) r2[k][a] = fma(v[k], q[a], fma(u[k], p[a], c[a] + gb));
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k)
+#pragma unroll
+        for (int a = 0; a < XC; ++a) h[k][a] = __builtin_amdgcn_rsq(r2[k][a]);
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        double tr = 0.0, ti = 0.0;
+#pragma unroll
+        for (int a = 0; a < XC; ++a) {
+          const double z = fma(0.5 * h[k][a], fma(-(r2[k][a] * h[k][a]), h[k][a], 1.0), h[k][a]);
+          double z3 = 0.0, cs = 1.0, sn = 0.0, fr = 1.0, fi = 0.0;
+          if (D) z3 = z * z * z;
+          if constexpr (KERNEL == BEM_HELMHOLTZ) {
+            const double kr = kappa * r2[k][a] * z;
+            sincos_cw(kr, &sn, &cs);
+            if (D) fr = fma(kr, sn, cs), fi = fma(-kr, cs, sn);
+          }
+          auto add = [&](double f, double re, double im, double *ar, double *ai) {
+            const double x = f * re;
+            if constexpr (P1) {
+              ar[0] += x;
+              ar[1] = fma(u[k], x, ar[1]);
+              ar[2] = fma(v[k], x, ar[2]);
+            } else {
+              ar[0] = fma(f, re, ar[0]);
+            }
+            if constexpr (KERNEL == BEM_HELMHOLTZ) {
+              const double y = f * im;
+              if constexpr (P1) {
+                ai[0] += y;
+                ai[1] = fma(u[k], y, ai[1]);
+                ai[2] = fma(v[k], y, ai[2]);
+              } else {
+                ai[0] = fma(f, im, ai[0]);
+              }
+            }
+          };
+          if (S) add(wb[k] * z, cs, sn, acc[a].sr, acc[a].si);
+          if (D) add(wb[k] * z3, fr, fi, acc[a].dr, acc[a].di);
+          if (MIRROR) {
+            const double x = w[a] * z3;
+            tr = fma(x, fr, tr);
+            if constexpr (KERNEL == BEM_HELMHOLTZ) ti = fma(x, fi, ti);
+          }
+        }
+        if (MIRROR) {
+          const double wm = wb[k] * fma(m1, u[k], fma(m2, v[k], -m0));
+          *mr = fma(wm, tr, *mr);
+          if constexpr (KERNEL == BEM_HELMHOLTZ) *mi = fma(wm, ti, *mi);
         }
       }
+    };
+    for (int b = 0; b < nq; b += U) step(b, nq - b);
+#pragma unroll
+    for (int a = 0; a < XC; ++a) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b) acc[a].dr[b] *= dn[a], acc[a].di[b] *= dn[a];
+      row(min(a0 + a, nq - 1), w[a], acc[a]);
     }
-    are = fma(R[2 * nq + qa], ire, are);
-    aim = fma(R[2 * nq + qa], iim, aim);
   }
+}
+
+// sqrt(g_i g_j) / (4 pi) sum_a w_a sum_b w_b k(x_a, y_b) over the x-points of
+// this lane (sub of G, see regular_rows); the lanes' parts add up to the entry.
+template <int KERNEL, int LAYER, int XC = 4>
+__device__ __forceinline__ Acc<KERNEL> regular_pair_fp64(const double *g, int64_t L,
+                                                         const double *rule, int nq, double kappa,
+                                                         int i, int j, int sub = 0, int G = 1) {
+  double re = 0.0, im = 0.0;
+  regular_rows<KERNEL, LAYER, false, false, XC>(g, L, rule, nq, kappa, i, j, sub, G,
+                                                [&](int, double w, const RowSum &r) {
+    re = fma(w, LAYER == BEM_SLP ? r.sr[0] : r.dr[0], re);
+    if constexpr (KERNEL == BEM_HELMHOLTZ) im = fma(w, LAYER == BEM_SLP ? r.si[0] : r.di[0], im);
+  });
   const double scale = g[G_SG * L + i] * g[G_SG * L + j] * kInv4Pi;
   Acc<KERNEL> v;
-  v.re = are * scale;
-  if constexpr (KERNEL == BEM_HELMHOLTZ) v.im = aim * scale;
+  v.re = re * scale;
+  if constexpr (KERNEL == BEM_HELMHOLTZ) v.im = im * scale;
   return v;
+}
+
+// Both layers of (i, j) and the double layer of (j, i) in one pass.
+template <int KERNEL>
+__device__ __forceinline__ void regular_pair_both_fp64(const double *g, int64_t L, const double *rule,
+                                                       int nq, double kappa, int i, int j,
+                                                       Acc<KERNEL> *vs, Acc<KERNEL> *vd,
+                                                       Acc<KERNEL> *vm) {
+  double s[2] = {0, 0}, d[2] = {0, 0}, m[2] = {0, 0};
+  regular_rows<KERNEL, kSS, true, false, 4>(g, L, rule, nq, kappa, i, j, 0, 1,
+                                            [&](int, double w, const RowSum &r) {
+    s[0] = fma(w, r.sr[0], s[0]);
+    d[0] = fma(w, r.dr[0], d[0]);
+    if constexpr (KERNEL == BEM_HELMHOLTZ) s[1] = fma(w, r.si[0], s[1]), d[1] = fma(w, r.di[0], d[1]);
+  }, &m[0], &m[1]);
+  const double f = g[G_SG * L + i] * g[G_SG * L + j] * kInv4Pi;
+  vs->re = s[0] * f, vd->re = d[0] * f, vm->re = m[0] * f;
+  if constexpr (KERNEL == BEM_HELMHOLTZ) vs->im = s[1] * f, vd->im = d[1] * f, vm->im = m[1] * f;
 }
 
 __device__ __forceinline__ int shared_vertex_count(int a0, int a1, int a2, int b0, int b1, int b2) {
@@ -293,8 +417,6 @@ struct PairGeo {
   double scale;  // sqrt(g_i) sqrt(g_j) / (4 pi)
 };
 
-typedef const double __attribute__((address_space(4))) *uniform_ptr;
-
 // Loads and relabels pair (i, j) of class cls; false (and the flag) if a
 // vertex id is out of range.
 __device__ __forceinline__ bool pair_geometry(const double *v, const int32_t *tri, int nv,
@@ -335,8 +457,6 @@ template <class T>
 __device__ __forceinline__ T pick4(const T (&v)[4], int k) {
   return k == 0 ? v[0] : k == 1 ? v[1] : k == 2 ? v[2] : v[3];
 }
-
-constexpr int kSS = 2;  // layer value of the singular sums: both layers
 
 // Largest squared distance of a point of tau_i from one of tau_j: between two
 // vertices (every direction d of the rule is such a difference).

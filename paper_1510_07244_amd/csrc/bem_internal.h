@@ -64,6 +64,7 @@ enum GeoField {
   G_NX, G_NY, G_NZ,     // outward unit normal
   G_LOX, G_LOY, G_LOZ,  // bounding box
   G_HIX, G_HIY, G_HIZ,
+  G_R2,                 // largest squared distance of a point from the centroid
   GEO_NF
 };
 

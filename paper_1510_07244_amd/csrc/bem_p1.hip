@@ -53,52 +53,31 @@ __device__ __forceinline__ void kernel_value(double dx, double dy, double dz, co
   }
 }
 
-// Regular pair by the triangle rule of each triangle (lane per pair):
-// inner sums over the column points for the three column shape functions,
-// then the row point's three shape functions.
-template <int KERNEL, int LAYER>
-__device__ void p1_regular(const P1Args &a, int i, int j, Acc9<KERNEL> *L) {
-  const int64_t G = a.ldg;
-  const double *g = a.geo;
-  double vi[3], e1i[3], e2i[3], vj[3], e1j[3], e2j[3], n[3];
-  for (int c = 0; c < 3; ++c) {
-    vi[c] = g[(G_V0X + c) * G + i], e1i[c] = g[(G_E1X + c) * G + i], e2i[c] = g[(G_E2X + c) * G + i];
-    vj[c] = g[(G_V0X + c) * G + j], e1j[c] = g[(G_E1X + c) * G + j], e2j[c] = g[(G_E2X + c) * G + j];
-    n[c] = g[(G_NX + c) * G + j];
-  }
+// Regular pair by the triangle rule of each triangle: for every x-point of
+// this lane (sub of G) the sums over the column points times 1, u and v give
+// those of the three column shape functions, then the row point's three.
+template <int KERNEL, int LAYER, int XC>
+__device__ void p1_regular(const P1Args &a, int i, int j, int sub, int G, Acc9<KERNEL> *L) {
   for (int e = 0; e < 9; ++e) L->re[e] = L->im[e] = 0.0;
   for (int k = 0; k < 3; ++k) L->pr[k] = L->pc[k] = k;
   const int nq = a.nq;
-  for (int p = 0; p < nq; ++p) {
-    const double s = a.rule[p], t = a.rule[nq + p], w = a.rule[2 * nq + p];
-    const double x0 = fma(s, e1i[0], fma(t, e2i[0], vi[0]));
-    const double x1 = fma(s, e1i[1], fma(t, e2i[1], vi[1]));
-    const double x2 = fma(s, e1i[2], fma(t, e2i[2], vi[2]));
-    double ire[3] = {0, 0, 0}, iim[3] = {0, 0, 0};
-    for (int q = 0; q < nq; ++q) {
-      const double u = a.rule[q], v = a.rule[nq + q], wq = a.rule[2 * nq + q];
-      const double y0 = fma(u, e1j[0], fma(v, e2j[0], vj[0]));
-      const double y1 = fma(u, e1j[1], fma(v, e2j[1], vj[1]));
-      const double y2 = fma(u, e1j[2], fma(v, e2j[2], vj[2]));
-      double kre, kim;
-      kernel_value<KERNEL, LAYER>(x0 - y0, x1 - y1, x2 - y2, n, a.kappa, &kre, &kim);
-      const double mu[3] = {1.0 - u, u - v, v};
-#pragma unroll
-      for (int b = 0; b < 3; ++b) {
-        ire[b] = fma(wq * mu[b], kre, ire[b]);
-        if constexpr (KERNEL == BEM_HELMHOLTZ) iim[b] = fma(wq * mu[b], kim, iim[b]);
-      }
-    }
+  regular_rows<KERNEL, LAYER, false, true, XC>(a.geo, a.ldg, a.rule, nq, a.kappa, i, j, sub, G,
+                                               [&](int p, double w, const RowSum &r) {
+    const double *re = LAYER == BEM_SLP ? r.sr : r.dr, *im = LAYER == BEM_SLP ? r.si : r.di;
+    const double s = a.rule[p], t = a.rule[nq + p];
     const double la[3] = {w * (1.0 - s), w * (s - t), w * t};
+    const double br[3] = {re[0] - re[1], re[1] - re[2], re[2]};
+    const double bi[3] = {im[0] - im[1], im[1] - im[2], im[2]};
 #pragma unroll
     for (int k = 0; k < 3; ++k)
 #pragma unroll
       for (int b = 0; b < 3; ++b) {
-        L->re[3 * k + b] = fma(la[k], ire[b], L->re[3 * k + b]);
-        if constexpr (KERNEL == BEM_HELMHOLTZ) L->im[3 * k + b] = fma(la[k], iim[b], L->im[3 * k + b]);
+        L->re[3 * k + b] = fma(la[k], br[b], L->re[3 * k + b]);
+        if constexpr (KERNEL == BEM_HELMHOLTZ) L->im[3 * k + b] = fma(la[k], bi[b], L->im[3 * k + b]);
       }
-  }
-  const double sc = g[G_SG * G + i] * g[G_SG * G + j] * kInv4Pi;
+  });
+  const double *g = a.geo;
+  const double sc = g[G_SG * a.ldg + i] * g[G_SG * a.ldg + j] * kInv4Pi;
   for (int e = 0; e < 9; ++e) L->re[e] *= sc, L->im[e] *= sc;
 }
 
@@ -173,35 +152,46 @@ __device__ __forceinline__ void store9(const P1Args &a, int64_t k, const Acc9<KE
   if (!finite) atomicOr(a.flags, FLAG_NONFINITE);
 }
 
-template <int KERNEL, int LAYER>
+// G lanes per regular pair, as in the kernel of arbitrary entries.
+template <int KERNEL, int LAYER, int G, int XC>
 __global__ __launch_bounds__(kThreads) void k_p1_pairs(const P1Args a) {
-  __shared__ int list[kThreads];
+  constexpr int E = kThreads / G;  // pairs of a workgroup
+  __shared__ int list[E];
   __shared__ int count;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, sub = tid % G;
   if (tid == 0) count = 0;
   __syncthreads();
-  const int64_t e = (int64_t)blockIdx.x * kThreads + tid;
+  const int64_t e = (int64_t)blockIdx.x * E + tid / G;
+  int i = -1, j = -1;
+  bool regular = false;
   if (e < a.n) {
-    const int i = a.rows[e], j = a.cols[e];
+    i = a.rows[e], j = a.cols[e];
     if (i < 0 || i >= a.nt || j < 0 || j >= a.nt) {
       atomicOr(a.flags, FLAG_EINVAL);
     } else {
       const int cls = shared_vertex_count(a.tri[3 * (int64_t)i], a.tri[3 * (int64_t)i + 1],
                                           a.tri[3 * (int64_t)i + 2], a.tri[3 * (int64_t)j],
                                           a.tri[3 * (int64_t)j + 1], a.tri[3 * (int64_t)j + 2]);
-      if (cls) {
-        list[atomicAdd(&count, 1)] = tid;
-      } else {
-        Acc9<KERNEL> L;
-        p1_regular<KERNEL, LAYER>(a, i, j, &L);
-        store9<KERNEL>(a, e, L);
-      }
+      regular = cls == 0;
+      if (cls && sub == 0) list[atomicAdd(&count, 1)] = tid / G;
     }
+  }
+  if (regular) {  // the lanes of a pair together
+    Acc9<KERNEL> L;
+    p1_regular<KERNEL, LAYER, XC>(a, i, j, sub, G, &L);
+#pragma unroll
+    for (int o = G / 2; o >= 1; o /= 2)
+#pragma unroll
+      for (int k = 0; k < 9; ++k) {
+        L.re[k] += __shfl_xor(L.re[k], o, kWave);
+        if constexpr (KERNEL == BEM_HELMHOLTZ) L.im[k] += __shfl_xor(L.im[k], o, kWave);
+      }
+    if (sub == 0) store9<KERNEL>(a, e, L);
   }
   __syncthreads();
   const int ns = count, wave = tid / kWave, lane = tid & (kWave - 1);
   for (int it = wave; it < ns; it += kThreads / kWave) {
-    const int64_t ee = (int64_t)blockIdx.x * kThreads + list[it];
+    const int64_t ee = (int64_t)blockIdx.x * E + list[it];
     const int i = a.rows[ee], j = a.cols[ee];
     const int cls = shared_vertex_count(a.tri[3 * (int64_t)i], a.tri[3 * (int64_t)i + 1],
                                         a.tri[3 * (int64_t)i + 2], a.tri[3 * (int64_t)j],
@@ -224,39 +214,61 @@ __global__ __launch_bounds__(kThreads) void k_p1_gather(const P1GatherArgs a) {
     atomicOr(a.flags, FLAG_EINVAL);
     return;
   }
+  // a row triangle's products kQ at a time: their index and value loads are
+  // issued together (one by one, each waits for the last: 32 us for a block of
+  // 200 x 200 vertices)
+  constexpr int kQ = 8;
   double re = 0.0, im = 0.0;
   for (int p = r0; p < r1; ++p) {
     const int ta = a.rs_tri[p], ka = a.rs_loc[p];
-    for (int q = c0; q < c1; ++q) {
-      const int tb = a.cs_tri[q], kb = a.cs_loc[q];
-      if (ta < 0 || ta >= a.ntr || tb < 0 || tb >= a.ntc || ka < 0 || ka > 2 || kb < 0 || kb > 2) {
-        atomicOr(a.flags, FLAG_EINVAL);
-        continue;
+    const bool row = ta >= 0 && ta < a.ntr && ka >= 0 && ka <= 2;
+    for (int q = c0; q < c1; q += kQ) {
+      int64_t at[kQ];
+      bool ok[kQ];
+#pragma unroll
+      for (int u = 0; u < kQ; ++u) {
+        const bool in = q + u < c1;
+        const int tb = in ? a.cs_tri[q + u] : 0, kb = in ? a.cs_loc[q + u] : 0;
+        ok[u] = row && tb >= 0 && tb < a.ntc && kb >= 0 && kb <= 2;
+        if (in && !ok[u]) atomicOr(a.flags, FLAG_EINVAL);
+        ok[u] = ok[u] && in;
+        at[u] = ((int64_t)ta * a.ntc + tb) * 9 + 3 * ka + kb;
       }
-      const int64_t k = ((int64_t)ta * a.ntc + tb) * 9 + 3 * ka + kb;
-      if (CPLX) {
-        re += static_cast<const double *>(a.local)[2 * k];
-        im += static_cast<const double *>(a.local)[2 * k + 1];
-      } else {
-        re += static_cast<const double *>(a.local)[k];
+      double vr[kQ], vi[kQ];
+#pragma unroll
+      for (int u = 0; u < kQ; ++u) {
+        const double *v = static_cast<const double *>(a.local) + (CPLX ? 2 : 1) * at[u];
+        vr[u] = ok[u] ? v[0] : 0.0;
+        vi[u] = CPLX && ok[u] ? v[1] : 0.0;
       }
+#pragma unroll
+      for (int u = 0; u < kQ; ++u)
+        if (ok[u]) re += vr[u], im += vi[u];
     }
   }
   if (CPLX) static_cast<double2 *>(a.out)[e] = make_double2(re, im);
   else static_cast<double *>(a.out)[e] = re;
 }
 
+// lanes per pair: see the kernel of arbitrary entries
+template <int KERNEL, int LAYER>
+void launch_p1_kl(const P1Args &a, hipStream_t s) {
+  const dim3 block(kThreads);
+  auto grid = [&](int G) { return dim3((unsigned)((a.n * G + kThreads - 1) / kThreads)); };
+  if (a.n < (1 << 15)) hipLaunchKernelGGL((k_p1_pairs<KERNEL, LAYER, 16, 1>), grid(16), block, 0, s, a);
+  else hipLaunchKernelGGL((k_p1_pairs<KERNEL, LAYER, 4, 4>), grid(4), block, 0, s, a);
+}
+
 }  // namespace
 
 hipError_t launch_p1_pairs(int kernel, int layer, const P1Args &a, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
-  const dim3 grid((unsigned)((a.n + kThreads - 1) / kThreads)), block(kThreads);
   if (kernel == BEM_LAPLACE) {
-    if (layer == BEM_SLP) hipLaunchKernelGGL((k_p1_pairs<BEM_LAPLACE, BEM_SLP>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_p1_pairs<BEM_LAPLACE, BEM_DLP>), grid, block, 0, s, a);
+    if (layer == BEM_SLP) launch_p1_kl<BEM_LAPLACE, BEM_SLP>(a, s);
+    else launch_p1_kl<BEM_LAPLACE, BEM_DLP>(a, s);
   } else {
-    if (layer == BEM_SLP) hipLaunchKernelGGL((k_p1_pairs<BEM_HELMHOLTZ, BEM_SLP>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_p1_pairs<BEM_HELMHOLTZ, BEM_DLP>), grid, block, 0, s, a);
+    if (layer == BEM_SLP) launch_p1_kl<BEM_HELMHOLTZ, BEM_SLP>(a, s);
+    else launch_p1_kl<BEM_HELMHOLTZ, BEM_DLP>(a, s);
   }
   return hipGetLastError();
 }

@@ -20,15 +20,15 @@ script to print the coefficients as hexadecimal floats;
 tests/test_host_sincos.py checks the header's against this construction's
 error bounds.
 
-short_phase (|r| <= 1/2, no reduction: phases relative to a reference
-distance) has its own polynomials, T = 1/4: FP64 P and Q of degree 4, FP32 P
-of degree 2 and Q of degree 1.
+short_phase (|r| <= 3/4, no reduction: phases relative to a reference
+distance) has its own polynomials, T = 9/16: FP64 P of degree 5 and Q of
+degree 4, FP32 degree 2 each.
 """
 import numpy as np
 
 L = np.longdouble
 T = L(np.pi / 2) ** 2
-T_SHORT = L(0.25)
+T_SHORT = L(0.5625)
 
 
 def _fact(n):
@@ -154,8 +154,8 @@ def max_rel_error(kind, coefs, npts=200001, T=T):
 if __name__ == "__main__":
     for kind, deg, typ, lim in (("sin", 7, np.float64, T), ("cos", 6, np.float64, T),
                                 ("sin", 3, np.float32, T), ("cos", 3, np.float32, T),
-                                ("sin", 4, np.float64, T_SHORT), ("cos", 4, np.float64, T_SHORT),
-                                ("sin", 2, np.float32, T_SHORT), ("cos", 1, np.float32, T_SHORT)):
+                                ("sin", 5, np.float64, T_SHORT), ("cos", 4, np.float64, T_SHORT),
+                                ("sin", 2, np.float32, T_SHORT), ("cos", 2, np.float32, T_SHORT)):
         c, E = coefficients(kind, deg, lim)
         r = [typ(x) for x in c]
         print(kind, typ.__name__, float(lim), "levelled", E, "rounded", max_rel_error(kind, r, T=lim))

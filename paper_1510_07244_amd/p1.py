@@ -14,24 +14,29 @@ def vertex_stars(tri, vertices):
     triangles with the star entries renumbered into it."""
     tri = np.asarray(tri)
     vertices = np.asarray(vertices, dtype=np.int64)
-    want = np.zeros(int(tri.max()) + 1 if tri.size else 0, dtype=bool)
-    want[vertices] = True
-    t_ids, locs, verts = [], [], []
-    for k in range(3):
-        hit = np.nonzero(want[tri[:, k]])[0]
-        t_ids.append(hit)
-        locs.append(np.full(hit.size, k))
-        verts.append(tri[hit, k])
-    t_ids, locs, verts = np.concatenate(t_ids), np.concatenate(locs), np.concatenate(verts)
-    tset = np.unique(t_ids)
-    where = {int(v): i for i, v in enumerate(vertices)}
-    order = np.lexsort((t_ids, np.array([where[int(v)] for v in verts], dtype=np.int64)))
-    owner = np.array([where[int(v)] for v in verts], dtype=np.int64)[order]
+    pos = np.full(int(tri.max()) + 1 if tri.size else 0, -1, dtype=np.int64)
+    pos[vertices] = np.arange(vertices.size)
+    owner = pos[tri]  # a vertex's number in the list, per corner
+    t_ids, locs = np.nonzero(owner >= 0)
+    owner = owner[t_ids, locs]
+    order = np.argsort(owner, kind="stable")  # by vertex, then triangle
+    used = np.zeros(tri.shape[0], dtype=bool)
+    used[t_ids] = True
+    tset = np.flatnonzero(used)
     ptr = np.zeros(vertices.size + 1, dtype=np.int32)
-    np.add.at(ptr, owner + 1, 1)
-    ptr = np.cumsum(ptr).astype(np.int32)
-    local = np.searchsorted(tset, t_ids[order]).astype(np.int32)
+    np.cumsum(np.bincount(owner, minlength=vertices.size), out=ptr[1:])
+    local = (np.cumsum(used) - 1)[t_ids[order]].astype(np.int32)
     return ptr, local, locs[order].astype(np.int32), tset.astype(np.int32)
+
+
+def _upload(arrays):
+    """int32 device tensors of the arrays: one copy from pinned memory, on the
+    current stream and without waiting for it."""
+    import torch
+    sizes = [a.size for a in arrays]
+    host = torch.empty(sum(sizes), dtype=torch.int32, pin_memory=True)
+    np.concatenate(arrays, out=host.numpy())
+    return host.cuda(non_blocking=True).split(sizes)
 
 
 def p1_block(ctx, mesh, tri, op, row_vertices, col_vertices, stream=None):
@@ -40,15 +45,16 @@ def p1_block(ctx, mesh, tri, op, row_vertices, col_vertices, stream=None):
     sums the local matrices of every triangle around v against every
     triangle around w.  mesh: the device Mesh; tri: its host triangles."""
     import torch
+    from .h2mv import _on
     rp, rt, rl, rset = vertex_stars(tri, row_vertices)
     cp, ct, cl, cset = vertex_stars(tri, col_vertices)
-    R, C = np.meshgrid(rset, cset, indexing="ij")
-    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).cuda()
-    cplx = op.kernel == 1
-    dt = torch.complex128 if cplx else torch.float64
-    local = torch.empty(9 * R.size, dtype=dt, device="cuda")
-    ctx.p1_pairs(mesh, op, dev(R.ravel()), dev(C.ravel()), local, stream)
-    out = torch.empty(len(row_vertices) * len(col_vertices), dtype=dt, device="cuda")
-    ctx.p1_gather(dev(rp), dev(rt), dev(rl), dev(cp), dev(ct), dev(cl), rset.size, cset.size,
-                  local, out, stream)
+    nr, nc = rset.size, cset.size
+    dt = torch.complex128 if op.kernel == 1 else torch.float64
+    with _on(stream):  # copies and allocations in the order of the kernels
+        rp, rt, rl, cp, ct, cl, rset, cset = _upload([rp, rt, rl, cp, ct, cl, rset, cset])
+        local = torch.empty(9 * nr * nc, dtype=dt, device="cuda")
+        ctx.p1_pairs(mesh, op, rset[:, None].expand(nr, nc).reshape(-1),
+                     cset.expand(nr, nc).reshape(-1), local, stream)
+        out = torch.empty(len(row_vertices) * len(col_vertices), dtype=dt, device="cuda")
+        ctx.p1_gather(rp, rt, rl, cp, ct, cl, nr, nc, local, out, stream)
     return out

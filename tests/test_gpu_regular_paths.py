@@ -66,8 +66,8 @@ def test_every_rule_variant(pk, rule, q, kernel, kappa, precision):
     _check(pk, kappa, rule, q, precision, True, kernel=kernel)
 
 
-# 1.75: half of the 128 triangles (radii 0.24 .. 0.33) are short
-@pytest.mark.parametrize("kappa", [0.0, 1e-13, 1e-9, -1.5, 1.75, -1.75, 20.0])
+# radii 0.236 .. 0.333: all triangles short up to 2.24, half of them at 2.6
+@pytest.mark.parametrize("kappa", [0.0, 1e-13, 1e-9, -1.5, 2.24, -2.24, 2.6, 20.0])
 @pytest.mark.parametrize("q", [3, 4])
 @pytest.mark.parametrize("precision", [0, 1])
 def test_short_and_general_phases(pk, kappa, q, precision):
