@@ -638,8 +638,12 @@ __global__ __launch_bounds__(kThreads, 2) void k_blocks_learned(const BlockArgs 
   if (!block_header(a, blockIdx.x, &h) || h.nr == 0 || h.nc == 0) return;
   const Lds l = carve<false>(lds_raw, a.nq_pad, a.tr, a.tc);
   h.brief = block_is_brief<KERNEL>(a, l, h);
+  unsigned turn = blockIdx.y;  // as k_blocks
   for (int64_t r0 = 0; r0 < h.nr; r0 += a.tr)
-    for (int64_t c0 = 0; c0 < h.nc; c0 += a.tc) subtile_learned<KERNEL, LAYER>(a, o, l, h, r0, c0);
+    for (int64_t c0 = 0; c0 < h.nc; c0 += a.tc) {
+      if (turn == 0) subtile_learned<KERNEL, LAYER>(a, o, l, h, r0, c0);
+      turn = turn == 0 ? gridDim.y - 1 : turn - 1;
+    }
 }
 
 template <int KERNEL, int LAYER, int RULE, bool MIXED>
@@ -650,9 +654,13 @@ __global__ __launch_bounds__(kThreads, 2) void k_blocks(const BlockArgs a, const
   const Lds l = carve<MIXED>(lds_raw, a.nq_pad, a.tr, a.tc, LAYER == kBoth);
   h.brief = block_is_brief<KERNEL>(a, l, h);
   load_rule(a, l);
+  // the block's sub-tiles, dealt to gridDim.y workgroups
+  unsigned turn = blockIdx.y;
   for (int64_t r0 = 0; r0 < h.nr; r0 += a.tr)
-    for (int64_t c0 = 0; c0 < h.nc; c0 += a.tc)
-      subtile<KERNEL, LAYER, RULE, MIXED>(a, l, h, r0, c0, coupling);
+    for (int64_t c0 = 0; c0 < h.nc; c0 += a.tc) {
+      if (turn == 0) subtile<KERNEL, LAYER, RULE, MIXED>(a, l, h, r0, c0, coupling);
+      turn = turn == 0 ? gridDim.y - 1 : turn - 1;
+    }
 }
 
 // Persistent form: every workgroup pops work items (batch, block, r0, c0) --
@@ -748,7 +756,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_persistent(const BlockArgs *__r
 
 template <int KERNEL, bool MIXED, int RULE>
 hipError_t launch_rule(int layer, bool coupling, const BlockArgs &a, size_t lds, hipStream_t s) {
-  const dim3 grid(a.nblocks), block(kThreads);
+  const dim3 grid(a.nblocks, a.split), block(kThreads);
   const int cp = coupling ? 1 : 0;
   if (layer == BEM_SLP) hipLaunchKernelGGL((k_blocks<KERNEL, BEM_SLP, RULE, MIXED>), grid, block, lds, s, a, cp);
   else if (layer == BEM_DLP) hipLaunchKernelGGL((k_blocks<KERNEL, BEM_DLP, RULE, MIXED>), grid, block, lds, s, a, cp);
@@ -794,7 +802,7 @@ hipError_t PersistentLaunch<KERNEL, MIXED>::run(int rule, const PersistentArgs &
 template <int KERNEL>
 hipError_t LearnedLaunch<KERNEL>::run(int layer, const BlockArgs &a, const OrderRules &o, size_t lds,
                                       hipStream_t s) {
-  const dim3 grid(a.nblocks), block(kThreads);
+  const dim3 grid(a.nblocks, a.split), block(kThreads);
   if (layer == BEM_SLP) hipLaunchKernelGGL((k_blocks_learned<KERNEL, BEM_SLP>), grid, block, lds, s, a, o);
   else hipLaunchKernelGGL((k_blocks_learned<KERNEL, BEM_DLP>), grid, block, lds, s, a, o);
   return hipGetLastError();

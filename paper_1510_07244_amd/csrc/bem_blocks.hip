@@ -3,6 +3,8 @@
 // bem_learned_*.hip).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "bem_block_core.h"
 #include "bem_block_launch.h"
 
@@ -73,6 +75,34 @@ bool block_tile_shape(int nq_pad, bool mixed, size_t lds_budget, int *tr, int *t
     return false;
   };
   return lists ? try_list(near_shapes, 7) : try_list(coupling_shapes, 11);
+}
+
+// Workgroups per block, and narrower sub-tiles, for a launch of few blocks.
+// The chip holds 512 workgroups at once (256 CUs, two by registers); from
+// that many blocks on, one workgroup each is better (it stages a block's
+// geometry once).  Below it a block's sub-tiles are dealt to several
+// workgroups, and their columns halved (to 8 at the least, which still gives
+// every thread an entry per pass) until the list has about 1024 sub-tiles:
+// two rounds, so that unequal ones even out.  The number of sub-tiles is the
+// mean block's; any split is correct, larger blocks give their workgroups
+// several turns.  At most 4096 workgroups in all: what a workgroup reads of
+// its whole block (the Helmholtz phase kind) stays small.
+// 64 Laplace blocks of 64 x 64, seven points, both kinds of split: 70 -> 25 us;
+// double layer, order 5: 420 -> 111; mixed Helmholtz coupling, 64 blocks:
+// 497 -> 158; near field in 376 blocks: 231 -> 191; aiming at 512 or 2048
+// sub-tiles instead: 183 / 160 against 156 us for 419 coupling blocks; the
+// split from 880 blocks on instead of below 512: 1318 -> 1870 us.
+int split_blocks(const BlockArgs &a, bool mixed, bool lists, bool both, int *tc, size_t *lds_bytes) {
+  constexpr int64_t kFull = 512, kTiles = 1024, kMost = 4096;
+  if (a.nblocks >= kFull || a.nblocks <= 0) return 1;
+  const int64_t mr = std::max<int64_t>(a.row_len / a.nblocks, 1);
+  const int64_t mc = std::max<int64_t>(a.col_len / a.nblocks, 1);
+  const int64_t down = (mr + a.tr - 1) / a.tr;
+  int c = *tc;
+  while (c > 8 && a.nblocks * down * ((mc + c - 1) / c) < kTiles) c = std::max(8, c / 2);
+  *tc = c;
+  *lds_bytes = block_lds_bytes(a.nq_pad, a.tr, c, mixed, lists, both);
+  return (int)std::min<int64_t>(down * ((mc + c - 1) / c), kMost / a.nblocks);
 }
 
 hipError_t launch_blocks(int kernel, int layer, int rule, bool coupling, bool mixed,
