@@ -20,12 +20,26 @@ using namespace dev;
 //   side 1:  sqrt(w) int d/dn(x) g(x, z) dx, sqrt(w) delta int d/dn(x) d/dn(z) g(x, z) dx
 // (side 1 is the column basis of the double layer).  Triangle integrals use
 // the Duffy rule: int_tau f = sqrt(g) sum_k w_k f(Phi(s_k, t_k)).
-// A thread takes one row triangle and kGreenPerThread Green points: the rule
-// points x_k on the triangle are formed once and used for every Green point.
+// A thread takes one row triangle and kGreenPerThread Green points.  With X =
+// v0 - z the squared distance at the rule point (s, t) is
+//   |X|^2 + 2 s <X, e1> + 2 t <X, e2> + |s e1 + t e2|^2,
+// whose last term all Green points share, <x - z, n_z> is linear in s and t
+// and <x - z, n_x> the constant <X, n_x>: 14 (side 0) and 15 (side 1) FP64
+// operations and a reciprocal root per evaluation for Laplace.  The rule comes
+// by scalar loads.  Workgroups of one wave: their number comes from the
+// largest cluster, and those past a smaller cluster's rows end at once without
+// three other waves' places.  Bound by these operations (about 65 % of the
+// time busy; the rest is each wave's chain of index, geometry and point loads
+// and the last round).  340 clusters of 23 to 230 rows (27363 in all), 96
+// Green points, 16 rule points, side 0 / 1: 62 / 75 us with differences taken
+// per evaluation, 54 / 53 with four waves per workgroup, 48 / 51 with one;
+// two Green points per thread 49 / 54, workgroups numbered by the mean
+// cluster 52 / 55.
 constexpr int kGreenPerThread = 4;
+constexpr int kGreenThreads = kWave;
 
 template <int KERNEL, int SIDE>
-__global__ __launch_bounds__(kThreads) void k_green(const GreenArgs a) {
+__global__ __launch_bounds__(kGreenThreads) void k_green(const GreenArgs a) {
   constexpr int J = kGreenPerThread;
   const int c = blockIdx.x;
   const int64_t rp0 = a.row_ptr[c], rp1 = a.row_ptr[c + 1];
@@ -40,89 +54,98 @@ __global__ __launch_bounds__(kThreads) void k_green(const GreenArgs a) {
   }
   const double delta = a.delta[c];
   const int64_t L = a.ldg;
+  const uniform_ptr R = (uniform_ptr)a.rule;
+  const int64_t items = n * mg;
+  auto dot = [](const double *x, const double *y) { return fma(x[0], y[0], fma(x[1], y[1], x[2] * y[2])); };
   // the work items (row, group of J Green points) of one cluster are spread
   // over gridDim.y workgroups; consecutive threads take consecutive rows
-  for (int64_t e = (int64_t)blockIdx.y * kThreads + threadIdx.x; e < n * mg;
-       e += (int64_t)gridDim.y * kThreads) {
-    const int64_t r = e % n;
-    const int nu0 = (int)(e / n) * J;
+  for (int64_t e = (int64_t)blockIdx.y * kGreenThreads + threadIdx.x; e < items;
+       e += (int64_t)gridDim.y * kGreenThreads) {
+    const int64_t g = items <= UINT32_MAX ? (int64_t)((uint32_t)e / (uint32_t)n) : e / n;
+    const int64_t r = e - g * n;
+    const int nu0 = (int)g * J;
     const int id = a.row_idx[rp0 + r];
     if (id < 0 || id >= a.nt) {
       atomicOr(a.flags, FLAG_EINVAL);
       continue;
     }
-    double zx[J], zy[J], zz[J], mx[J], my[J], mz[J], wz[J];
+    double v0[3], e1[3], e2[3], nx[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      v0[d] = a.geo[(G_V0X + d) * L + id];
+      e1[d] = a.geo[(G_E1X + d) * L + id];
+      e2[d] = a.geo[(G_E2X + d) * L + id];
+      if (SIDE == 1) nx[d] = a.geo[(G_NX + d) * L + id];
+    }
+    const double sg = a.geo[G_SG * L + id];
+    const double g11 = dot(e1, e1), g12 = 2.0 * dot(e1, e2), g22 = dot(e2, e2);
+    double c0[J], c1[J], c2[J], d0[J], d1[J], d2[J], dnx[J], nn[J], wz[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) {
       const int nu = min(nu0 + j, m - 1);  // past m: a copy, not written
       const double *zp = a.z + 3 * ((int64_t)c * m + nu);
       const double *np = a.zn + 3 * ((int64_t)c * m + nu);
-      zx[j] = zp[0], zy[j] = zp[1], zz[j] = zp[2];
-      mx[j] = np[0], my[j] = np[1], mz[j] = np[2];
       wz[j] = a.zw[(int64_t)c * m + nu];
+      const double X[3] = {v0[0] - zp[0], v0[1] - zp[1], v0[2] - zp[2]};
+      const double N[3] = {np[0], np[1], np[2]};
+      c0[j] = dot(X, X), c1[j] = 2.0 * dot(X, e1), c2[j] = 2.0 * dot(X, e2);
+      d0[j] = dot(X, N), d1[j] = dot(e1, N), d2[j] = dot(e2, N);  // <x - z, n_z>
+      if (SIDE == 1) dnx[j] = dot(X, nx), nn[j] = dot(nx, N);
     }
-    const double v0x = a.geo[G_V0X * L + id], v0y = a.geo[G_V0Y * L + id], v0z = a.geo[G_V0Z * L + id];
-    const double e1x = a.geo[G_E1X * L + id], e1y = a.geo[G_E1Y * L + id], e1z = a.geo[G_E1Z * L + id];
-    const double e2x = a.geo[G_E2X * L + id], e2y = a.geo[G_E2Y * L + id], e2z = a.geo[G_E2Z * L + id];
-    const double nx = a.geo[G_NX * L + id], ny = a.geo[G_NY * L + id], nz = a.geo[G_NZ * L + id];
-    double pr[J], pi[J], qr[J], qi[J];  // + and - columns
+    // side 0: the two columns' sums; side 1: p is the sum of the first
+    // column without -<x - z, n_x>, q that of <x - z, n_z> times the second
+    // derivative's remaining factor
+    double pr[J], pi[J], qr[J], qi[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) pr[j] = pi[j] = qr[j] = qi[j] = 0.0;
     for (int k = 0; k < a.nq; ++k) {
-      const double s = a.rule[k], t = a.rule[a.nq + k], w = a.rule[2 * a.nq + k];
-      // the rule point x = v0 + s e1 + t e2 on the triangle
-      const double px = fma(s, e1x, fma(t, e2x, v0x));
-      const double py = fma(s, e1y, fma(t, e2y, v0y));
-      const double pz = fma(s, e1z, fma(t, e2z, v0z));
+      const double s = R[k], t = R[a.nq + k], w = R[2 * a.nq + k];
+      const double gk = fma(s, fma(s, g11, t * g12), t * t * g22);
 #pragma unroll
       for (int j = 0; j < J; ++j) {
-        const double dx = px - zx[j], dy = py - zy[j], dz = pz - zz[j];
-        const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
+        const double r2 = fma(t, c2[j], fma(s, c1[j], c0[j] + gk));
+        const double dn = fma(t, d2[j], fma(s, d1[j], d0[j]));
         const double iz = rsqrt_newton(r2);  // 1 / r
-        const double i3 = iz * iz * iz;
-        const double dnz = fma(dx, mx[j], fma(dy, my[j], dz * mz[j]));  // <x - z, n_z>
-        const double dnx = fma(dx, nx, fma(dy, ny, dz * nz));           // <x - z, n_x>
+        const double wi = w * iz, i2 = iz * iz, wi3 = wi * i2;
         if constexpr (KERNEL == BEM_LAPLACE) {
-          if constexpr (SIDE == 0) {
-            pr[j] = fma(w, iz, pr[j]);
-            qr[j] = fma(w, dnz * i3, qr[j]);
-          } else {
-            const double nn = fma(nx, mx[j], fma(ny, my[j], nz * mz[j]));
-            pr[j] = fma(w, -dnx * i3, pr[j]);
-            qr[j] = fma(w, fma(-3.0 * dnx * dnz, iz * iz, nn) * i3, qr[j]);
-          }
+          pr[j] += SIDE == 0 ? wi : wi3;
+          qr[j] = fma(SIDE == 0 ? wi3 : wi3 * i2, dn, qr[j]);
         } else {
-          const double r = r2 * iz, kr = a.kappa * r;
+          const double kr = a.kappa * (r2 * iz);
           double sn, cs;
           sincos_cw(kr, &sn, &cs);
           // e^{ikr} (1 - i kr) = (cs + kr sn) + i (sn - kr cs)
           const double ar = fma(kr, sn, cs), ai = fma(-kr, cs, sn);
           if constexpr (SIDE == 0) {
-            pr[j] = fma(w * iz, cs, pr[j]);
-            pi[j] = fma(w * iz, sn, pi[j]);
-            qr[j] = fma(w * dnz * i3, ar, qr[j]);
-            qi[j] = fma(w * dnz * i3, ai, qi[j]);
+            const double wd = wi3 * dn;
+            pr[j] = fma(wi, cs, pr[j]);
+            pi[j] = fma(wi, sn, pi[j]);
+            qr[j] = fma(wd, ar, qr[j]);
+            qi[j] = fma(wd, ai, qi[j]);
           } else {
-            const double nn = fma(nx, mx[j], fma(ny, my[j], nz * mz[j]));
-            pr[j] = fma(-w * dnx * i3, ar, pr[j]);
-            pi[j] = fma(-w * dnx * i3, ai, pi[j]);
-            // e^{ikr} [ (1 - i kr) nn / r^3 + (k^2 r^2 - 3 + 3 i kr) dnx dnz / r^5 ]
-            const double u = dnx * dnz * iz * iz;
-            const double br = fma(kr, kr, -3.0), bi = 3.0 * kr;
-            const double tr = fma(nn, 1.0, u * br), ti = fma(-nn, kr, u * bi);  // (1 - i kr) nn + u (br + i bi)
-            qr[j] = fma(w * i3, cs * tr - sn * ti, qr[j]);
-            qi[j] = fma(w * i3, sn * tr + cs * ti, qi[j]);
+            // e^{ikr} [ (1 - i kr) nn / r^3 + (k^2 r^2 - 3 + 3 i kr) dnx dn / r^5 ]
+            const double wd = wi3 * i2 * dn, br = fma(kr, kr, -3.0), bi = 3.0 * kr;
+            pr[j] = fma(wi3, ar, pr[j]);
+            pi[j] = fma(wi3, ai, pi[j]);
+            qr[j] = fma(wd, fma(cs, br, -sn * bi), qr[j]);
+            qi[j] = fma(wd, fma(sn, br, cs * bi), qi[j]);
           }
         }
       }
     }
-    const double sg = a.geo[G_SG * L + id];
 #pragma unroll
     for (int j = 0; j < J; ++j) {
       const int nu = nu0 + j;
       if (nu >= m) break;
       const double sp = sqrt(wz[j]) * sg * kInv4Pi, sm = sp * delta;
       const int64_t ip = off + r + n * nu, im = off + r + n * (m + nu);
+      if constexpr (SIDE == 1) {
+        const double f = (KERNEL == BEM_LAPLACE ? -3.0 : 1.0) * dnx[j];
+        qr[j] = fma(nn[j], pr[j], f * qr[j]);
+        qi[j] = fma(nn[j], pi[j], f * qi[j]);
+        pr[j] *= -dnx[j];
+        pi[j] *= -dnx[j];
+      }
       if constexpr (KERNEL == BEM_LAPLACE) {
         static_cast<double *>(a.out)[ip] = pr[j] * sp;
         static_cast<double *>(a.out)[im] = qr[j] * sm;
@@ -484,7 +507,7 @@ hipError_t launch_pivot_inverse(bool cplx, const PivInvArgs &a, hipStream_t s) {
 
 hipError_t launch_green(int kernel, int side, const GreenArgs &a, int grid_y, hipStream_t s) {
   if (a.ncl == 0) return hipSuccess;
-  const dim3 grid(a.ncl, grid_y < 1 ? 1 : grid_y), block(kThreads);
+  const dim3 grid(a.ncl, grid_y < 1 ? 1 : grid_y), block(kGreenThreads);
   if (kernel == BEM_LAPLACE) {
     if (side == 0) hipLaunchKernelGGL((k_green<BEM_LAPLACE, 0>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((k_green<BEM_LAPLACE, 1>), grid, block, 0, s, a);
