@@ -78,31 +78,42 @@ bool block_tile_shape(int nq_pad, bool mixed, size_t lds_budget, int *tr, int *t
 }
 
 // Workgroups per block, and narrower sub-tiles, for a launch of few blocks.
-// The chip holds 512 workgroups at once (256 CUs, two by registers); from
-// that many blocks on, one workgroup each is better (it stages a block's
-// geometry once).  Below it a block's sub-tiles are dealt to several
-// workgroups, and their columns halved (to 8 at the least, which still gives
-// every thread an entry per pass) until the list has about 1024 sub-tiles:
-// two rounds, so that unequal ones even out.  The number of sub-tiles is the
-// mean block's; any split is correct, larger blocks give their workgroups
-// several turns.  At most 4096 workgroups in all: what a workgroup reads of
-// its whole block (the Helmholtz phase kind) stays small.
-// 64 Laplace blocks of 64 x 64, seven points, both kinds of split: 70 -> 25 us;
-// double layer, order 5: 420 -> 111; mixed Helmholtz coupling, 64 blocks:
-// 497 -> 158; near field in 376 blocks: 231 -> 191; aiming at 512 or 2048
-// sub-tiles instead: 183 / 160 against 156 us for 419 coupling blocks; the
-// split from 880 blocks on instead of below 512: 1318 -> 1870 us.
-int split_blocks(const BlockArgs &a, bool mixed, bool lists, bool both, int *tc, size_t *lds_bytes) {
-  constexpr int64_t kFull = 512, kTiles = 1024, kMost = 4096;
-  if (a.nblocks >= kFull || a.nblocks <= 0) return 1;
+// The chip holds 512 workgroups at once (256 CUs, two by registers).  Well
+// above that one workgroup per block is best: it stages a block's geometry
+// once.  Below, and for the first unequal round beyond, a block's sub-tiles
+// are dealt to several workgroups, so that idle CUs take part of the large
+// blocks; the number is that of the mean block's sub-tiles, or twice it for
+// the larger ones (any number is correct).  At most 4096 workgroups in all:
+// what one reads of its whole block (the Helmholtz phase kind) stays small.
+//
+// Coupling blocks are mostly one sub-tile: below 768 blocks its columns are
+// halved until there are 1536 (Helmholtz, order 3, 523 blocks: 436 us whole,
+// 332 aiming at 1024, 267 at 1536; 632 blocks 456, 373, 331; Laplace double
+// layer, 410 blocks 255, 177, 172); from 768 to 1023 blocks only the larger
+// ones are dealt out (909 blocks 520 -> 472, halved too 532; 838 blocks 340 ->
+// 332); 1143 blocks lose by it (572 -> 597).
+// Near-field sub-tiles collect their singular pairs class by class, each class
+// padded to a wave: narrower ones pay that again (mixed Helmholtz, 376 blocks:
+// 420 us whole, 287 dealt out, 323 and 409 aiming at 512 and 1024 narrower
+// ones).  So only lists of fewer than 320 blocks are narrowed, to 512 (64
+// Laplace blocks of 64 x 64, seven points: 70 us whole, 43 aiming at 128, 29 at
+// 256, 26 at 512); up to 767 blocks are dealt out (both layers, 556 blocks: 386
+// -> 312; 674 blocks 377 -> 324); 1041 lose by it (1236 -> 1315).
+int split_blocks(const BlockArgs &a, bool coupling, bool mixed, bool lists, bool both, int *tc,
+                 size_t *lds_bytes) {
+  constexpr int64_t kDealt = 768, kDealtCoupling = 1024, kNarrow = 320, kMost = 4096;
+  if (a.nblocks <= 0 || a.nblocks >= (coupling ? kDealtCoupling : kDealt)) return 1;
   const int64_t mr = std::max<int64_t>(a.row_len / a.nblocks, 1);
   const int64_t mc = std::max<int64_t>(a.col_len / a.nblocks, 1);
   const int64_t down = (mr + a.tr - 1) / a.tr;
+  const bool narrow = a.nblocks < (coupling ? kDealt : kNarrow);
+  const int64_t tiles = !narrow ? 0 : coupling ? 1536 : 512;
   int c = *tc;
-  while (c > 8 && a.nblocks * down * ((mc + c - 1) / c) < kTiles) c = std::max(8, c / 2);
+  while (c > 8 && a.nblocks * down * ((mc + c - 1) / c) < tiles) c = std::max(8, c / 2);
   *tc = c;
   *lds_bytes = block_lds_bytes(a.nq_pad, a.tr, c, mixed, lists, both);
-  return (int)std::min<int64_t>(down * ((mc + c - 1) / c), kMost / a.nblocks);
+  const int64_t turns = coupling && narrow ? 1 : 2;
+  return (int)std::min<int64_t>(turns * down * ((mc + c - 1) / c), kMost / a.nblocks);
 }
 
 hipError_t launch_blocks(int kernel, int layer, int rule, bool coupling, bool mixed,

@@ -363,7 +363,8 @@ bool block_tile_shape(int nq_pad, bool mixed, size_t lds_budget, int *tr, int *t
 size_t block_lds_bytes(int nq_pad, int tr, int tc, bool mixed, bool lists = true,
                        bool both = false);
 // smaller sub-tiles and workgroups per block for a launch of few blocks
-int split_blocks(const BlockArgs &a, bool mixed, bool lists, bool both, int *tc, size_t *lds_bytes);
+int split_blocks(const BlockArgs &a, bool coupling, bool mixed, bool lists, bool both, int *tc,
+                 size_t *lds_bytes);
 int rule_chunk(int nq, int kernel);
 // kernel variant of a rule (regular_rule, order, points) and its padded points
 int rule_variant(int regular_rule, int q, int nq);

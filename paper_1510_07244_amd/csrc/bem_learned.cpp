@@ -292,7 +292,7 @@ int bem_assemble_nearfield_learned(bem_ctx *ctx, const bem_mesh *mesh, const bem
   size_t lds;
   if (!block_tile_shape(a.nq_pad, false, ctx->lds_budget, &a.tr, &a.tc, &lds))
     return fail(ctx, BEM_EUNSUPPORTED, "quadrature order too high for the LDS budget");
-  a.split = split_blocks(a, false, true, false, &a.tc, &lds);
+  a.split = split_blocks(a, false, false, true, false, &a.tc, &lds);
   a.ss = ss_args(*plain);
   a.kappa = op->kernel == BEM_HELMHOLTZ ? op->kappa : 0.0;
   a.flags = ctx->flags;

@@ -44,3 +44,34 @@ def test_few_blocks_equal_many(size, kernel, layer, precision):
     ctx.close()
     tol = 1e-6 if precision else 1e-13
     assert np.linalg.norm(got - want) <= tol * np.linalg.norm(want)
+
+
+# 320 blocks and more keep their shape, 768 and more one workgroup each
+@pytest.mark.parametrize("nblocks", [319, 320, 767, 768, 1023, 1024])
+@pytest.mark.parametrize("coupling", [False, True])
+def test_lists_around_the_limits(nblocks, coupling):
+    import torch
+    import paper_1510_07244_amd as pk
+    m = octahedron_sphere(4)
+    mesh = pk.Mesh(torch.from_numpy(m.v), torch.from_numpy(m.tri))
+    op = pk.make_op(0, 0, q_regular=3)
+    # two kinds of block, alternating: 7 x 90 and 90 x 7, without touching
+    # pairs (coupling launches refuse them)
+    small = np.arange(7, dtype=np.int32)
+    apart = ~np.isin(m.tri, m.tri[small]).any(1)
+    large = np.nonzero(apart)[0][:90].astype(np.int32)
+    rows = [small if k % 2 else large for k in range(nblocks)]
+    cols = [large if k % 2 else small for k in range(nblocks)]
+    blocks, total = pk.Blocks.from_lists(rows, cols)
+    out = torch.full((total,), float("nan"), dtype=torch.float64, device="cuda")
+    ctx = pk.Context(0)
+    run = ctx.assemble_coupling if coupling else ctx.assemble_nearfield
+    run(mesh, op, blocks, out)
+    ctx.check()
+    ctx.close()
+    got = out.cpu().numpy().reshape(nblocks, 630)
+    # the single layer is symmetric: both kinds hold the same entries
+    a, b = got[0].reshape(7, 90).T, got[1].reshape(90, 7).T
+    scale = np.abs(a).max()
+    assert np.abs(a - b.T).max() <= 1e-13 * scale
+    assert (got[0::2] == got[0]).all() and (got[1::2] == got[1]).all()
