@@ -334,9 +334,12 @@ inline __device__ DuffyPtr<float>::type DuffyPtr<float>::of(const double *t) { r
 // pair 1/2 +- delta three (2 to 2.4 per point pair, from 4 for coordinates of
 // every x-point); equal weights of a pair are applied once, to its sum.  The
 // rule's constants are wave-uniform (scalar registers).
-// Laplace to order 4: every xi unrolled, products of constants and the double
-// layer's point weights w <X - Y, n_j> (w (n0 + xi na +- xi delta nb)) kept.
-// Else (ROLL) one xi at a time in a loop: unrolled, the chains of Q^2 sines
+// Laplace: every xi unrolled, products of constants and the double layer's
+// point weights w <X - Y, n_j> (w (n0 + xi na +- xi delta nb)) kept (up to 72
+// of 229 registers, no spills; a loop over xi instead, order 5 / 6: coupling of
+// 6272 triangles, double layer 3.36 / 6.76 -> 4.21 / 8.64 ms, single layer 1.41 /
+// 3.13 -> 1.62 / 3.23, one-pass near field 1.03 / 2.03 -> 1.17 / 2.18).
+// Helmholtz (ROLL) one xi at a time in a loop: unrolled, the chains of Q^2 sines
 // and cosines spill (the 32768-triangle Helmholtz near field took 34 ms);
 // the double layer's weights are formed at every point pair, or (both layers)
 // their three terms summed separately and combined per column point.
@@ -354,7 +357,7 @@ __device__ __forceinline__ void duffy_sums(const EntryGeo &g, const double *tabl
   typedef DuffyAt<Q> C;
   constexpr int H = C::H, HC = C::HC;
   constexpr bool ODD = Q & 1, HELM = KERNEL == BEM_HELMHOLTZ;
-  constexpr bool ROLL = HELM || Q >= 5;
+  constexpr bool ROLL = HELM;
   constexpr bool LIN = ROLL && LAYER == kBoth;    // double-layer weights in three sums
   constexpr bool FLY = ROLL && LAYER == BEM_DLP;  // formed at every point pair
   const typename DuffyPtr<T>::type c = DuffyPtr<T>::of(table);
