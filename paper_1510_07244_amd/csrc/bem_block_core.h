@@ -334,15 +334,23 @@ inline __device__ DuffyPtr<float>::type DuffyPtr<float>::of(const double *t) { r
 // pair 1/2 +- delta three (2 to 2.4 per point pair, from 4 for coordinates of
 // every x-point); equal weights of a pair are applied once, to its sum.  The
 // rule's constants are wave-uniform (scalar registers).
-// Laplace: every xi unrolled, products of constants and the double layer's
-// point weights w <X - Y, n_j> (w (n0 + xi na +- xi delta nb)) kept (up to 72
-// of 229 registers, no spills; a loop over xi instead, order 5 / 6: coupling of
-// 6272 triangles, double layer 3.36 / 6.76 -> 4.21 / 8.64 ms, single layer 1.41 /
-// 3.13 -> 1.62 / 3.23, one-pass near field 1.03 / 2.03 -> 1.17 / 2.18).
-// Helmholtz (ROLL) one xi at a time in a loop: unrolled, the chains of Q^2 sines
-// and cosines spill (the 32768-triangle Helmholtz near field took 34 ms);
-// the double layer's weights are formed at every point pair, or (both layers)
-// their three terms summed separately and combined per column point.
+// Every xi unrolled, products of constants and the double layer's point weights
+// w <X - Y, n_j> (w (n0 + xi na +- xi delta nb)) kept: up to 72 of 229 registers
+// for Laplace, no spills (a loop over xi instead, order 5 / 6: coupling of 6272
+// triangles, double layer 3.36 / 6.76 -> 4.21 / 8.64 ms, single layer 1.41 / 3.13
+// -> 1.62 / 3.23, one-pass near field 1.03 / 2.03 -> 1.17 / 2.18).  Helmholtz
+// with the scheduling held to one xi (free, the chains of Q^2 sines and
+// cosines spill); 4608 triangles, loop -> unrolled: coupling, double layer,
+// order 3 / 4 / 5 / 6: 1.28 / 3.27 / 7.50 / 15.1 -> 1.16 / 3.06 / 7.09 / 14.4 ms,
+// single layer 0.63 / 1.42 -> 0.57 / 1.39 and no gain from order 5 on (3.21,
+// 6.64 -> 3.21, 6.67), one-pass near field, order 5: 2.44 -> 2.36.
+// ROLL, the loop, where unrolling does not pay: Helmholtz single layer from
+// order 5, and FP32 Helmholtz but for the double layer up to order 4 (single
+// layer with general phases 2.19 -> 2.31 ms; one kernel for all layers, step of
+// 3200 triangles with the double layer unrolled, order 5 / 6: 3.61 / 6.87 -> 3.73
+// / 7.43).  There the double layer's weights are formed at every point pair
+// (their terms summed separately: 4.20 -> 4.40 ms), or (both layers) their
+// three terms are summed separately and combined per column point.
 // Per point pair (FP64 instructions, v_rsq_f64 as four): Laplace single, double,
 // both layers 12, 14, 16 -> 10.3, 12.8, 15.2; Helmholtz 46, 50, 55 -> 28, 34,
 // 43 with short phases.  Vector units 94 % busy (18432 triangles, Helmholtz
@@ -357,7 +365,8 @@ __device__ __forceinline__ void duffy_sums(const EntryGeo &g, const double *tabl
   typedef DuffyAt<Q> C;
   constexpr int H = C::H, HC = C::HC;
   constexpr bool ODD = Q & 1, HELM = KERNEL == BEM_HELMHOLTZ;
-  constexpr bool ROLL = HELM;
+  constexpr bool FP64 = std::is_same<T, double>::value;
+  constexpr bool ROLL = HELM && (FP64 ? LAYER == BEM_SLP && Q >= 5 : LAYER != BEM_DLP || Q >= 5);
   constexpr bool LIN = ROLL && LAYER == kBoth;    // double-layer weights in three sums
   constexpr bool FLY = ROLL && LAYER == BEM_DLP;  // formed at every point pair
   const typename DuffyPtr<T>::type c = DuffyPtr<T>::of(table);
@@ -415,7 +424,7 @@ __device__ __forceinline__ void duffy_sums(const EntryGeo &g, const double *tabl
     sincos_cw((double)kr00, &s0, &c0);
   }
   EntrySums<KERNEL, LAYER, SHORT, T> sum;
-  for_points<ROLL>(pts, Q * Q, [&](const typename PTS::P &pt) {
+  for_points<HELM>(pts, Q * Q, [&](const typename PTS::P &pt) {
     T y[3], wy;
     PTS::unpack(pt, y, &wy);
     const T D0 = M::mad(mf, y[0], V0), D1 = M::mad(mf, y[1], V1), D2 = M::mad(mf, y[2], V2);
@@ -499,6 +508,10 @@ __device__ __forceinline__ void duffy_sums(const EntryGeo &g, const double *tabl
             } else {
               ps.t2r = M::mad(WN[ROLL ? 0 : j][a], ar, ps.t2r);
               if (two) ps.t2r = M::mad(WN[ROLL ? 0 : j][a + 1], br, ps.t2r);
+              if constexpr (HELM) {
+                ps.t2i = M::mad(WN[ROLL ? 0 : j][a], ai, ps.t2i);
+                if (two) ps.t2i = M::mad(WN[ROLL ? 0 : j][a + 1], bi, ps.t2i);
+              }
             }
           }
         }
@@ -536,7 +549,11 @@ __device__ __forceinline__ void duffy_sums(const EntryGeo &g, const double *tabl
       }
     } else {
 #pragma unroll
-      for (int j = 0; j < Q; ++j) row(j, c[4 * j], c[4 * j + 1], (T)0, (T)0);
+      for (int j = 0; j < Q; ++j) {
+        row(j, c[4 * j], c[4 * j + 1], (T)0, (T)0);
+        // one xi's chains at a time: scheduled across, they spill
+        if constexpr (HELM) __builtin_amdgcn_sched_barrier(0);
+      }
     }
     if constexpr (LIN) {
       ps.t2r = M::mad(n0, ps.t1r, M::mad(na, txr, nb * tbr));
