@@ -162,6 +162,27 @@ struct PointsLds32 {
   static __device__ __forceinline__ void unpack(const P &q, float *y, float *w) { y[0] = q.x, y[1] = q.y, y[2] = q.z, *w = q.w; }
 };
 
+// Column points formed from the triangle in LDS (2 (v0 - origin), 2 e1, 2 e2,
+// sqrt(g), a stride apart) and the rule r[3][n] read by scalar loads.
+constexpr int kColumnFields = 10;
+struct PointsOfRule {
+  const double *c;
+  int stride;
+  uniform_ptr r;
+  int n;
+  struct P { double y[3], w; };
+  __device__ __forceinline__ P get(int b) const {
+    const double s = r[b], t = r[n + b];
+    P p;
+#pragma unroll
+    for (int m = 0; m < 3; ++m)
+      p.y[m] = fma(s, c[(3 + m) * stride], fma(t, c[(6 + m) * stride], c[m * stride]));
+    p.w = r[2 * n + b] * c[9 * stride];
+    return p;
+  }
+  static __device__ __forceinline__ void unpack(const P &q, double *y, double *w) { y[0] = q.y[0], y[1] = q.y[1], y[2] = q.y[2], *w = q.w; }
+};
+
 // Two points per step, the next one's LDS reads issued before the current
 // one's arithmetic (no register copies between steps).
 // ONE: one point per step with the copies (a third copy of a long body, for

@@ -530,24 +530,25 @@ __device__ void subtile(const BlockArgs &a, const Lds &l, const BlockHdr &h, int
   }
 }
 
-template <int KERNEL, int LAYER>
-__device__ __forceinline__ void regular_sums_q(int q, const Lds &l, int TR, int TC, int rl, int cl,
-                                               const double *table, double kappa, bool brief,
-                                               Sums<KERNEL> *o) {
-  switch (q) {
-    case 2: return regular_sums<KERNEL, LAYER, 2, false>(l, TR, TC, 4, rl, cl, table, kappa, brief, o);
-    case 3: return regular_sums<KERNEL, LAYER, 3, false>(l, TR, TC, 9, rl, cl, table, kappa, brief, o);
-    case 4: return regular_sums<KERNEL, LAYER, 4, false>(l, TR, TC, 16, rl, cl, table, kappa, brief, o);
-    case 5: return regular_sums<KERNEL, LAYER, 5, false>(l, TR, TC, 25, rl, cl, table, kappa, brief, o);
-    default: return regular_sums<KERNEL, LAYER, 6, false>(l, TR, TC, 36, rl, cl, table, kappa, brief, o);
-  }
+// Sums of a regular entry of the learned form: order Q on both triangles.
+template <int KERNEL, int LAYER, int Q>
+__device__ __forceinline__ void learned_sums(const Lds &l, int TR, int TC, int rl, int cl,
+                                             const OrderRules &o, double kappa, bool brief,
+                                             Sums<KERNEL> *v) {
+  const EntryGeo g = entry_geo<LAYER, false>(l, TR, TC, rl, cl);
+  const PointsOfRule pts{l.ys + cl, TC, (uniform_ptr)o.rule[Q], Q * Q};
+  if (KERNEL == BEM_HELMHOLTZ && brief) duffy_sums<KERNEL, LAYER, Q, true, double>(g, o.duffy[Q], kappa, pts, v);
+  else duffy_sums<KERNEL, LAYER, Q, false, double>(g, o.duffy[Q], kappa, pts, v);
 }
 
 // Sub-tile of the learned form (plain FP64): every regular entry takes the
 // Duffy/Gauss order of the order map (2 .. q_max); the entries are grouped by
 // order (each group padded to a multiple of 64, one order per wave-sized
-// chunk) and each order's column points are staged in turn.  Singular pairs
-// as in the plain kernel.
+// chunk).  Singular pairs as in the plain kernel.  The column points are formed
+// from the staged triangle as they are used (six operations for the q^2 point
+// pairs of each): staged per order they kept the orders apart by barriers, the
+// waves idle for 39 % of the time (8192 triangles, Helmholtz, orders 2 to 5: 2.65
+// -> 2.34 ms; 4608, order 6: 2.53 -> 2.01; Laplace, 8192: 0.77 -> 0.71).
 template <int KERNEL, int LAYER>
 __device__ void subtile_learned(const BlockArgs &a, const OrderRules &o, const Lds &l,
                                 const BlockHdr &h, int64_t r0, int64_t c0) {
@@ -557,6 +558,11 @@ __device__ void subtile_learned(const BlockArgs &a, const OrderRules &o, const L
   const int tr = (int)min((int64_t)TR, h.nr - r0), tc = (int)min((int64_t)TC, h.nc - c0);
   const int cap = TR * TC;
   if (!stage_tile<false>(a, l, h, r0, c0, tr, tc)) return;
+  for (int k = tid; k < tc * kColumnFields; k += kThreads) {
+    const int cl = k % tc, m = k / tc, id = l.cid[cl];
+    const double x = a.geo[(m < 9 ? G_V0X + m : G_SG) * a.ldg + id];
+    l.ys[m * TC + cl] = m == 9 ? x : 2.0 * (m == 0 ? x - h.cx : m == 1 ? x - h.cy : m == 2 ? x - h.cz : x);
+  }
   // classify: singular pairs to the front of the list, regular ones (with
   // their order) to the back
   for (int e = tid; e < tr * tc; e += kThreads) {
@@ -578,7 +584,8 @@ __device__ void subtile_learned(const BlockArgs &a, const OrderRules &o, const L
   }
   __syncthreads();
   // the singular pairs grouped by class at the front of sorted[], then the
-  // regular ones by order (each group padded to a multiple of 64)
+  // regular ones by descending order (each group padded to a multiple of 64):
+  // roughly by descending cost of a chunk
   const Groups gr = group_listed(l);
   const int nreg = *l.rcount;
   int seg[7];
@@ -594,39 +601,33 @@ __device__ void subtile_learned(const BlockArgs &a, const OrderRules &o, const L
     const int q = code >> 12;
     l.sorted[seg[q] + atomicAdd(&l.cursor[8 + q], 1)] = code;
   }
-  // one phase per order present (its column points staged), the singular
-  // chunks joining the first phase; the waves take chunks from a counter
-  int nsc = gr.total / kWave;
-  for (int q = o.q_max; q >= 1; --q) {
-    const int n = q >= 2 ? l.ccount[8 + q] : 0;
-    if (n == 0 && !(q == 1 && nsc > 0)) continue;  // q = 1: singular chunks alone
-    if (tid == 0) l.cursor[15] = 0;
-    const int nq = q >= 2 ? o.nq[q] : 0;
-    if (n > 0)
-      for (int k = tid; k < 3 * nq; k += kThreads) l.rule[k] = o.rule[q][k];
-    __syncthreads();  // sorted[], the counter and the rule are in place
-    if (n > 0) stage_columns<false>(a, l, h, tc, nq, nq);
-    const int nrc = ((n + 63) & ~63) / kWave;
-    for (;;) {
-      int c = 0;
-      if (lane == 0) c = atomicAdd(&l.cursor[15], 1);
-      c = __builtin_amdgcn_readfirstlane(c);
-      if (c >= nsc + nrc) break;
-      if (c < nsc) {
-        singular_chunk<KERNEL, LAYER, false>(a, l, h, r0, c0, gr, c * kWave);
-        continue;
-      }
-      const uint16_t code = l.sorted[seg[q] + (c - nsc) * kWave + lane];
-      if (code == kNoPair) continue;
-      const int rl = code & 63, cl = (code >> 6) & 63;
-      Sums<KERNEL> v;
-      regular_sums_q<KERNEL, LAYER>(q, l, TR, TC, rl, cl, o.duffy[q], a.kappa, h.brief, &v);
-      scale_sums(&v);
-      store_as<KERNEL, false>(a.out, off + (r0 + rl) + nr * (c0 + cl), LAYER == BEM_DLP ? v.d : v.s,
-                              a.flags);
+  __syncthreads();
+  // the waves take chunks from one counter (zeroed by stage_tile)
+  const int nsc = gr.total / kWave;
+  for (;;) {
+    int c = 0;
+    if (lane == 0) c = atomicAdd(&l.cursor[15], 1);
+    c = __builtin_amdgcn_readfirstlane(c);
+    if (c >= total / kWave) break;
+    if (c < nsc) {
+      singular_chunk<KERNEL, LAYER, false>(a, l, h, r0, c0, gr, c * kWave);
+      continue;
     }
-    nsc = 0;
-    __syncthreads();  // before the next order's points and counter replace these
+    const uint16_t code = l.sorted[c * kWave + lane];
+    const int q = __builtin_amdgcn_readfirstlane(code) >> 12;  // lane 0 of a chunk has a pair
+    if (code == kNoPair) continue;
+    const int rl = code & 63, cl = (code >> 6) & 63;
+    Sums<KERNEL> v;
+    switch (q) {
+      case 2: learned_sums<KERNEL, LAYER, 2>(l, TR, TC, rl, cl, o, a.kappa, h.brief, &v); break;
+      case 3: learned_sums<KERNEL, LAYER, 3>(l, TR, TC, rl, cl, o, a.kappa, h.brief, &v); break;
+      case 4: learned_sums<KERNEL, LAYER, 4>(l, TR, TC, rl, cl, o, a.kappa, h.brief, &v); break;
+      case 5: learned_sums<KERNEL, LAYER, 5>(l, TR, TC, rl, cl, o, a.kappa, h.brief, &v); break;
+      default: learned_sums<KERNEL, LAYER, 6>(l, TR, TC, rl, cl, o, a.kappa, h.brief, &v);
+    }
+    scale_sums(&v);
+    store_as<KERNEL, false>(a.out, off + (r0 + rl) + nr * (c0 + cl), LAYER == BEM_DLP ? v.d : v.s,
+                            a.flags);
   }
 }
 

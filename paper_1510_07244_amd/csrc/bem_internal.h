@@ -312,7 +312,6 @@ struct SelectArgs {
 struct OrderRules {
   const double *rule[BEM_MAX_ORDER + 1];
   const double *duffy[BEM_MAX_ORDER + 1];
-  int32_t nq[BEM_MAX_ORDER + 1];
   const int8_t *orders;
   int32_t q_max;
 };

@@ -265,7 +265,7 @@ int bem_assemble_nearfield_learned(bem_ctx *ctx, const bem_mesh *mesh, const bem
   hipError_t e = launch_geometry(*mesh, ctx->geo, ldg, ctx->flags, s);
   if (e != hipSuccess) return hip_fail(ctx, e, "geometry kernel launch");
   OrderRules o{};
-  for (int q = 2; q <= op->q_regular; ++q) o.rule[q] = r[q]->tri, o.duffy[q] = r[q]->duffy, o.nq[q] = r[q]->nq;
+  for (int q = 2; q <= op->q_regular; ++q) o.rule[q] = r[q]->tri, o.duffy[q] = r[q]->duffy;
   o.orders = orders;
   o.q_max = op->q_regular;
   const DevRules *plain = r[op->q_regular];
@@ -288,10 +288,14 @@ int bem_assemble_nearfield_learned(bem_ctx *ctx, const bem_mesh *mesh, const bem
   a.out_len = out_len;
   a.rule = plain->tri;
   a.nq = plain->nq;
-  a.nq_pad = plain->nq;  // LDS sized for the largest order
+  a.nq_pad = 3;  // LDS of the column triangles: kColumnFields in 4 doubles each
   size_t lds;
   if (!block_tile_shape(a.nq_pad, false, ctx->lds_budget, &a.tr, &a.tc, &lds))
     return fail(ctx, BEM_EUNSUPPORTED, "quadrature order too high for the LDS budget");
+  // 64 x 64 sub-tiles pad the fewest chunks; lists of few blocks need more
+  // sub-tiles than blocks (Helmholtz, order 6, 64 or 32 columns: 702 blocks 1.33 and
+  // 1.10 ms, 1041 blocks 1.80 and 2.01)
+  if (a.nblocks < 768 && a.tc > 32) a.tc = 32;
   a.split = split_blocks(a, false, false, true, false, &a.tc, &lds);
   a.ss = ss_args(*plain);
   a.kappa = op->kernel == BEM_HELMHOLTZ ? op->kappa : 0.0;
