@@ -151,15 +151,15 @@ def cmd_traffic(a):
     trace = read_trace(a.trace) if a.trace else {}
     js = bench_json(a.bench_log) if a.bench_log else None
     # the launches, identified by kernel and workgroups (k-th occurrence)
-    launches = [("SLP near field (2400 blocks)", "k_blocks<0, 0, 8, false>", 2400, 0,
+    launches = [("SLP near field (2400 blocks)", "k_blocks<0, 0, 4, false>", 2400, 0,
                  a.near_entries * 8, None),
-                ("DLP near field (2400 blocks)", "k_blocks<0, 1, 8, false>", 2400, 0,
+                ("DLP near field (2400 blocks)", "k_blocks<0, 1, 4, false>", 2400, 0,
                  a.near_entries * 8, "near_per_layer.roofline_dlp"),
-                ("DLP coupling (3760 blocks)", "k_blocks<0, 1, 8, false>", 3760, 0,
+                ("DLP coupling (3760 blocks)", "k_blocks<0, 1, 4, false>", 3760, 0,
                  a.coupling_entries * 8, "roofline"),
-                ("SLP+DLP near field, one pass (1292 blocks)", "k_blocks<0, 2, 8, false>", 1292, 0,
+                ("SLP+DLP near field, one pass (1292 blocks)", "k_blocks<0, 2, 4, false>", 1292, 0,
                  2 * a.near_entries * 8, "roofline_near_both"),
-                ("SLP coupling, mirrored (1880 blocks)", "k_blocks<0, 0, 8, false>", 1880, 0,
+                ("SLP coupling, mirrored (1880 blocks)", "k_blocks<0, 0, 4, false>", 1880, 0,
                  2 * a.slp_coupling_entries * 8, "roofline_slp_coupling"),
                 ("Helmholtz kappa 4 DLP coupling, q 5 (3760 blocks)", "k_blocks<1, 1, 5, false>",
                  3760, 0, a.helmholtz_dlp_entries * 16, None),

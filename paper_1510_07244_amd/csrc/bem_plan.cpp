@@ -479,7 +479,18 @@ int bem_plan_batched(bem_ctx *ctx, const bem_op *op, int32_t nbatch, const bem_b
       }
     }
   }
-  if (cands.empty())
+  // requested shapes are held to the room that 48 bytes per column point (32
+  // in the mixed form) leave, the limit configurations are written against;
+  // the sub-tiles themselves take less
+  bool over = false;
+  if (want.tile_cols && any_lists) {
+    const size_t tr = want.tile_rows ? want.tile_rows : want.autotune ? 32 : 64, tc = want.tile_cols;
+    const size_t np = (p->nq + xc - 1) / xc * xc;
+    const size_t dbl = (p->mixed ? 4 : 6) * np * tc + 10 * tr + 3 * np + 3 * tc + (any_both ? 3 * tr : 0) +
+                       (p->mixed ? 6 * tr + 9 * tc : 0);
+    over = dbl * 8 + (4 * tr + 4 * tc + 36) * 4 + 2 * (2 * tr * tc + 512) > ctx->lds_budget;
+  }
+  if (cands.empty() || over)
     return bail(fail(ctx, BEM_EUNSUPPORTED, "no sub-tile shape fits the LDS budget"));
 
   // ---- per-candidate device state

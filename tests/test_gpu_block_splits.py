@@ -75,3 +75,29 @@ def test_lists_around_the_limits(nblocks, coupling):
     scale = np.abs(a).max()
     assert np.abs(a - b.T).max() <= 1e-13 * scale
     assert (got[0::2] == got[0]).all() and (got[1::2] == got[1]).all()
+
+
+@pytest.mark.parametrize("cols,fits", [(48, True), (56, False)])
+def test_requested_shapes_keep_their_limit(cols, fits):
+    """Order 5, 64 rows: 79.7 KB at 48 bytes per column point with 48 columns,
+    91.7 KB with 56, of 80 KiB."""
+    import torch
+    import paper_1510_07244_amd as pk
+    m = octahedron_sphere(4)
+    mesh = pk.Mesh(torch.from_numpy(m.v), torch.from_numpy(m.tri))
+    op = pk.make_op(0, 0, q_regular=5)
+    idx = np.arange(100, dtype=np.int32)
+    blocks, total = pk.Blocks.from_lists([idx], [idx])
+    out = torch.full((total,), float("nan"), dtype=torch.float64, device="cuda")
+    ctx = pk.Context(0)
+    make = lambda: pk.Plan(ctx, op, [(mesh, blocks, out, False)], tune=dict(tile_rows=64, tile_cols=cols))
+    if fits:
+        plan = make()
+        plan.run()
+        ctx.check()
+        plan.close()
+        assert torch.isfinite(out).all()
+    else:
+        with pytest.raises(Exception, match="LDS budget"):
+            make()
+    ctx.close()

@@ -2,7 +2,7 @@
 order with a kernel of its own and the general sums (order 1, orders from 7,
 seven points per triangle), and for Helmholtz triangles on both sides of the
 limit of the short phases (kappa times the distance of a triangle's points
-from its centroid at most 1/2) within one block, kappa of either sign, zero
+from its centroid at most 3/4) within one block, kappa of either sign, zero
 and too small for scaled coordinates.
 
 Plain FP64 within 1e-12 of the block's largest entry (sums of at most 144^2
