@@ -194,13 +194,63 @@ struct RowSum {
   double sr[3], si[3], dr[3], di[3];
 };
 
+// Orthonormal axes of a triangle's plane: e1 = l u and e2 = a u + b w up to
+// rounding of their own size, n = u x w.  The second axis is orthogonalised
+// twice and the third taken from the first two, so that both edges have no
+// component along n beyond that rounding however flat the triangle is.
+struct TriFrame {
+  double u[3], w[3], n[3], l, a, b;
+};
+__device__ __forceinline__ double dot3(const double *a, const double *b) {
+  return fma(a[0], b[0], fma(a[1], b[1], a[2] * b[2]));
+}
+__device__ __forceinline__ TriFrame tri_frame(const double *e1, const double *e2) {
+  TriFrame f;
+  const double l2 = dot3(e1, e1), il = rsqrt_newton(l2);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) f.u[c] = e1[c] * il, f.w[c] = e2[c];
+#pragma unroll
+  for (int pass = 0; pass < 2; ++pass) {
+    const double k = dot3(f.w, f.u);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) f.w[c] = fma(-k, f.u[c], f.w[c]);
+  }
+  double b2 = dot3(f.w, f.w);
+  if (b2 == 0.0) {  // flat to the last bit (its area is rounding): the axis that u has least of
+    const double x = fabs(f.u[0]), y = fabs(f.u[1]), z = fabs(f.u[2]);
+    const int k = x <= y && x <= z ? 0 : y <= z ? 1 : 2;
+    const double uk = k == 0 ? f.u[0] : k == 1 ? f.u[1] : f.u[2];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) f.w[c] = fma(-uk, f.u[c], c == k ? 1.0 : 0.0);
+    b2 = dot3(f.w, f.w);
+  }
+  const double ib = rsqrt_newton(b2);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) f.w[c] *= ib;
+  f.n[0] = fma(f.u[1], f.w[2], -f.u[2] * f.w[1]);
+  f.n[1] = fma(f.u[2], f.w[0], -f.u[0] * f.w[2]);
+  f.n[2] = fma(f.u[0], f.w[1], -f.u[1] * f.w[0]);
+  f.l = dot3(e1, f.u);
+  f.a = dot3(e2, f.u);
+  f.b = dot3(e2, f.w);
+  return f;
+}
+
 // One regular (disjoint) pair (i, j) in FP64 with its rule points formed from
 // the geometry arrays, XC x-points at a time: the chunks sub, sub + G, ... of
-// the rule's nq points (G lanes share a pair; each returns its part).  On the
-// column triangle the squared distance from an x-point is a quadratic
-// polynomial: |X|^2 - 2 u <X, e1> - 2 v <X, e2> + |u e1 + v e2|^2 with X = x -
-// v0_j, three operations per point pair beyond the term all x-points share;
-// <x - y, n_j> is one value per x-point.  The rule is read by scalar loads.
+// the rule's nq points (G lanes share a pair; each returns its part).
+// Distances are sums of squared coordinate differences in axes of the column
+// triangle's plane: an x-point's height above it is squared once, so a point
+// pair takes two differences and two multiply-adds, and the height is
+// <x - y, n_j> too.  Nothing cancels beyond the difference of the points
+// itself (1/r to eps h / r at triangle size h): these are also the pairs that
+// the mixed form leaves to FP64 because they are close.  A quadratic
+// polynomial of the column's rule coordinates takes one operation less and loses
+// eps (h / r)^2 (facing sheets 1e-4 h apart: 1e-8 where this and the plain
+// difference lose 1e-13; NaN from 1e-8 h on) at the same speed: 1000 entries 10.4
+// and 10.3 us, 300000 81.6 and 80.1, 440000 piecewise-linear pairs 120 and 124,
+// mixed matrix step of 8192 triangles 2.01 ms both.  The rule is read by scalar
+// loads.
 // row(k, w, sums) is called for every x-point k with its weight (zero and a
 // repeated point past the last one); with MIRROR *mr, *mi receive the double
 // layer of (j, i), which needs the row's weights inside.
@@ -211,7 +261,7 @@ __device__ __forceinline__ void regular_rows(const double *g, int64_t L, const d
   constexpr int NB = P1 ? 3 : 1;
   constexpr bool S = LAYER != BEM_DLP, D = LAYER != BEM_SLP;
   const uniform_ptr R = (uniform_ptr)rule;
-  double X0[3], e1i[3], e2i[3], e1j[3], e2j[3], n[3] = {0, 0, 0}, ni[3] = {0, 0, 0};
+  double X0[3], e1i[3], e2i[3], e1j[3], e2j[3];
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     X0[c] = g[(G_V0X + c) * L + i] - g[(G_V0X + c) * L + j];
@@ -219,15 +269,20 @@ __device__ __forceinline__ void regular_rows(const double *g, int64_t L, const d
     e2i[c] = g[(G_E2X + c) * L + i];
     e1j[c] = g[(G_E1X + c) * L + j];
     e2j[c] = g[(G_E2X + c) * L + j];
-    if (D) n[c] = g[(G_NX + c) * L + j];
-    if (MIRROR) ni[c] = g[(G_NX + c) * L + i];
   }
-  auto dot = [](const double *a, const double *b) { return fma(a[0], b[0], fma(a[1], b[1], a[2] * b[2])); };
-  const double a11 = dot(e1j, e1j), a12 = 2.0 * dot(e1j, e2j), a22 = dot(e2j, e2j);
+  const TriFrame f = tri_frame(e1j, e2j);
+  // x - v0_j in the axes, linear in the row's rule coordinates
+  const double p0 = dot3(X0, f.u), p1 = dot3(e1i, f.u), p2 = dot3(e2i, f.u);
+  const double q0 = dot3(X0, f.w), q1 = dot3(e1i, f.w), q2 = dot3(e2i, f.w);
+  const double h0 = dot3(X0, f.n), h1 = dot3(e1i, f.n), h2 = dot3(e2i, f.n);
   // <y - x, n_i> = m1 u + m2 v - m0
-  const double m0 = dot(X0, ni), m1 = dot(e1j, ni), m2 = dot(e2j, ni);
+  double m0 = 0.0, m1 = 0.0, m2 = 0.0;
+  if constexpr (MIRROR) {
+    const TriFrame r = tri_frame(e1i, e2i);
+    m0 = dot3(X0, r.n), m1 = dot3(e1j, r.n), m2 = dot3(e2j, r.n);
+  }
   for (int a0 = sub * XC; a0 < nq; a0 += G * XC) {
-    double c[XC], p[XC], q[XC], dn[XC], w[XC];
+    double p[XC], q[XC], h[XC], w[XC];
     RowSum acc[XC];
 #pragma unroll
     for (int a = 0; a < XC; ++a) {
@@ -235,39 +290,38 @@ __device__ __forceinline__ void regular_rows(const double *g, int64_t L, const d
       // lanes of a pair take different x-points: per-lane loads
       const double s = rule[k], t = rule[nq + k];
       w[a] = a0 + a < nq ? rule[2 * nq + k] : 0.0;
-      double X[3];
-#pragma unroll
-      for (int d = 0; d < 3; ++d) X[d] = fma(s, e1i[d], fma(t, e2i[d], X0[d]));
-      c[a] = dot(X, X);
-      p[a] = -2.0 * dot(X, e1j);
-      q[a] = -2.0 * dot(X, e2j);
-      dn[a] = dot(X, n);
+      p[a] = fma(s, p1, fma(t, p2, p0));
+      q[a] = fma(s, q1, fma(t, q2, q0));
+      h[a] = fma(s, h1, fma(t, h2, h0));
 #pragma unroll
       for (int b = 0; b < NB; ++b) acc[a].sr[b] = acc[a].si[b] = acc[a].dr[b] = acc[a].di[b] = 0.0;
     }
     constexpr int U = XC == 1 ? 4 : 1;  // column points per step
     auto step = [&](int b0, int nu) {
-      double u[U], v[U], wb[U], r2[U][XC], h[U][XC];
+      double u[U], v[U], wb[U], r2[U][XC], y[U][XC];
 #pragma unroll
       for (int k = 0; k < U; ++k) {
         const int b = U == 1 ? b0 : min(b0 + k, nq - 1);
         u[k] = R[b];
         v[k] = R[nq + b];
         wb[k] = k < nu ? R[2 * nq + b] : 0.0;
-        const double gb = fma(u[k], fma(u[k], a11, v[k] * a12), v[k] * v[k] * a22);
+        const double yp = fma(u[k], f.l, v[k] * f.a), yq = v[k] * f.b;
 #pragma unroll
-        for (int a = 0; a < XC; ++a) r2[k][a] = fma(v[k], q[a], fma(u[k], p[a], c[a] + gb));
+        for (int a = 0; a < XC; ++a) {
+          const double dp = p[a] - yp, dq = q[a] - yq;
+          r2[k][a] = fma(dp, dp, fma(dq, dq, h[a] * h[a]));
+        }
       }
 #pragma unroll
       for (int k = 0; k < U; ++k)
 #pragma unroll
-        for (int a = 0; a < XC; ++a) h[k][a] = __builtin_amdgcn_rsq(r2[k][a]);
+        for (int a = 0; a < XC; ++a) y[k][a] = __builtin_amdgcn_rsq(r2[k][a]);
 #pragma unroll
       for (int k = 0; k < U; ++k) {
         double tr = 0.0, ti = 0.0;
 #pragma unroll
         for (int a = 0; a < XC; ++a) {
-          const double z = fma(0.5 * h[k][a], fma(-(r2[k][a] * h[k][a]), h[k][a], 1.0), h[k][a]);
+          const double z = fma(0.5 * y[k][a], fma(-(r2[k][a] * y[k][a]), y[k][a], 1.0), y[k][a]);
           double z3 = 0.0, cs = 1.0, sn = 0.0, fr = 1.0, fi = 0.0;
           if (D) z3 = z * z * z;
           if constexpr (KERNEL == BEM_HELMHOLTZ) {
@@ -314,7 +368,7 @@ __device__ __forceinline__ void regular_rows(const double *g, int64_t L, const d
 #pragma unroll
     for (int a = 0; a < XC; ++a) {
 #pragma unroll
-      for (int b = 0; b < NB; ++b) acc[a].dr[b] *= dn[a], acc[a].di[b] *= dn[a];
+      for (int b = 0; b < NB; ++b) acc[a].dr[b] *= h[a], acc[a].di[b] *= h[a];
       row(min(a0 + a, nq - 1), w[a], acc[a]);
     }
   }
