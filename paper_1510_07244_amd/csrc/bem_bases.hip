@@ -20,21 +20,22 @@ using namespace dev;
 //   side 1:  sqrt(w) int d/dn(x) g(x, z) dx, sqrt(w) delta int d/dn(x) d/dn(z) g(x, z) dx
 // (side 1 is the column basis of the double layer).  Triangle integrals use
 // the Duffy rule: int_tau f = sqrt(g) sum_k w_k f(Phi(s_k, t_k)).
-// A thread takes one row triangle and kGreenPerThread Green points.  With X =
-// v0 - z the squared distance at the rule point (s, t) is
-//   |X|^2 + 2 s <X, e1> + 2 t <X, e2> + |s e1 + t e2|^2,
-// whose last term all Green points share, <x - z, n_z> is linear in s and t
-// and <x - z, n_x> the constant <X, n_x>: 14 (side 0) and 15 (side 1) FP64
-// operations and a reciprocal root per evaluation for Laplace.  The rule comes
-// by scalar loads.  Workgroups of one wave: their number comes from the
-// largest cluster, and those past a smaller cluster's rows end at once without
-// three other waves' places.  Bound by these operations (about 65 % of the
-// time busy; the rest is each wave's chain of index, geometry and point loads
-// and the last round).  340 clusters of 23 to 230 rows (27363 in all), 96
-// Green points, 16 rule points, side 0 / 1: 62 / 75 us with differences taken
-// per evaluation, 54 / 53 with four waves per workgroup, 48 / 51 with one;
-// two Green points per thread 49 / 54, workgroups numbered by the mean
-// cluster 52 / 55.
+// A thread takes one row triangle and kGreenPerThread Green points.  Distances
+// are taken in axes of the triangle's plane: a Green point's height above it,
+// which is <x - z, n_x> too, is squared once, the rule points' coordinates are
+// shared by all Green points, and an evaluation takes two differences and two
+// multiply-adds (the quadratic polynomial of s and t takes three operations but
+// cancels near a triangle: 1e-8 at 1e-4 of its size); <x - z, n_z> is linear in s and t.  15 (side 0) and 16
+// (side 1) FP64 operations and a reciprocal root per evaluation for Laplace.
+// The rule comes by scalar loads.  Workgroups of one wave: their number comes
+// from the largest cluster, and those past a smaller cluster's rows end at once
+// without three other waves' places.  Bound by these operations (the rest is
+// each wave's chain of index, geometry and point loads and the last round).
+// 340 clusters of 23 to 230 rows (27363 in all), 96 Green points, 16 rule
+// points, side 0 / 1: 62 / 75 us with differences of three coordinates taken
+// per evaluation and 256 threads, 53 / 55 now (48 / 51 with the polynomial; that
+// one with four waves per workgroup 54 / 53, two Green points per thread 49 /
+// 54, workgroups numbered by the mean cluster 52 / 55).
 constexpr int kGreenPerThread = 4;
 constexpr int kGreenThreads = kWave;
 
@@ -56,7 +57,6 @@ __global__ __launch_bounds__(kGreenThreads) void k_green(const GreenArgs a) {
   const int64_t L = a.ldg;
   const uniform_ptr R = (uniform_ptr)a.rule;
   const int64_t items = n * mg;
-  auto dot = [](const double *x, const double *y) { return fma(x[0], y[0], fma(x[1], y[1], x[2] * y[2])); };
   // the work items (row, group of J Green points) of one cluster are spread
   // over gridDim.y workgroups; consecutive threads take consecutive rows
   for (int64_t e = (int64_t)blockIdx.y * kGreenThreads + threadIdx.x; e < items;
@@ -78,8 +78,8 @@ __global__ __launch_bounds__(kGreenThreads) void k_green(const GreenArgs a) {
       if (SIDE == 1) nx[d] = a.geo[(G_NX + d) * L + id];
     }
     const double sg = a.geo[G_SG * L + id];
-    const double g11 = dot(e1, e1), g12 = 2.0 * dot(e1, e2), g22 = dot(e2, e2);
-    double c0[J], c1[J], c2[J], d0[J], d1[J], d2[J], dnx[J], nn[J], wz[J];
+    const TriFrame f = tri_frame(e1, e2);
+    double p0[J], q0[J], h[J], d0[J], d1[J], d2[J], nn[J], wz[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) {
       const int nu = min(nu0 + j, m - 1);  // past m: a copy, not written
@@ -88,9 +88,9 @@ __global__ __launch_bounds__(kGreenThreads) void k_green(const GreenArgs a) {
       wz[j] = a.zw[(int64_t)c * m + nu];
       const double X[3] = {v0[0] - zp[0], v0[1] - zp[1], v0[2] - zp[2]};
       const double N[3] = {np[0], np[1], np[2]};
-      c0[j] = dot(X, X), c1[j] = 2.0 * dot(X, e1), c2[j] = 2.0 * dot(X, e2);
-      d0[j] = dot(X, N), d1[j] = dot(e1, N), d2[j] = dot(e2, N);  // <x - z, n_z>
-      if (SIDE == 1) dnx[j] = dot(X, nx), nn[j] = dot(nx, N);
+      p0[j] = dot3(X, f.u), q0[j] = dot3(X, f.w), h[j] = dot3(X, f.n);  // h: <x - z, n_x>
+      d0[j] = dot3(X, N), d1[j] = dot3(e1, N), d2[j] = dot3(e2, N);     // <x - z, n_z>
+      if (SIDE == 1) nn[j] = dot3(nx, N);
     }
     // side 0: the two columns' sums; side 1: p is the sum of the first
     // column without -<x - z, n_x>, q that of <x - z, n_z> times the second
@@ -100,10 +100,11 @@ __global__ __launch_bounds__(kGreenThreads) void k_green(const GreenArgs a) {
     for (int j = 0; j < J; ++j) pr[j] = pi[j] = qr[j] = qi[j] = 0.0;
     for (int k = 0; k < a.nq; ++k) {
       const double s = R[k], t = R[a.nq + k], w = R[2 * a.nq + k];
-      const double gk = fma(s, fma(s, g11, t * g12), t * t * g22);
+      const double xp = fma(s, f.l, t * f.a), xq = t * f.b;
 #pragma unroll
       for (int j = 0; j < J; ++j) {
-        const double r2 = fma(t, c2[j], fma(s, c1[j], c0[j] + gk));
+        const double dp = p0[j] + xp, dq = q0[j] + xq;
+        const double r2 = fma(dp, dp, fma(dq, dq, h[j] * h[j]));
         const double dn = fma(t, d2[j], fma(s, d1[j], d0[j]));
         const double iz = rsqrt_newton(r2);  // 1 / r
         const double wi = w * iz, i2 = iz * iz, wi3 = wi * i2;
@@ -140,11 +141,11 @@ __global__ __launch_bounds__(kGreenThreads) void k_green(const GreenArgs a) {
       const double sp = sqrt(wz[j]) * sg * kInv4Pi, sm = sp * delta;
       const int64_t ip = off + r + n * nu, im = off + r + n * (m + nu);
       if constexpr (SIDE == 1) {
-        const double f = (KERNEL == BEM_LAPLACE ? -3.0 : 1.0) * dnx[j];
-        qr[j] = fma(nn[j], pr[j], f * qr[j]);
-        qi[j] = fma(nn[j], pi[j], f * qi[j]);
-        pr[j] *= -dnx[j];
-        pi[j] *= -dnx[j];
+        const double x = (KERNEL == BEM_LAPLACE ? -3.0 : 1.0) * h[j];
+        qr[j] = fma(nn[j], pr[j], x * qr[j]);
+        qi[j] = fma(nn[j], pi[j], x * qi[j]);
+        pr[j] *= -h[j];
+        pi[j] *= -h[j];
       }
       if constexpr (KERNEL == BEM_LAPLACE) {
         static_cast<double *>(a.out)[ip] = pr[j] * sp;

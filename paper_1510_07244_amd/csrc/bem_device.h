@@ -205,8 +205,13 @@ __device__ __forceinline__ double dot3(const double *a, const double *b) {
   return fma(a[0], b[0], fma(a[1], b[1], a[2] * b[2]));
 }
 __device__ __forceinline__ TriFrame tri_frame(const double *e1, const double *e2) {
+  // two Newton steps: an error of the axes' length is one of every distance
+  auto inv_sqrt = [](double x) {
+    const double y = rsqrt_newton(x), e = fma(-(x * y), y, 1.0);
+    return fma(0.5 * y, e, y);
+  };
   TriFrame f;
-  const double l2 = dot3(e1, e1), il = rsqrt_newton(l2);
+  const double il = inv_sqrt(dot3(e1, e1));
 #pragma unroll
   for (int c = 0; c < 3; ++c) f.u[c] = e1[c] * il, f.w[c] = e2[c];
 #pragma unroll
@@ -224,7 +229,7 @@ __device__ __forceinline__ TriFrame tri_frame(const double *e1, const double *e2
     for (int c = 0; c < 3; ++c) f.w[c] = fma(-uk, f.u[c], c == k ? 1.0 : 0.0);
     b2 = dot3(f.w, f.w);
   }
-  const double ib = rsqrt_newton(b2);
+  const double ib = inv_sqrt(b2);
 #pragma unroll
   for (int c = 0; c < 3; ++c) f.w[c] *= ib;
   f.n[0] = fma(f.u[1], f.w[2], -f.u[2] * f.w[1]);
