@@ -12,7 +12,6 @@ namespace blk {
 
 using namespace dev;
 
-constexpr double kPad = 1.0e4;       // coordinate of column padding points (weight 0)
 constexpr uint16_t kNoPair = 0xffff; // empty slot of the sorted singular list
 constexpr uint16_t kSwapped = 0x4000; // listed code: the mirror block's entry (j, i)
 constexpr int kNearSingular = 0;     // list class of near-singular regular pairs (mixed)
@@ -34,10 +33,13 @@ enum RowField {
 };
 
 // LDS layout of one sub-tile (up to TR rows x TC columns; triangle rule of nq
-// points, padded to nqp with zero weights by the general rules):
+// points, room for nqp: rule_pad):
 //   ys[nqp][TC]    column points (Y, w sqrt(g_j)): four doubles, Y = 2 (y - c);
 //                  mixed: four floats, Y = 2 (y - v0_j) local to the triangle.
-//                  Read as 16-byte words (broadcast in a wave).
+//                  Read as 16-byte words (broadcast in a wave).  The general sums
+//                  and the learned form keep the column triangles instead,
+//                  [kColumnFields][TC] doubles, the general sums then 4 |y_b -
+//                  v0_j|^2 of the points, [nq][TC] doubles (mixed: floats)
 //   rg[ROW_NF][TR] row geometry
 //   rule[3][nqp]   s, t, w of the triangle rule
 //   cn[4][TC]      column normals n_j, <Y, n_j> (one value on the triangle's
@@ -183,6 +185,25 @@ struct PointsOfRule {
   static __device__ __forceinline__ void unpack(const P &q, double *y, double *w) { y[0] = q.y[0], y[1] = q.y[1], y[2] = q.y[2], *w = q.w; }
 };
 
+// The rule's constants in the precision of the sums, wave-uniform.
+template <class T>
+struct TablePtr {
+  typedef const T __attribute__((address_space(4))) *type;
+  static __device__ __forceinline__ type of(const double *t) { return (type)t; }
+};
+
+// Points of a column triangle for the general sums: the rule's coordinates
+// and weight (general_table, scalar loads) and 4 |y - v0|^2 from LDS.
+template <class T>
+struct PointsOfTriangle {
+  const T *g;
+  int stride;
+  typename TablePtr<T>::type t;
+  int n;
+  struct P { T g, u, v, w; };
+  __device__ __forceinline__ P get(int b) const { return {g[b * stride], t[b], t[n + b], t[2 * n + b]}; }
+};
+
 // Two points per step, the next one's LDS reads issued before the current
 // one's arithmetic (no register copies between steps).
 // ONE: one point per step with the copies (a third copy of a long body, for
@@ -229,14 +250,14 @@ struct PointSums {
 template <int KERNEL, int LAYER, bool SHORT, class T>
 struct PairValue {
   typedef Arith<T> M;
-  T kr_, ki_, fr, fi, z3;
+  T kr_, ki_, fr, fi, z3, z, sn, cs;
   __device__ __forceinline__ void eval(T s, T h, T kq, T kr0) {
     if constexpr (KERNEL == BEM_LAPLACE) {
-      const T z = M::inv(h, M::newton(s, h));
+      z = M::inv(h, M::newton(s, h));
       kr_ = z;
       if constexpr (LAYER != BEM_SLP) z3 = z * z * z;
     } else {
-      T z, kr = 0, sn, cs;
+      T kr = 0;
       if constexpr (SHORT) {
         T t, u;  // kappa r = t u
         if constexpr (std::is_same<T, double>::value) {
@@ -270,6 +291,34 @@ struct PairValue {
   __device__ __forceinline__ T dr() const { return KERNEL == BEM_LAPLACE ? z3 : z3 * fr; }
   __device__ __forceinline__ T di() const { return z3 * fi; }
 };
+
+// Adds the value of one x-point at squared distance sq (estimate h of its
+// reciprocal root) with weight w, w <X - Y, n_j> = wn.
+template <int KERNEL, int LAYER, class T>
+__device__ __forceinline__ void add_value(T sq, T h, T kq, T w, T wn, PointSums<KERNEL, LAYER, T> *ps) {
+  typedef Arith<T> M;
+  PairValue<KERNEL, LAYER, false, T> v;
+  v.eval(sq, h, kq, (T)0);
+  if constexpr (KERNEL == BEM_LAPLACE) {
+    if constexpr (LAYER != BEM_DLP) ps->sr = M::mad(w, v.z, ps->sr);
+    if constexpr (LAYER == kBoth) ps->t1r = M::mad(w, v.z3, ps->t1r);
+    if constexpr (LAYER != BEM_SLP) ps->t2r = M::mad(wn, v.z3, ps->t2r);
+  } else {
+    // the weight goes to the factor that real and imaginary part share
+    if constexpr (LAYER != BEM_DLP) {
+      const T wz = w * v.z;
+      ps->sr = M::mad(wz, v.cs, ps->sr), ps->si = M::mad(wz, v.sn, ps->si);
+    }
+    if constexpr (LAYER == BEM_DLP) {
+      const T wz = wn * v.z3;
+      ps->t2r = M::mad(wz, v.fr, ps->t2r), ps->t2i = M::mad(wz, v.fi, ps->t2i);
+    } else if constexpr (LAYER == kBoth) {
+      const T re = v.dr(), im = v.di();
+      ps->t1r = M::mad(w, re, ps->t1r), ps->t1i = M::mad(w, im, ps->t1i);
+      ps->t2r = M::mad(wn, re, ps->t2r), ps->t2i = M::mad(wn, im, ps->t2i);
+    }
+  }
+}
 
 // Adds one column point's sums, weighted: wy (entry), wm (transposed double
 // layer), both rotated by e^{i kr0} = (cy, sy) when SHORT.
@@ -321,19 +370,6 @@ struct EntrySums {
   }
 };
 
-template <class T>
-struct DuffyPtr;
-template <>
-struct DuffyPtr<double> {
-  typedef uniform_ptr type;
-  static __device__ __forceinline__ type of(const double *t) { return (type)t; }
-};
-template <>
-struct DuffyPtr<float> {
-  typedef const float __attribute__((address_space(4))) *type;
-  static __device__ __forceinline__ type of(const double *t);
-};
-
 // Offsets in the table of a Duffy rule of order Q (duffy_table): per xi
 // (xi, xi^2, w_xi xi, w_xi xi^2); the half-width nodes delta > 0 of eta =
 // 1/2 +- delta, their squares, the eta weights w (pairs, then the centre of an
@@ -345,7 +381,6 @@ struct DuffyAt {
   static constexpr int J = 0, D = 4 * Q, D2 = D + H, W = D2 + H, WD = W + HC, XD = WD + H,
                        WF = XD + Q * H;
 };
-inline __device__ DuffyPtr<float>::type DuffyPtr<float>::of(const double *t) { return (type)t; }
 
 // Sums over the point pairs of one regular entry, Duffy rule of order Q on
 // both triangles.  Bound by FP64 (FP32) issue, so the point pair is cut to
@@ -390,7 +425,7 @@ __device__ __forceinline__ void duffy_sums(const EntryGeo &g, const double *tabl
   constexpr bool ROLL = HELM && (FP64 ? LAYER == BEM_SLP && Q >= 5 : LAYER != BEM_DLP || Q >= 5);
   constexpr bool LIN = ROLL && LAYER == kBoth;    // double-layer weights in three sums
   constexpr bool FLY = ROLL && LAYER == BEM_DLP;  // formed at every point pair
-  const typename DuffyPtr<T>::type c = DuffyPtr<T>::of(table);
+  const typename TablePtr<T>::type c = TablePtr<T>::of(table);
   // short phases: coordinates scaled by f so that kappa r needs no factor
   const double ka = fabs(kappa), f = HELM && SHORT ? ka * M::kScale : 1.0;
   const T V0 = (T)(f * g.V[0]), V1 = (T)(f * g.V[1]), V2 = (T)(f * g.V[2]);
@@ -588,76 +623,145 @@ __device__ __forceinline__ void duffy_sums(const EntryGeo &g, const double *tabl
   sum.finish(g.sg, HELM && SHORT ? ka * M::kInvK : M::kInv, c0, s0, kappa < 0.0, out);
 }
 
-// The same for any triangle rule (rule[3][nqp]: s, t, w, padded to a multiple
-// of XC with zero weights): x-points in register chunks of XC, three
-// operations per squared distance.
-template <int KERNEL, int LAYER, int XC, class T, class PTS>
-__device__ __forceinline__ void general_sums(const EntryGeo &g, const double *rule, int nqp,
-                                             double kappa, const PTS &pts, Sums<KERNEL> *out) {
+// The same for any triangle rule (general_table, in T and in FP64), x-points in register chunks
+// of XC (zero weights and the last point repeated past the end).  With X0 = 2
+// (v0_i - v0_j), x = v0_i + (s/2) A + (e/2) B and E = 2 e_j the squared distance
+// is a polynomial of the rule coordinates of both triangles,
+//   4 |x - y|^2 = |X0|^2 + s <X0, A> + e <X0, B> + s^2 k0 + s e c1 + e^2 a22
+//     - u <2 X0 + s A + e B, E1> - v <2 X0 + s A + e B, E2> + |u E1 + v E2|^2:
+// nine coefficients of the pair, nine operations per x-point for its three
+// in (1, u, v), one number per column point from LDS, three operations per point
+// pair.  (Quadratic in the row's coordinates alone, each column point took twelve
+// per chunk.)
+// The chunks' sums are added in FP64: in the mixed form the FP32 sums are no
+// longer than the rule, whatever the chunk.
+// Against four operations per pair on coordinates of every x-point in chunks of
+// 8, 9, 7, 5 or 4 (Laplace, double layer, coupling; 3200 triangles orders 7 and 8,
+// 2048 above): 5.77 -> 5.53 ms, 9.61 -> 9.12, order 9 10.0 -> 7.5, order 12 33.6 ->
+// 23.3; the matrix step of 1152 triangles, order 8 / 9 / 12: 6.3 / 9.7 / 31.1 ->
+// 6.0 / 9.3 / 30.2.
+template <int KERNEL, int LAYER, int XC, class T>
+__device__ __forceinline__ void general_sums(const EntryGeo &g, const double *col, const T *gb, int TC,
+                                             const double *table, const double *table64, int nq,
+                                             double kappa, Sums<KERNEL> *out) {
   typedef Arith<T> M;
+  const typename TablePtr<T>::type c = TablePtr<T>::of(table);
+  const uniform_ptr d = (uniform_ptr)table64;
+  auto dot = [](const T *a, const T *b) { return M::mad(a[0], b[0], M::mad(a[1], b[1], a[2] * b[2])); };
+  T X[3], A[3], B[3], E1[3], E2[3];
+  double c0 = 0, n0 = 0, ns = 0, nt = 0, m0 = 0, m1 = 0, m2 = 0;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    // relative to the column triangle's first vertex (mixed: already)
+    const double x = std::is_same<T, double>::value ? g.V[k] - col[k * TC] : g.V[k];
+    const double f1 = col[(3 + k) * TC], f2 = col[(6 + k) * TC];
+    X[k] = (T)x, A[k] = (T)g.A[k], B[k] = (T)g.B[k], E1[k] = (T)f1, E2[k] = (T)f2;
+    c0 = fma(x, x, c0);  // its rounding is in every point pair: in FP64
+    if constexpr (LAYER != BEM_SLP)
+      n0 = fma(x, g.n[k], n0), ns = fma(fma(-0.25, g.B[k], 0.5 * g.A[k]), g.n[k], ns), nt = fma(0.5 * g.B[k], g.n[k], nt);
+    if constexpr (LAYER == kBoth) m0 = fma(-x, g.m[k], m0), m1 = fma(f1, g.m[k], m1), m2 = fma(f2, g.m[k], m2);
+  }
+  const T C0 = (T)c0, K0 = (T)g.k0, C1 = (T)g.c1, A22 = (T)g.a22;
+  const T ra = dot(X, A), rb = dot(X, B);
+  const T p0 = (T)-2 * dot(X, E1), pa = -dot(A, E1), pb = -dot(B, E1);
+  const T q0 = (T)-2 * dot(X, E2), qa = -dot(A, E2), qb = -dot(B, E2);
+  const T M0 = (T)m0, M1 = (T)m1, M2 = (T)m2;  // 2 <y - x, n_i> = m0 + u m1 + v m2
+  const T kq = (T)(M::kPhase * kappa);
+  const PointsOfTriangle<T> pts{gb, TC, c, nq};
+  EntrySums<KERNEL, LAYER, false, double> total;
+  for (int ch = 0; ch < nq; ch += XC) {
+    EntrySums<KERNEL, LAYER, false, T> sum;
+    T r[XC], p[XC], q[XC], W[XC], WN[XC];
+#pragma unroll
+    for (int a = 0; a < XC; ++a) {
+      const int k = min(ch + a, nq - 1);
+      const T s = c[k], e = c[3 * nq + k];
+      r[a] = M::mad(c[4 * nq + k], K0, M::mad(c[5 * nq + k], C1, M::mad(c[6 * nq + k], A22, M::mad(s, ra, M::mad(e, rb, C0)))));
+      p[a] = M::mad(s, pa, M::mad(e, pb, p0));
+      q[a] = M::mad(s, qa, M::mad(e, qb, q0));
+      W[a] = ch + a < nq ? c[2 * nq + k] : (T)0;
+      if constexpr (LAYER != BEM_SLP)
+        WN[a] = ch + a < nq ? (T)(d[2 * nq + k] * fma(d[k], ns, fma(d[nq + k], nt, n0))) : (T)0;
+    }
+    for_points<KERNEL == BEM_HELMHOLTZ>(pts, nq, [&](const typename PointsOfTriangle<T>::P &y) {
+      T sq[XC], h[XC];
+#pragma unroll
+      for (int a = 0; a < XC; ++a) sq[a] = M::mad(y.v, q[a], M::mad(y.u, p[a], r[a] + y.g));
+#pragma unroll
+      for (int a = 0; a < XC; ++a) h[a] = M::rsq(sq[a]);
+      PointSums<KERNEL, LAYER, T> ps;
+#pragma unroll
+      for (int a = 0; a < XC; ++a) add_value(sq[a], h[a], kq, W[a], WN[a], &ps);
+      T wm = 0;
+      if constexpr (LAYER == kBoth) wm = y.w * M::mad(y.v, M2, M::mad(y.u, M1, M0));
+      sum.add(ps, y.w, wm, (T)1, (T)0);
+    });
+    total.sr += sum.sr, total.si += sum.si;
+    total.dr += sum.dr, total.di += sum.di;
+    total.mr += sum.mr, total.mi += sum.mi;
+  }
+  total.finish(g.sg * col[9 * TC], M::kInv, 1.0, 0.0, false, out);
+}
+
+// The same for the seven-point rule, whose pairs are too few for the general
+// sums' coefficients (coupling of 10368 triangles, Laplace single / double layer:
+// 888 / 1135 us with them, 737 / 870 so, 837 / 953 with three differences per
+// point pair): all x-points in registers, the distance a polynomial of the row's
+// rule coordinates alone.  Helmholtz is bound by its sines and cosines: 1946 /
+// 2140 us, 1945 / 2132.
+template <int KERNEL, int LAYER, class T, class PTS>
+__device__ __forceinline__ void seven_sums(const EntryGeo &g, const double *table, const double *table64,
+                                           double kappa, const PTS &pts, Sums<KERNEL> *out) {
+  typedef Arith<T> M;
+  constexpr int XC = 7;
+  const typename TablePtr<T>::type c = TablePtr<T>::of(table);
+  const uniform_ptr d = (uniform_ptr)table64;
   const T V0 = (T)g.V[0], V1 = (T)g.V[1], V2 = (T)g.V[2];
   const T A0 = (T)g.A[0], A1 = (T)g.A[1], A2 = (T)g.A[2];
   const T B0 = (T)g.B[0], B1 = (T)g.B[1], B2 = (T)g.B[2];
   T m0 = 0, m1 = 0, m2 = 0;
   if constexpr (LAYER == kBoth) m0 = (T)g.m[0], m1 = (T)g.m[1], m2 = (T)g.m[2];
-  const double n0 = fma(g.V[0], g.n[0], fma(g.V[1], g.n[1], g.V[2] * g.n[2])) - g.yn;
-  const double na = 0.5 * fma(g.A[0], g.n[0], fma(g.A[1], g.n[1], g.A[2] * g.n[2]));
-  const double nb = 0.5 * fma(g.B[0], g.n[0], fma(g.B[1], g.n[1], g.B[2] * g.n[2]));
-  const T kq = (T)(M::kPhase * kappa);
-  EntrySums<KERNEL, LAYER, false, T> sum;
-  for (int ch = 0; ch < nqp; ch += XC) {
-    T s[XC], e[XC], q[XC], W[XC], WN[XC];
-#pragma unroll
-    for (int a = 0; a < XC; ++a) {
-      const double sa = rule[ch + a], wa = rule[2 * nqp + ch + a];
-      const double ea = fma(-0.5, sa, rule[nqp + ch + a]);
-      s[a] = (T)sa;
-      e[a] = (T)ea;
-      q[a] = (T)fma(sa * sa, g.k0, fma(sa * ea, g.c1, ea * ea * g.a22));
-      W[a] = (T)wa;
-      if constexpr (LAYER != BEM_SLP) WN[a] = (T)(wa * fma(sa, na, fma(ea, nb, n0)));
-    }
-    for_points<KERNEL == BEM_HELMHOLTZ>(pts, nqp, [&](const typename PTS::P &pt) {
-      T y[3], wy;
-      PTS::unpack(pt, y, &wy);
-      const T D0 = V0 - y[0], D1 = V1 - y[1], D2 = V2 - y[2];
-      const T U = M::mad(D0, D0, M::mad(D1, D1, D2 * D2));
-      const T R = M::mad(D0, A0, M::mad(D1, A1, D2 * A2));
-      const T S = M::mad(D0, B0, M::mad(D1, B1, D2 * B2));
-      T sq[XC], h[XC];
-#pragma unroll
-      for (int a = 0; a < XC; ++a) sq[a] = M::mad(e[a], S, M::mad(s[a], R, U + q[a]));
-#pragma unroll
-      for (int a = 0; a < XC; ++a) h[a] = M::rsq(sq[a]);
-      PointSums<KERNEL, LAYER, T> ps;
-#pragma unroll
-      for (int a = 0; a < XC; ++a) {
-        PairValue<KERNEL, LAYER, false, T> v;
-        v.eval(sq[a], h[a], kq, (T)0);
-        if constexpr (LAYER != BEM_DLP) {
-          ps.sr = M::mad(W[a], v.kr_, ps.sr);
-          if constexpr (KERNEL == BEM_HELMHOLTZ) ps.si = M::mad(W[a], v.ki_, ps.si);
-        }
-        if constexpr (LAYER != BEM_SLP) {
-          const T ar = v.dr();
-          T ai = 0;
-          if constexpr (KERNEL == BEM_HELMHOLTZ) ai = v.di();
-          if constexpr (LAYER == kBoth) ps.t1r = M::mad(W[a], ar, ps.t1r), ps.t1i = M::mad(W[a], ai, ps.t1i);
-          ps.t2r = M::mad(WN[a], ar, ps.t2r);
-          ps.t2i = M::mad(WN[a], ai, ps.t2i);
-        }
-      }
-      T wm = 0;
-      if constexpr (LAYER == kBoth) wm = -wy * M::mad(D0, m0, M::mad(D1, m1, D2 * m2));
-      sum.add(ps, wy, wm, (T)1, (T)0);
-    });
+  // 2 <x - y, n_j> = n0 + s ns + t nt: often far below 2 |x - y|, in FP64
+  double n0 = 0, ns = 0, nt = 0;
+  if constexpr (LAYER != BEM_SLP) {
+    n0 = fma(g.V[0], g.n[0], fma(g.V[1], g.n[1], g.V[2] * g.n[2])) - g.yn;
+    nt = 0.5 * fma(g.B[0], g.n[0], fma(g.B[1], g.n[1], g.B[2] * g.n[2]));
+    ns = fma(-0.5, nt, 0.5 * fma(g.A[0], g.n[0], fma(g.A[1], g.n[1], g.A[2] * g.n[2])));
   }
+  const T kq = (T)(M::kPhase * kappa);
+  T q[XC], WN[XC];
+#pragma unroll
+  for (int a = 0; a < XC; ++a) {
+    q[a] = (T)fma(d[4 * XC + a], g.k0, fma(d[5 * XC + a], g.c1, d[6 * XC + a] * g.a22));
+    if constexpr (LAYER != BEM_SLP) WN[a] = (T)(d[2 * XC + a] * fma(d[a], ns, fma(d[XC + a], nt, n0)));
+  }
+  EntrySums<KERNEL, LAYER, false, T> sum;
+  for_points<false>(pts, XC, [&](const typename PTS::P &pt) {
+    T y[3], wy;
+    PTS::unpack(pt, y, &wy);
+    const T D0 = V0 - y[0], D1 = V1 - y[1], D2 = V2 - y[2];
+    const T U = M::mad(D0, D0, M::mad(D1, D1, D2 * D2));
+    const T R = M::mad(D0, A0, M::mad(D1, A1, D2 * A2));
+    const T S = M::mad(D0, B0, M::mad(D1, B1, D2 * B2));
+    T sq[XC], h[XC];
+#pragma unroll
+    for (int a = 0; a < XC; ++a) sq[a] = M::mad(c[3 * XC + a], S, M::mad(c[a], R, U + q[a]));
+#pragma unroll
+    for (int a = 0; a < XC; ++a) h[a] = M::rsq(sq[a]);
+    PointSums<KERNEL, LAYER, T> ps;
+#pragma unroll
+    for (int a = 0; a < XC; ++a)
+      add_value(sq[a], h[a], kq, c[2 * XC + a], LAYER != BEM_SLP ? WN[a] : (T)0, &ps);
+    T wm = 0;
+    if constexpr (LAYER == kBoth) wm = -wy * M::mad(D0, m0, M::mad(D1, m1, D2 * m2));
+    sum.add(ps, wy, wm, (T)1, (T)0);
+  });
   sum.finish(g.sg, M::kInv, 1.0, 0.0, false, out);
 }
 
-// Rule variants of the kernels: the Duffy orders 2 .. 6, else the general sums
-// in chunks of 4 or 7 x-points.
-constexpr int kRule4 = 14, kRule7 = 17;
+// Rule variants of the kernels: the Duffy orders 2 .. 6, seven points, else the
+// general sums in chunks of 4, 7, 8 or 9 x-points (rule_variant).
+constexpr int kSeven = 13, kRule4 = 14, kRule7 = 17, kRule8 = 18, kRule9 = 19;
 
 // Operands of entry (rl, cl) of the staged sub-tile.
 template <int LAYER, bool MIXED>
@@ -685,24 +789,24 @@ __device__ __forceinline__ EntryGeo entry_geo(const Lds &l, int TR, int TC, int 
 // All sums of regular entry (rl, cl), FP64 or (mixed) FP32.  brief: Helmholtz
 // with short phases, uniform in the workgroup (block_is_brief).
 template <int KERNEL, int LAYER, int RULE, bool MIXED>
-__device__ __forceinline__ void regular_sums(const Lds &l, int TR, int TC, int nqp, int rl, int cl,
-                                             const double *table, double kappa, bool brief, Sums<KERNEL> *o) {
+__device__ __forceinline__ void regular_sums(const Lds &l, int TR, int TC, int nq, int rl, int cl,
+                                             const double *table, const double *table64, double kappa, bool brief, Sums<KERNEL> *o) {
   const EntryGeo g = entry_geo<LAYER, MIXED>(l, TR, TC, rl, cl);
   typedef typename std::conditional<MIXED, float, double>::type T;
-  typename std::conditional<MIXED, PointsLds32, PointsLds64>::type pts;
-  if constexpr (MIXED) {
-    pts.p = reinterpret_cast<const float4 *>(l.ys) + cl;
-    pts.stride = TC;
-  } else {
-    pts.p = reinterpret_cast<const double2 *>(l.ys) + 2 * cl;
-    pts.stride = 2 * TC;
-  }
   if constexpr (RULE >= kRule4) {
-    general_sums<KERNEL, LAYER, RULE - 10, T>(g, l.rule, nqp, kappa, pts, o);
-  } else if constexpr (KERNEL == BEM_LAPLACE) {
-    duffy_sums<KERNEL, LAYER, RULE, false, T>(g, table, kappa, pts, o);
+    const T *gb = reinterpret_cast<const T *>(l.ys + kColumnFields * TC);
+    general_sums<KERNEL, LAYER, RULE - 10, T>(g, l.ys + cl, gb + cl, TC, table, table64, nq, kappa, o);
   } else {
-    if (brief) duffy_sums<KERNEL, LAYER, RULE, true, T>(g, table, kappa, pts, o);
+    typename std::conditional<MIXED, PointsLds32, PointsLds64>::type pts;
+    if constexpr (MIXED) {
+      pts.p = reinterpret_cast<const float4 *>(l.ys) + cl;
+      pts.stride = TC;
+    } else {
+      pts.p = reinterpret_cast<const double2 *>(l.ys) + 2 * cl;
+      pts.stride = 2 * TC;
+    }
+    if constexpr (RULE == kSeven) seven_sums<KERNEL, LAYER, T>(g, table, table64, kappa, pts, o);
+    else if (KERNEL == BEM_HELMHOLTZ && brief) duffy_sums<KERNEL, LAYER, RULE, true, T>(g, table, kappa, pts, o);
     else duffy_sums<KERNEL, LAYER, RULE, false, T>(g, table, kappa, pts, o);
   }
 }

@@ -110,14 +110,13 @@ __device__ bool block_is_brief(const BlockArgs &a, const Lds &l, const BlockHdr 
   }
 }
 
-// The quadrature rule into LDS (padded with zero weights to nqp points).
+// The quadrature rule into LDS.
 __device__ __forceinline__ void load_rule(const BlockArgs &a, const Lds &l) {
   const int nqp = a.nq_pad, nq = a.nq;
-  for (int k = thread_id(); k < nqp; k += kThreads) {
-    const bool real = k < nq;
-    l.rule[k] = real ? a.rule[k] : 0.0;
-    l.rule[nqp + k] = real ? a.rule[nq + k] : 0.0;
-    l.rule[2 * nqp + k] = real ? a.rule[2 * nq + k] : 0.0;
+  for (int k = thread_id(); k < nq; k += kThreads) {
+    l.rule[k] = a.rule[k];
+    l.rule[nqp + k] = a.rule[nq + k];
+    l.rule[2 * nqp + k] = a.rule[2 * nq + k];
   }
 }
 
@@ -198,34 +197,45 @@ __device__ bool stage_tile(const BlockArgs &a, const Lds &l, const BlockHdr &h, 
   return true;
 }
 
-// Phase B: the column quadrature points of the rule in l.rule (nq points
-// padded to nqp with zero weights), then a barrier.
-template <bool MIXED>
-__device__ void stage_columns(const BlockArgs &a, const Lds &l, const BlockHdr &h, int tc, int nq,
-                              int nqp) {
-  const int TC = a.tc;
+// The sub-tile's column triangles [kColumnFields][TC] into l.ys: 2 (v0 - c),
+// 2 e1, 2 e2 and sqrt(g).
+__device__ __forceinline__ void stage_triangles(const BlockArgs &a, const Lds &l, const BlockHdr &h, int tc) {
+  for (int k = thread_id(); k < tc * kColumnFields; k += kThreads) {
+    const int cl = k % tc, m = k / tc, id = l.cid[cl];
+    const double x = a.geo[(m < 9 ? G_V0X + m : G_SG) * a.ldg + id];
+    l.ys[m * a.tc + cl] = m == 9 ? x : 2.0 * (m == 0 ? x - h.cx : m == 1 ? x - h.cy : m == 2 ? x - h.cz : x);
+  }
+}
+
+// Phase B: what the regular sums keep of the columns, then a barrier.
+// Rules with kernels of their own: the column points of the rule in l.rule.  General rules: the triangles, and 4 |y - v0|^2 of every point.
+template <int RULE, bool MIXED>
+__device__ void stage_columns(const BlockArgs &a, const Lds &l, const BlockHdr &h, int tc) {
+  const int TC = a.tc, nqp = a.nq_pad;
   const int64_t L = a.ldg;
   const double cx = h.cx, cy = h.cy, cz = h.cz;
-  for (int k = thread_id(); k < tc * nqp; k += kThreads) {
+  constexpr bool LOCAL = MIXED || RULE >= kRule4;  // relative to the triangle's first vertex
+  if constexpr (RULE >= kRule4) stage_triangles(a, l, h, tc);
+  for (int k = thread_id(); k < tc * a.nq; k += kThreads) {
     const int cl = k % tc, q = k / tc;
     const int id = l.cid[cl];
-    const bool real = q < nq;
     const double s = l.rule[q], t = l.rule[nqp + q];
-    const double W = l.rule[2 * nqp + q] * a.geo[G_SG * L + id];  // 0 for padding
-    // padding points far away; mixed: local to the column triangle
-    double P0 = -kPad, P1 = -kPad, P2 = -kPad;
-    if (real) {
-      P0 = 2.0 * fma(s, a.geo[G_E1X * L + id], fma(t, a.geo[G_E2X * L + id], MIXED ? 0.0 : a.geo[G_V0X * L + id] - cx));
-      P1 = 2.0 * fma(s, a.geo[G_E1Y * L + id], fma(t, a.geo[G_E2Y * L + id], MIXED ? 0.0 : a.geo[G_V0Y * L + id] - cy));
-      P2 = 2.0 * fma(s, a.geo[G_E1Z * L + id], fma(t, a.geo[G_E2Z * L + id], MIXED ? 0.0 : a.geo[G_V0Z * L + id] - cz));
-    }
-    if constexpr (!MIXED) {
-      double2 *y = reinterpret_cast<double2 *>(l.ys) + 2 * ((int64_t)q * TC + cl);
-      y[0] = make_double2(P0, P1);
-      y[1] = make_double2(P2, W);
+    const double P0 = 2.0 * fma(s, a.geo[G_E1X * L + id], fma(t, a.geo[G_E2X * L + id], LOCAL ? 0.0 : a.geo[G_V0X * L + id] - cx));
+    const double P1 = 2.0 * fma(s, a.geo[G_E1Y * L + id], fma(t, a.geo[G_E2Y * L + id], LOCAL ? 0.0 : a.geo[G_V0Y * L + id] - cy));
+    const double P2 = 2.0 * fma(s, a.geo[G_E1Z * L + id], fma(t, a.geo[G_E2Z * L + id], LOCAL ? 0.0 : a.geo[G_V0Z * L + id] - cz));
+    if constexpr (RULE >= kRule4) {
+      typedef typename std::conditional<MIXED, float, double>::type T;
+      reinterpret_cast<T *>(l.ys + kColumnFields * TC)[q * TC + cl] = (T)fma(P0, P0, fma(P1, P1, P2 * P2));
     } else {
-      float4 *y = reinterpret_cast<float4 *>(l.ys) + ((int64_t)q * TC + cl);
-      *y = make_float4((float)P0, (float)P1, (float)P2, (float)W);
+      const double W = l.rule[2 * nqp + q] * a.geo[G_SG * L + id];
+      if constexpr (!MIXED) {
+        double2 *y = reinterpret_cast<double2 *>(l.ys) + 2 * ((int64_t)q * TC + cl);
+        y[0] = make_double2(P0, P1);
+        y[1] = make_double2(P2, W);
+      } else {
+        float4 *y = reinterpret_cast<float4 *>(l.ys) + ((int64_t)q * TC + cl);
+        *y = make_float4((float)P0, (float)P1, (float)P2, (float)W);
+      }
     }
   }
   __syncthreads();
@@ -450,7 +460,7 @@ template <int KERNEL, int LAYER, int RULE, bool MIXED>
 __device__ void subtile(const BlockArgs &a, const Lds &l, const BlockHdr &h, int64_t r0,
                         int64_t c0, int coupling) {
   const int tid = thread_id(), lane = tid & (kWave - 1);
-  const int nqp = a.nq_pad, TR = a.tr, TC = a.tc;
+  const int TR = a.tr, TC = a.tc;
   const int64_t nr = h.nr, off = h.off;
   const double ratio = a.near_ratio;
   const int tr = (int)min((int64_t)TR, h.nr - r0), tc = (int)min((int64_t)TC, h.nc - c0);
@@ -461,7 +471,7 @@ __device__ void subtile(const BlockArgs &a, const Lds &l, const BlockHdr &h, int
   const bool lower = h.diag && r0 == c0 && tr == tc;
   const bool upper_skip = h.diag && !lower;
   if (!stage_tile<MIXED>(a, l, h, r0, c0, tr, tc)) return;
-  stage_columns<MIXED>(a, l, h, tc, a.nq, nqp);
+  stage_columns<RULE, MIXED>(a, l, h, tc);
   // phase C: list the pairs of the FP64 pass
   for (int e = tid; e < tr * tc; e += kThreads) {
     const int rl = e % tr, cl = e / tr;
@@ -517,7 +527,7 @@ __device__ void subtile(const BlockArgs &a, const Lds &l, const BlockHdr &h, int
     int cls;
     if (fp64_pair<MIXED>(l, TR, TC, rl, cl, ratio, &cls)) continue;
     Sums<KERNEL> o;
-    regular_sums<KERNEL, LAYER, RULE, MIXED>(l, TR, TC, nqp, rl, cl, a.duffy, a.kappa, h.brief, &o);
+    regular_sums<KERNEL, LAYER, RULE, MIXED>(l, TR, TC, a.nq, rl, cl, a.sums, a.rule, a.kappa, h.brief, &o);
     scale_sums(&o);
     const int64_t dst = off + (r0 + rl) + nr * (c0 + cl);
     const int64_t mdst = h.moff + (c0 + cl) + h.nc * (r0 + rl);
@@ -558,11 +568,7 @@ __device__ void subtile_learned(const BlockArgs &a, const OrderRules &o, const L
   const int tr = (int)min((int64_t)TR, h.nr - r0), tc = (int)min((int64_t)TC, h.nc - c0);
   const int cap = TR * TC;
   if (!stage_tile<false>(a, l, h, r0, c0, tr, tc)) return;
-  for (int k = tid; k < tc * kColumnFields; k += kThreads) {
-    const int cl = k % tc, m = k / tc, id = l.cid[cl];
-    const double x = a.geo[(m < 9 ? G_V0X + m : G_SG) * a.ldg + id];
-    l.ys[m * TC + cl] = m == 9 ? x : 2.0 * (m == 0 ? x - h.cx : m == 1 ? x - h.cy : m == 2 ? x - h.cz : x);
-  }
+  stage_triangles(a, l, h, tc);
   // classify: singular pairs to the front of the list, regular ones (with
   // their order) to the back
   for (int e = tid; e < tr * tc; e += kThreads) {
@@ -653,7 +659,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_blocks(const BlockArgs a, const
   BlockHdr h;
   if (!block_header(a, blockIdx.x, &h) || h.nr == 0 || h.nc == 0) return;
   const Lds l = carve<MIXED>(lds_raw, a.nq_pad, a.tr, a.tc, LAYER == kBoth);
-  h.brief = block_is_brief<KERNEL>(a, l, h);
+  h.brief = RULE < kSeven && block_is_brief<KERNEL>(a, l, h);
   load_rule(a, l);
   // the block's sub-tiles, dealt to gridDim.y workgroups
   unsigned turn = blockIdx.y;
@@ -713,7 +719,7 @@ __device__ __forceinline__ void persistent_item(const BlockArgs *__restrict__ ba
     load_rule(a, l);
     *carved = shape;
   }
-  h.brief = block_is_brief<KERNEL>(a, l, h);
+  h.brief = RULE < kSeven && block_is_brief<KERNEL>(a, l, h);
   if (whole) {  // the whole block, sub-tile by sub-tile
     for (int64_t r0 = 0; r0 < h.nr; r0 += a.tr)
       for (int64_t c0 = 0; c0 < h.nc; c0 += a.tc) subtile<KERNEL, LAYER, RULE, MIXED>(a, l, h, r0, c0, cp);
@@ -765,16 +771,21 @@ hipError_t launch_rule(int layer, bool coupling, const BlockArgs &a, size_t lds,
   return hipGetLastError();
 }
 
-// f(integral constant of the rule variant)
-template <class F>
+// f(integral constant of the rule variant).  Helmholtz takes chunks of 4 in
+// place of 8 and 9, whose sines and cosines would not fit the registers.
+template <int KERNEL, class F>
 hipError_t with_rule(int rule, F &&f) {
+  constexpr bool HELM = KERNEL == BEM_HELMHOLTZ;
   switch (rule) {
     case 2: return f(std::integral_constant<int, 2>{});
     case 3: return f(std::integral_constant<int, 3>{});
     case 4: return f(std::integral_constant<int, 4>{});
     case 5: return f(std::integral_constant<int, 5>{});
     case 6: return f(std::integral_constant<int, 6>{});
+    case kSeven: return f(std::integral_constant<int, kSeven>{});
     case kRule7: return f(std::integral_constant<int, kRule7>{});
+    case kRule8: return f(std::integral_constant<int, HELM ? kRule4 : kRule8>{});
+    case kRule9: return f(std::integral_constant<int, HELM ? kRule4 : kRule9>{});
     case kRule4: return f(std::integral_constant<int, kRule4>{});
     default: return hipErrorInvalidValue;
   }
@@ -785,7 +796,7 @@ hipError_t with_rule(int rule, F &&f) {
 template <int KERNEL, bool MIXED>
 hipError_t BlockLaunch<KERNEL, MIXED>::blocks(int layer, int rule, bool coupling, const BlockArgs &a,
                                               size_t lds, hipStream_t s) {
-  return with_rule(rule, [&](auto r) {
+  return with_rule<KERNEL>(rule, [&](auto r) {
     return launch_rule<KERNEL, MIXED, decltype(r)::value>(layer, coupling, a, lds, s);
   });
 }
@@ -793,7 +804,7 @@ hipError_t BlockLaunch<KERNEL, MIXED>::blocks(int layer, int rule, bool coupling
 template <int KERNEL, bool MIXED>
 hipError_t PersistentLaunch<KERNEL, MIXED>::run(int rule, const PersistentArgs &p, size_t lds,
                                                 hipStream_t s) {
-  return with_rule(rule, [&](auto r) {
+  return with_rule<KERNEL>(rule, [&](auto r) {
     hipLaunchKernelGGL((k_persistent<KERNEL, decltype(r)::value, MIXED>), dim3(p.grid), dim3(kThreads),
                        lds, s, p.batches, p.mode, p.tiles, p.ntiles, p.nbatch, p.counter);
     return hipGetLastError();

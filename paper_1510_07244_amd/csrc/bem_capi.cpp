@@ -114,16 +114,13 @@ int get_rules(bem_ctx *ctx, const bem_op *op, const bem::DevRules **out) {
     };
     const bem::TriRule tr = bem::triangle_rule(op->regular_rule, op->q_regular);
     d.nq = (int)tr.s.size();
-    const size_t at_tri = put({&tr.s, &tr.t, &tr.w});
-    size_t at_duffy = 0, at_duffy32 = 0;
-    const bool duffy = bem::rule_variant(op->regular_rule, op->q_regular, d.nq) == op->q_regular;
-    if (duffy) {
-      std::vector<double> t = bem::duffy_table(op->q_regular), f((t.size() + 1) / 2);
-      std::vector<float> t32(t.begin(), t.end());
-      std::memcpy(f.data(), t32.data(), t32.size() * sizeof(float));
-      at_duffy = put({&t});
-      at_duffy32 = put({&f});
-    }
+    const bool duffy = bem::rule_is_duffy(bem::rule_variant(op->regular_rule, op->q_regular, d.nq));
+    const std::vector<double> t = duffy ? bem::duffy_table(op->q_regular) : bem::general_table(tr);
+    const std::vector<float> t32(t.begin(), t.end());
+    std::vector<double> f((t.size() + 1) / 2);
+    std::memcpy(f.data(), t32.data(), t32.size() * sizeof(float));
+    const size_t at_sums = put({&t}), at_sums32 = put({&f});
+    const size_t at_tri = duffy ? put({&tr.s, &tr.t, &tr.w}) : at_sums;  // its first rows
     const bem::XiRule xr = bem::xi_rule(op->q_singular);
     std::vector<double> w2(xr.x.size());
     for (size_t k = 0; k < w2.size(); ++k) w2[k] = xr.w3[k] / xr.x[k];
@@ -148,7 +145,7 @@ int get_rules(bem_ctx *ctx, const bem_op *op, const bem::DevRules **out) {
       return hip_fail(ctx, e, "hipMemcpy(quadrature tables)");
     }
     d.tri = d.mem + at_tri;
-    if (duffy) d.duffy = d.mem + at_duffy, d.duffy32 = d.mem + at_duffy32;
+    d.sums = d.mem + at_sums, d.sums32 = d.mem + at_sums32;
     d.xi = d.mem + at_xi;
     for (int cls = 1; cls <= 3; ++cls) d.ss[cls] = d.mem + at_ss[cls], d.sing[cls] = d.mem + at_sing[cls];
     auto ins = ctx->rules.emplace(key, d);
@@ -234,7 +231,7 @@ int assemble_blocks(bem_ctx *ctx, const bem_mesh *mesh, const bem_op *op,
   a.nq_pad = bem::rule_pad(variant, rules->nq);
   size_t lds;
   const bool mixed = op->precision == BEM_MIXED;
-  a.duffy = mixed ? rules->duffy32 : rules->duffy;
+  a.sums = mixed ? rules->sums32 : rules->sums;
   if (!bem::block_tile_shape(a.nq_pad, mixed, ctx->lds_budget, &a.tr, &a.tc, &lds, coupling,
                              both))
     return fail(ctx, BEM_EUNSUPPORTED, "quadrature order too high for the LDS budget");

@@ -27,6 +27,8 @@ struct TriRule {
 TriRule triangle_rule(int rule, int q);
 // Constants of the Duffy rule of order q in the block kernels' layout (DuffyAt).
 std::vector<double> duffy_table(int q);
+// Constants of any other rule: s, t, w, e = t - s / 2, s^2, s e, e^2 [7][points].
+std::vector<double> general_table(const TriRule &r);
 
 // Sauter-Schwab rule of one singular class, factored as (x^, y^) = xi g(eta):
 // per region and (eta1, eta2, eta3) Gauss triple the map g at xi = 1
@@ -78,9 +80,10 @@ enum : unsigned { FLAG_EINVAL = 1u, FLAG_NONFINITE = 2u, FLAG_LIST = 4u };
 struct DevRules {
   double *mem = nullptr;
   int nq = 0;                   // points per triangle (regular rule)
-  const double *tri = nullptr;  // [3][nq]: s, t, w
-  // Duffy rules of orders 2 .. 6: duffy_table in double and in float (else null)
-  const double *duffy = nullptr, *duffy32 = nullptr;
+  const double *tri = nullptr;  // [3][nq]: s, t, w (general_table: the first rows of sums)
+  // constants of the block kernels' regular sums, in double and in float:
+  // duffy_table for the Duffy orders 2 .. 6, else general_table
+  const double *sums = nullptr, *sums32 = nullptr;
   // Sauter-Schwab eta tables per class 1..3 (piecewise-linear bases)
   int np[4] = {0, 0, 0, 0};
   const double *ss[4] = {nullptr, nullptr, nullptr, nullptr};  // [5][np]: xs, xt, ys, yt, w
@@ -125,7 +128,7 @@ struct BlockArgs {
   void *out2;          // both layers in one pass: the double layer's output
   int64_t out_len;
   const double *rule;  // [3][nq]
-  const double *duffy;  // DevRules::duffy, mixed form duffy32 (float)
+  const double *sums;  // DevRules::sums, mixed form sums32 (float)
   int32_t nq, nq_pad;
   int32_t tr, tc;      // sub-tile rows / columns
   int32_t split;       // workgroups per block (per-block kernels)
@@ -365,8 +368,10 @@ size_t block_lds_bytes(int nq_pad, int tr, int tc, bool mixed, bool lists = true
 int split_blocks(const BlockArgs &a, bool coupling, bool mixed, bool lists, bool both, int *tc,
                  size_t *lds_bytes);
 int rule_chunk(int nq, int kernel);
-// kernel variant of a rule (regular_rule, order, points) and its padded points
+// kernel variant of a rule (regular_rule, order, points) and the room of its
+// column points in LDS
 int rule_variant(int regular_rule, int q, int nq);
+bool rule_is_duffy(int variant);
 int rule_pad(int variant, int nq);
 
 }  // namespace bem

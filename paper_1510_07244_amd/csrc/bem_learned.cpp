@@ -265,7 +265,7 @@ int bem_assemble_nearfield_learned(bem_ctx *ctx, const bem_mesh *mesh, const bem
   hipError_t e = launch_geometry(*mesh, ctx->geo, ldg, ctx->flags, s);
   if (e != hipSuccess) return hip_fail(ctx, e, "geometry kernel launch");
   OrderRules o{};
-  for (int q = 2; q <= op->q_regular; ++q) o.rule[q] = r[q]->tri, o.duffy[q] = r[q]->duffy;
+  for (int q = 2; q <= op->q_regular; ++q) o.rule[q] = r[q]->tri, o.duffy[q] = r[q]->sums;
   o.orders = orders;
   o.q_max = op->q_regular;
   const DevRules *plain = r[op->q_regular];

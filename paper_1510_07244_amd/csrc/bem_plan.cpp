@@ -548,7 +548,7 @@ int bem_plan_batched(bem_ctx *ctx, const bem_op *op, int32_t nbatch, const bem_b
       a.out_len = hb.out_len;
       a.rule = rules->tri;
       a.nq = rules->nq;
-      a.duffy = p->mixed ? rules->duffy32 : rules->duffy;
+      a.sums = p->mixed ? rules->sums32 : rules->sums;
       a.nq_pad = nqp;
       a.tr = sh[k].first;
       a.tc = sh[k].second;

@@ -100,6 +100,17 @@ std::vector<double> duffy_table(int q) {
   return t;
 }
 
+std::vector<double> general_table(const TriRule &r) {
+  const size_t n = r.s.size();
+  std::vector<double> t(7 * n);
+  for (size_t k = 0; k < n; ++k) {
+    const double s = r.s[k], e = r.t[k] - 0.5 * s;
+    const double row[7] = {s, r.t[k], r.w[k], e, s * s, s * e, e * e};
+    for (int f = 0; f < 7; ++f) t[f * n + k] = row[f];
+  }
+  return t;
+}
+
 // One point of a Sauter-Schwab region: returns (x^1, x^2, y^1, y^2) and the
 // Jacobian of the region map at (xi, h1, h2, h3) in [0,1]^4.  The maps send
 // [0,1]^4 onto a piece of {0 <= x2 <= x1 <= 1}^2 such that the pieces of one
