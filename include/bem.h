@@ -236,8 +236,8 @@ int bem_eval_entries(bem_ctx *ctx, const bem_mesh *mesh, const bem_op *op, int64
  * entries, 128 x 96 in plain coupling lists), sorted by decreasing
  * estimated cost; a fixed grid of workgroups pops items from it until it is
  * empty.  The queue, per-mesh geometry and launch are built once by
- * bem_plan_batched and captured in a HIP graph (a counter-reset kernel,
- * the geometry kernels and the persistent kernel); bem_run_batched replays
+ * bem_plan_batched and captured in a HIP graph (the geometry kernels, a
+ * counter-reset kernel and the persistent kernel); bem_run_batched replays
  * it.  Entries are bitwise equal to those of bem_assemble_nearfield /
  * bem_assemble_coupling.
  * --------------------------------------------------------------------- */

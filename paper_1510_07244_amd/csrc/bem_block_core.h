@@ -90,6 +90,14 @@ __device__ __forceinline__ Lds carve(double *base, int nqp, int TR, int TC, bool
   return l;
 }
 
+// Whether triangle id may be in a block of short Helmholtz phases: kappa times
+// the largest distance of a point from its centroid at most 3/4 (short_phase)
+// and at least 1e-10 (coordinates are scaled by kappa then).
+__device__ __forceinline__ bool is_brief(const BlockArgs &a, int id) {
+  const double x = id >= 0 && id < a.nt ? a.kappa * a.kappa * a.geo[G_R2 * a.ldg + id] : 0.0;
+  return x <= kShortPhase * kShortPhase && x >= 1e-20;
+}
+
 // ------------------------------------------------------------ regular sums
 // Arithmetic of the two precisions.  FP64: 1/r from the hardware estimate and
 // one Newton step, z = h u with u = 3 - s h^2.  FP32 (mixed form): the

@@ -81,9 +81,7 @@ __device__ __forceinline__ bool block_header(const BlockArgs &a, int b, BlockHdr
 }
 
 // Whether block h may take its Helmholtz phases relative to the centroids'
-// distance: kappa times the largest distance of a point from its centroid at
-// most 3/4 (short_phase) for every triangle of its rows and columns (and at
-// least 1e-10: coordinates are scaled by kappa then).  A property of the block
+// distance: is_brief for every triangle of its rows and columns.  A property of the block
 // alone, so that its entries do not depend on the kernel or the sub-tiles that
 // compute them, and one for all its entries: with a decision per entry, waves
 // that held both kinds ran both sums (0.64x on a coarse mesh).  Uniform; starts
@@ -97,11 +95,9 @@ __device__ bool block_is_brief(const BlockArgs &a, const Lds &l, const BlockHdr 
     __syncthreads();
     if (tid == 0) *l.bad = 0;
     __syncthreads();
-    const double k2 = a.kappa * a.kappa;
     for (int64_t k = tid; k < h.nr + h.nc; k += kThreads) {
       const int id = k < h.nr ? a.row_idx[h.rp0 + k] : a.col_idx[h.cp0 + (k - h.nr)];
-      const double x = id >= 0 && id < a.nt ? k2 * a.geo[G_R2 * a.ldg + id] : 0.0;
-      if (!(x <= kShortPhase * kShortPhase && x >= 1e-20)) *l.bad = 1;
+      if (!is_brief(a, id)) *l.bad = 1;
     }
     __syncthreads();
     const bool brief = *l.bad == 0;
@@ -719,7 +715,8 @@ __device__ __forceinline__ void persistent_item(const BlockArgs *__restrict__ ba
     load_rule(a, l);
     *carved = shape;
   }
-  h.brief = RULE < kSeven && block_is_brief<KERNEL>(a, l, h);
+  h.brief = KERNEL == BEM_HELMHOLTZ && RULE < kSeven &&
+            (a.brief ? a.brief[d.y] != 0 : block_is_brief<KERNEL>(a, l, h));
   if (whole) {  // the whole block, sub-tile by sub-tile
     for (int64_t r0 = 0; r0 < h.nr; r0 += a.tr)
       for (int64_t c0 = 0; c0 < h.nc; c0 += a.tc) subtile<KERNEL, LAYER, RULE, MIXED>(a, l, h, r0, c0, cp);

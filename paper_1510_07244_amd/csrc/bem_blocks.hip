@@ -13,6 +13,38 @@ namespace {
 
 __global__ void k_reset_counter(int32_t *counter) { *counter = 0; }
 
+// The same, and one workgroup per block for its phase kind.
+constexpr int kBeginThreads = 1024;
+__global__ __launch_bounds__(kBeginThreads) void k_begin(int32_t *counter, const BlockArgs *batches,
+                                                         int32_t nbatch) {
+  constexpr int U = 4;  // triangles in flight
+  const int tid = threadIdx.x;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) *counter = 0;
+  for (int32_t k = blockIdx.y; k < nbatch; k += gridDim.y) {
+    const BlockArgs &a = batches[k];
+    if (!a.brief) continue;  // uniform
+    for (int32_t b = blockIdx.x; b < a.nblocks; b += gridDim.x) {
+      const int64_t rp0 = a.row_ptr[b], nr = a.row_ptr[b + 1] - rp0;
+      const int64_t cp0 = a.col_ptr[b], nc = a.col_ptr[b + 1] - cp0;
+      // ranges that block_header refuses: not read
+      int bad = rp0 < 0 || nr < 0 || rp0 + nr > a.row_len || cp0 < 0 || nc < 0 || cp0 + nc > a.col_len;
+      const int64_t n = bad ? 0 : nr + nc;
+      for (int64_t i0 = tid; i0 < n; i0 += U * kBeginThreads) {
+        int id[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int64_t i = min(i0 + u * kBeginThreads, n - 1);
+          id[u] = i < nr ? a.row_idx[rp0 + i] : a.col_idx[cp0 + (i - nr)];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) bad |= !blk::is_brief(a, id[u]);
+      }
+      bad = __syncthreads_or(bad);
+      if (tid == 0) a.brief[b] = !bad;
+    }
+  }
+}
+
 }  // namespace
 
 // Duffy rules of orders 2 .. 6 (every order the configurations use) and the
@@ -140,8 +172,14 @@ hipError_t launch_blocks_learned(int kernel, int layer, const BlockArgs &a, cons
                                : LearnedLaunch<BEM_HELMHOLTZ>::run(layer, a, o, lds, s);
 }
 
-hipError_t launch_reset_counter(int32_t *counter, hipStream_t s) {
-  hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(1), 0, s, counter);
+hipError_t launch_begin(int32_t *counter, const BlockArgs *batches, int32_t nbatch, int32_t max_blocks,
+                        hipStream_t s) {
+  if (max_blocks == 0) {
+    hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(1), 0, s, counter);
+  } else {
+    const dim3 grid(std::min(max_blocks, 4096), std::min(nbatch, 4096));
+    hipLaunchKernelGGL(k_begin, grid, dim3(kBeginThreads), 0, s, counter, batches, nbatch);
+  }
   return hipGetLastError();
 }
 

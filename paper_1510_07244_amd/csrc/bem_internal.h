@@ -132,6 +132,8 @@ struct BlockArgs {
   int32_t nq, nq_pad;
   int32_t tr, tc;      // sub-tile rows / columns
   int32_t split;       // workgroups per block (per-block kernels)
+  int32_t *brief;      // per block: whether its Helmholtz phases are short
+                       // (launch_begin), null: every work item finds out
   SSArgs ss;
   double kappa;
   double near_ratio;   // mixed form: near-singular box-distance ratio
@@ -341,7 +343,11 @@ hipError_t launch_blocks_learned(int kernel, int layer, const BlockArgs &a, cons
 // PersistentArgs::mode, its sub-tile shape in its BlockArgs
 hipError_t launch_persistent(int kernel, bool mixed, int rule, const PersistentArgs &p,
                              size_t lds_bytes, hipStream_t s);
-hipError_t launch_reset_counter(int32_t *counter, hipStream_t s);
+// before launch_persistent: the queue's head to 0, and the phase kinds of the
+// blocks of every batch entry that keeps them (BlockArgs::brief; max_blocks: the
+// most of one entry, 0 if none keeps any)
+hipError_t launch_begin(int32_t *counter, const BlockArgs *batches, int32_t nbatch, int32_t max_blocks,
+                        hipStream_t s);
 
 hipError_t launch_green(int kernel, int side, const GreenArgs &a, int grid_y, hipStream_t s);
 hipError_t launch_contract(bool cplx, const ContractArgs &a, int grid_y, hipStream_t s);
