@@ -16,15 +16,17 @@ def vertex_stars(tri, vertices):
     vertices = np.asarray(vertices, dtype=np.int64)
     pos = np.full(int(tri.max()) + 1 if tri.size else 0, -1, dtype=np.int64)
     pos[vertices] = np.arange(vertices.size)
-    named = np.flatnonzero(vertices >= 0)
-    if named.size < vertices.size:  # ids from the end name no vertex
+    ends = vertices.size and tri.size and min(vertices.min(), tri.min()) < 0
+    if ends:  # ids from the end name no vertex
+        named = np.flatnonzero(vertices >= 0)
         pos[vertices[named]] = named
     owner = pos[tri[:, :3]]  # a vertex's number in the list, per corner
     t_ids, locs = np.nonzero(owner >= 0)
     owner = owner[t_ids, locs]
-    wrong = vertices[owner] != tri[t_ids, locs]
-    if wrong.any():
-        raise KeyError(int(tri[t_ids[wrong][0], locs[wrong][0]]))
+    if ends:
+        wrong = vertices[owner] != tri[t_ids, locs]
+        if wrong.any():
+            raise KeyError(int(tri[t_ids[wrong][0], locs[wrong][0]]))
     order = np.argsort(owner, kind="stable")  # by vertex, then triangle
     used = np.zeros(tri.shape[0], dtype=bool)
     used[t_ids] = True
