@@ -39,8 +39,11 @@ def vertex_stars(tri, vertices):
 
 def _upload(arrays):
     """int32 device tensors of the arrays: one copy from pinned memory, on the
-    current stream and without waiting for it."""
+    current stream and without waiting for it.  Refused under stream capture: the
+    pinned memory goes back to its pool, a replay would copy what is there then."""
     import torch
+    if torch.cuda.is_current_stream_capturing():
+        raise RuntimeError("index lists of a P1 block are uploaded at the call: it cannot be captured")
     sizes = [a.size for a in arrays]
     host = torch.empty(sum(sizes), dtype=torch.int32, pin_memory=True)
     np.concatenate(arrays, out=host.numpy())
