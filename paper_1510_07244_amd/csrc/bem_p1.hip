@@ -250,13 +250,16 @@ __global__ __launch_bounds__(kThreads) void k_p1_gather(const P1GatherArgs a) {
   else static_cast<double *>(a.out)[e] = re;
 }
 
-// lanes per pair: see the kernel of arbitrary entries
+// lanes per pair: see the kernel of arbitrary entries; 4 lanes and one, order 4,
+// Laplace / Helmholtz: 200000 pairs 66 / 142 and 69 / 157 us, 440000 120 / 288 and
+// 105 / 262.  One lane also leaves long lists all of a launch's 2^32 threads.
 template <int KERNEL, int LAYER>
 void launch_p1_kl(const P1Args &a, hipStream_t s) {
   const dim3 block(kThreads);
   auto grid = [&](int G) { return dim3((unsigned)((a.n * G + kThreads - 1) / kThreads)); };
   if (a.n < (1 << 15)) hipLaunchKernelGGL((k_p1_pairs<KERNEL, LAYER, 16, 1>), grid(16), block, 0, s, a);
-  else hipLaunchKernelGGL((k_p1_pairs<KERNEL, LAYER, 4, 4>), grid(4), block, 0, s, a);
+  else if (a.n < (1 << 18)) hipLaunchKernelGGL((k_p1_pairs<KERNEL, LAYER, 4, 4>), grid(4), block, 0, s, a);
+  else hipLaunchKernelGGL((k_p1_pairs<KERNEL, LAYER, 1, 4>), grid(1), block, 0, s, a);
 }
 
 }  // namespace
