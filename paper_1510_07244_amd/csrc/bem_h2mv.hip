@@ -444,13 +444,21 @@ hipError_t launch_gemv(bool cplx, bool trans, const GemvArgs &a, hipStream_t s) 
   const int64_t mean = std::max<int64_t>((a.out_len + a.ngroups - 1) / a.ngroups, 1);
   const int panel = cplx ? kPanel<true> : kPanel<false>;
   const int64_t want = trans ? (5 * mean / 4 + panel - 1) / panel : (2 * mean + kWave - 1) / kWave;
-  const dim3 grid((unsigned)a.ngroups, (unsigned)std::min<int64_t>(std::max<int64_t>(want, 1), kMaxVec / panel));
-  if (cplx) {
-    if (trans) hipLaunchKernelGGL(k_gemv_trans<true>, grid, dim3(kThreads), 0, s, a);
-    else hipLaunchKernelGGL(k_gemv<true>, grid, dim3(kGemvThreads), 0, s, a);
-  } else {
-    if (trans) hipLaunchKernelGGL(k_gemv_trans<false>, grid, dim3(kThreads), 0, s, a);
-    else hipLaunchKernelGGL(k_gemv<false>, grid, dim3(kGemvThreads), 0, s, a);
+  const unsigned gy = (unsigned)std::min<int64_t>(std::max<int64_t>(want, 1), kMaxVec / panel);
+  // a launch has 2^32 threads along the groups: more of them in turns
+  constexpr int32_t kMost = 1 << 21;
+  for (int32_t g0 = 0; g0 < a.ngroups; g0 += std::min(kMost, a.ngroups - g0)) {
+    GemvArgs t = a;
+    t.ngroups = std::min(kMost, a.ngroups - g0);
+    t.grp_ptr += g0, t.out_ptr += g0;
+    const dim3 grid((unsigned)t.ngroups, gy);
+    if (cplx) {
+      if (trans) hipLaunchKernelGGL(k_gemv_trans<true>, grid, dim3(kThreads), 0, s, t);
+      else hipLaunchKernelGGL(k_gemv<true>, grid, dim3(kGemvThreads), 0, s, t);
+    } else {
+      if (trans) hipLaunchKernelGGL(k_gemv_trans<false>, grid, dim3(kThreads), 0, s, t);
+      else hipLaunchKernelGGL(k_gemv<false>, grid, dim3(kGemvThreads), 0, s, t);
+    }
   }
   return hipGetLastError();
 }
