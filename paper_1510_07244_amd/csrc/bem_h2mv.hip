@@ -190,7 +190,8 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv(const GemvArgs a) {
   GemvGroup gr;
   if (!gemv_group(a, blockIdx.x, &gr)) return;
   const int m = gr.m;
-  for (int r0 = blockIdx.y * kWave; r0 < m; r0 += gridDim.y * kWave) {  // uniform
+  // (a group without outputs takes one turn, in which its blocks are checked)
+  for (int r0 = blockIdx.y * kWave; r0 < max(m, 1); r0 += gridDim.y * kWave) {  // uniform
     const int row = r0 + lane;
     T acc = T::zero();
     int64_t task = 0;  // panels of the group's blocks so far
