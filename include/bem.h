@@ -276,10 +276,14 @@ typedef struct {
                         mixed form); plain coupling lists take
                         bem_assemble_coupling's sub-tile (default: the
                         per-block kernel's) */
-  int32_t tile_cols; /* sub-tile columns, 1..64, of the same lists */
+  int32_t tile_cols; /* sub-tile columns, 1..64, of the same lists;
+                        BEM_EUNSUPPORTED where 48 bytes (mixed form: 32) per
+                        column and rule point, the points rounded up to whole
+                        x_chunks, and the rest of a sub-tile pass 80 KiB */
   int32_t x_chunk;   /* 4, 5, 7, 8 or 9, or 0: reported back (0: a divisor of
                         the rule's points); the kernels choose their register
-                        chunks by the rule alone, entries do not depend on it */
+                        chunks by the rule alone, entries do not depend on it
+                        (the limit of tile_cols does) */
   int32_t autotune;  /* 1: time the candidates of every field left 0 */
   int32_t granularity; /* work item of the queue: 1 whole blocks (each
                           popped block's sub-tiles in turn, like the

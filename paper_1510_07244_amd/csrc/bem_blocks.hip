@@ -88,6 +88,19 @@ size_t block_lds_bytes(int nq_pad, int tr, int tc, bool mixed, bool lists, bool 
   return dbl * 8 + ints * 4 + (lists ? (size_t)2 * (2 * (size_t)tr * tc + blk::kSortPad) : 0);
 }
 
+// The limit of a requested sub-tile shape (bem_tune): not what the kernels take,
+// which may shrink, but fixed, so that a stored configuration is taken or
+// refused alike by every version: 48 bytes (mixed: 32) per column point, the
+// rule's points rounded up to whole x_chunks, 80 bytes per row, 24 per column,
+// the normals, boxes, ids and pair lists.  64 rows fit beside the default
+// columns at every order, so a request of rows alone needs no check.
+size_t requested_lds_bytes(int nq, int x_chunk, int tr, int tc, bool mixed, bool both) {
+  const size_t r = tr, c = tc, np = (size_t)(nq + x_chunk - 1) / x_chunk * x_chunk;
+  const size_t dbl = (mixed ? 4 : 6) * np * c + 10 * r + 3 * np + 3 * c + (both ? 3 * r : 0) +
+                     (mixed ? 6 * r + 9 * c : 0);
+  return dbl * 8 + (4 * r + 4 * c + 36) * 4 + 2 * (2 * r * c + 512);
+}
+
 // Largest sub-tile within the LDS budget.  Near-field sub-tiles carry the
 // pair lists, whose entries pack row and column in 6 bits each (at most
 // 64 x 64); so do mixed-precision coupling sub-tiles (their near-singular

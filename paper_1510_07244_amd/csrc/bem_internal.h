@@ -370,6 +370,8 @@ bool block_tile_shape(int nq_pad, bool mixed, size_t lds_budget, int *tr, int *t
                       size_t *lds_bytes, bool coupling = false, bool both = false);
 size_t block_lds_bytes(int nq_pad, int tr, int tc, bool mixed, bool lists = true,
                        bool both = false);
+// bytes that a requested sub-tile shape is limited by (bem_tune)
+size_t requested_lds_bytes(int nq, int x_chunk, int tr, int tc, bool mixed, bool both);
 // smaller sub-tiles and workgroups per block for a launch of few blocks
 int split_blocks(const BlockArgs &a, bool coupling, bool mixed, bool lists, bool both, int *tc,
                  size_t *lds_bytes);

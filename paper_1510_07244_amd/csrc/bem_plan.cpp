@@ -490,19 +490,11 @@ int bem_plan_batched(bem_ctx *ctx, const bem_op *op, int32_t nbatch, const bem_b
       }
     }
   }
-  // requested shapes are held to the room that 48 bytes per column point (32
-  // in the mixed form) leave, the limit configurations are written against;
-  // the sub-tiles themselves take less
-  bool over = false;
-  if (want.tile_cols && any_lists) {
-    const size_t tr = want.tile_rows ? want.tile_rows : want.autotune ? 32 : 64, tc = want.tile_cols;
-    const size_t np = (p->nq + xc - 1) / xc * xc;
-    const size_t dbl = (p->mixed ? 4 : 6) * np * tc + 10 * tr + 3 * np + 3 * tc + (any_both ? 3 * tr : 0) +
-                       (p->mixed ? 6 * tr + 9 * tc : 0);
-    over = dbl * 8 + (4 * tr + 4 * tc + 36) * 4 + 2 * (2 * tr * tc + 512) > ctx->lds_budget;
-  }
-  if (cands.empty() || over)
-    return bail(fail(ctx, BEM_EUNSUPPORTED, "no sub-tile shape fits the LDS budget"));
+  if (want.tile_cols && any_lists &&
+      requested_lds_bytes(p->nq, xc, want.tile_rows ? want.tile_rows : want.autotune ? 32 : 64, want.tile_cols,
+                          p->mixed, any_both) > ctx->lds_budget)
+    return bail(fail(ctx, BEM_EUNSUPPORTED, "requested tile_cols over the limit within the LDS budget"));
+  if (cands.empty()) return bail(fail(ctx, BEM_EUNSUPPORTED, "no sub-tile shape fits the LDS budget"));
 
   // ---- per-candidate device state
   // queues depend on the sub-tile shapes and granularity, not on the chunk
