@@ -469,8 +469,9 @@ __device__ __forceinline__ void relabel(int i0, int i1, int i2, int j0, int j1, 
 // E1_i = E1_j and g3 = 0) and 3 q for an identical pair (g3 = g4 = 0).  The
 // Laplace kernels' radial sums are moments; the Helmholtz kernels' are power
 // series in theta = kappa |d| whose coefficients hold the rule's own radial
-// nodes (no other quadrature), taken up to theta = 2, where the first term
-// left out is below 1e-17 of the sum; a larger theta sums the radial nodes.
+// nodes (no other quadrature), taken up to theta = 2, where the terms left out
+// are below 3e-17 of the sum and 6e-17 of its real part at every order (vertex
+// pairs; 2e-18 the others); a larger theta sums the radial nodes.
 struct PairGeo {
   double E1i[3], E2i[3], E1j[3], E2j[3], n[3];
   double scale;  // sqrt(g_i) sqrt(g_j) / (4 pi)
