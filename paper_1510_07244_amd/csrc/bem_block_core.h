@@ -49,11 +49,11 @@ enum RowField {
 //   mixed only:    cg[3][TC] = 2 (v0_j - c); rb[6][TR], cb[6][TC] boxes
 //   ints           rid[TR], rv[3][TR], cid[TC], cv[3][TC], count, bad, rcount, pad, per-group counts[16] and
 //                  cursors[16] (classes at 0 .. 3, orders q at 8 + q)
-//   list[TR*TC]    uint16 codes (row | col << 6 | group << 12, kSwapped) of the pairs
+//   list[slots]    uint16 codes (row | col << 6 | group << 12, kSwapped) of the pairs
 //                  left to the FP64 pass (singular; near-singular if mixed),
 //                  from the front; with per-entry orders, the regular pairs
 //                  (group = order) from the back
-//   sorted[TR*TC + kSortPad]  codes grouped (by class or by order), each
+//   sorted[slots + kSortPad]  codes grouped (by class or by order), each
 //                  group padded to a multiple of 64 with kNoPair
 struct Lds {
   double *ys, *rg, *rule, *cn, *cc, *rn, *cg, *rb, *cb;
@@ -64,7 +64,8 @@ struct Lds {
 __host__ __device__ __forceinline__ int ypoint_doubles(bool mixed) { return mixed ? 2 : 4; }
 
 template <bool MIXED>
-__device__ __forceinline__ Lds carve(double *base, int nqp, int TR, int TC, bool both = false) {
+__device__ __forceinline__ Lds carve(double *base, const BlockArgs &a, bool both = false) {
+  const int nqp = a.nq_pad, TR = a.tr, TC = a.tc;
   Lds l;
   l.ys = base;
   l.rg = l.ys + ypoint_doubles(MIXED) * nqp * TC;
@@ -86,7 +87,7 @@ __device__ __forceinline__ Lds carve(double *base, int nqp, int TR, int TC, bool
   l.ccount = l.rcount + 2;
   l.cursor = l.ccount + 16;
   l.list = reinterpret_cast<uint16_t *>(l.cursor + 16);
-  l.sorted = l.list + TR * TC;
+  l.sorted = l.list + a.slots;
   return l;
 }
 

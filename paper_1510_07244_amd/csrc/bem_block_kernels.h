@@ -392,9 +392,24 @@ __device__ __forceinline__ void singular_chunk_both(const BlockArgs &a, const Ld
   }
 }
 
+// Near-singular pair of the mixed form: bounding boxes closer than ratio * the
+// larger box diagonal.  row(m), col(m): component m of the boxes (lower corner,
+// upper corner).
+template <class R, class C>
+__device__ __forceinline__ bool near_pair(double ratio, R &&row, C &&col) {
+  double gap2 = 0.0, di = 0.0, dj = 0.0;
+  for (int m = 0; m < 3; ++m) {
+    const double rlo = row(m), rhi = row(3 + m), clo = col(m), chi = col(3 + m);
+    const double g = fmax(0.0, fmax(clo - rhi, rlo - chi));
+    gap2 = fma(g, g, gap2);
+    di = fma(rhi - rlo, rhi - rlo, di);
+    dj = fma(chi - clo, chi - clo, dj);
+  }
+  return gap2 < ratio * ratio * fmax(di, dj);
+}
+
 // Whether entry (rl, cl) of the staged sub-tile goes to the FP64 pass:
-// a common vertex (cls > 0), or in the mixed form a near-singular pair
-// (bounding boxes closer than ratio * the larger box diagonal).
+// a common vertex (cls > 0), or in the mixed form a near-singular pair.
 template <bool MIXED>
 __device__ __forceinline__ bool fp64_pair(const Lds &l, int TR, int TC, int rl, int cl,
                                           double ratio, int *cls_out) {
@@ -403,20 +418,40 @@ __device__ __forceinline__ bool fp64_pair(const Lds &l, int TR, int TC, int rl, 
   *cls_out = cls;
   bool fp64 = cls != 0;
   if constexpr (MIXED) {
-    if (!fp64 && ratio > 0.0) {
-      double gap2 = 0.0, di = 0.0, dj = 0.0;
-      for (int m = 0; m < 3; ++m) {
-        const double rlo = l.rb[m * TR + rl], rhi = l.rb[(3 + m) * TR + rl];
-        const double clo = l.cb[m * TC + cl], chi = l.cb[(3 + m) * TC + cl];
-        const double g = fmax(0.0, fmax(clo - rhi, rlo - chi));
-        gap2 = fma(g, g, gap2);
-        di = fma(rhi - rlo, rhi - rlo, di);
-        dj = fma(chi - clo, chi - clo, dj);
-      }
-      fp64 = gap2 < ratio * ratio * fmax(di, dj);
-    }
+    if (!fp64 && ratio > 0.0)
+      fp64 = near_pair(ratio, [&](int m) { return l.rb[m * TR + rl]; }, [&](int m) { return l.cb[m * TC + cl]; });
   }
   return fp64;
+}
+
+// Pairs that the full sub-tile around the staged one, a.wide columns, lists in a
+// mirrored list (edge-adjacent ones twice).  Uniform; with barriers.
+template <bool MIXED>
+__device__ int full_count(const BlockArgs &a, const Lds &l, const BlockHdr &h, int64_t r0, int64_t c0, int tr) {
+  const int tid = thread_id(), TR = a.tr;
+  const int64_t w0 = c0 - c0 % a.wide;
+  const int wc = (int)min((int64_t)a.wide, h.nc - w0);
+  __syncthreads();
+  if (tid == 0) *l.bad = 0;
+  __syncthreads();
+  for (int e = tid; e < tr * wc; e += kThreads) {
+    const int rl = e % tr;
+    const int64_t c = w0 + e / tr;
+    if (h.diag && r0 + rl < c) continue;
+    const int id = a.col_idx[h.cp0 + c];
+    if (id < 0 || id >= a.nt) continue;  // reported by its own sub-tile
+    const int32_t *v = a.tri + 3 * (int64_t)id;
+    const int cls = shared_vertex_count(l.rv[rl], l.rv[TR + rl], l.rv[2 * TR + rl], v[0], v[1], v[2]);
+    int n = cls == 0 ? 0 : cls == CLS_EDGE ? 2 : 1;
+    if constexpr (MIXED) {
+      if (cls == 0 && a.near_ratio > 0.0)
+        n = near_pair(a.near_ratio, [&](int m) { return l.rb[m * TR + rl]; },
+                      [&](int m) { return a.geo[(G_LOX + m) * a.ldg + id]; });
+    }
+    if (n) atomicAdd(l.bad, n);
+  }
+  __syncthreads();
+  return *l.bad;
 }
 
 // Entry e of the lower triangle (row >= column) of an n x n tile, columns
@@ -483,7 +518,7 @@ __device__ void subtile(const BlockArgs &a, const Lds &l, const BlockHdr &h, int
       const uint16_t code = (uint16_t)(rl | (cl << 6) | (cls << 12));
       const int n = twice ? 2 : 1;
       const int slot = atomicAdd(l.count, n);
-      if (slot + n <= TR * TC) {  // else the sub-tile fails below
+      if (slot + n <= a.slots) {  // else the sub-tile fails below
         l.list[slot] = code;
         if (twice) l.list[slot + 1] = code | kSwapped;
       }
@@ -491,8 +526,10 @@ __device__ void subtile(const BlockArgs &a, const Lds &l, const BlockHdr &h, int
     }
   }
   __syncthreads();
-  if (*l.count > TR * TC) {  // uniform: more listed pairs than list slots
-    if (tid == 0) atomicOr(a.flags, FLAG_LIST);
+  // more listed pairs than entries (a mirrored list): too many if those of the
+  // full sub-tile are
+  if (*l.count > TR * TC && (*l.count > a.slots || full_count<MIXED>(a, l, h, r0, c0, tr) > TR * a.wide)) {
+    if (tid == 0) atomicOr(a.flags, FLAG_LIST);  // uniform
     return;
   }
   const Groups gr = group_listed(l);
@@ -562,7 +599,7 @@ __device__ void subtile_learned(const BlockArgs &a, const OrderRules &o, const L
   const int TR = a.tr, TC = a.tc;
   const int64_t nr = h.nr, off = h.off;
   const int tr = (int)min((int64_t)TR, h.nr - r0), tc = (int)min((int64_t)TC, h.nc - c0);
-  const int cap = TR * TC;
+  const int cap = a.slots;
   if (!stage_tile<false>(a, l, h, r0, c0, tr, tc)) return;
   stage_triangles(a, l, h, tc);
   // classify: singular pairs to the front of the list, regular ones (with
@@ -639,7 +676,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_blocks_learned(const BlockArgs 
   extern __shared__ __align__(16) double lds_raw[];  // 16-byte aligned: ds_read_b128 of points
   BlockHdr h;
   if (!block_header(a, blockIdx.x, &h) || h.nr == 0 || h.nc == 0) return;
-  const Lds l = carve<false>(lds_raw, a.nq_pad, a.tr, a.tc);
+  const Lds l = carve<false>(lds_raw, a);
   h.brief = block_is_brief<KERNEL>(a, l, h);
   unsigned turn = blockIdx.y;  // as k_blocks
   for (int64_t r0 = 0; r0 < h.nr; r0 += a.tr)
@@ -654,7 +691,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_blocks(const BlockArgs a, const
   extern __shared__ __align__(16) double lds_raw[];  // 16-byte aligned: ds_read_b128 of points
   BlockHdr h;
   if (!block_header(a, blockIdx.x, &h) || h.nr == 0 || h.nc == 0) return;
-  const Lds l = carve<MIXED>(lds_raw, a.nq_pad, a.tr, a.tc, LAYER == kBoth);
+  const Lds l = carve<MIXED>(lds_raw, a, LAYER == kBoth);
   h.brief = RULE < kSeven && block_is_brief<KERNEL>(a, l, h);
   load_rule(a, l);
   // the block's sub-tiles, dealt to gridDim.y workgroups
@@ -709,7 +746,7 @@ __device__ __forceinline__ void persistent_item(const BlockArgs *__restrict__ ba
     if (thread_id() == 0) atomicOr(a.flags, FLAG_EINVAL);
     return;
   }
-  const Lds l = carve<MIXED>(lds_raw, a.nq_pad, a.tr, a.tc, LAYER == kBoth);
+  const Lds l = carve<MIXED>(lds_raw, a, LAYER == kBoth);
   const int shape = a.tr | (a.tc << 10);
   if (shape != *carved) {
     load_rule(a, l);

@@ -80,12 +80,13 @@ int rule_chunk(int nq, int kernel) {
 
 // LDS of a sub-tile; without the pair lists (coupling launches: every pair is
 // regular, phase C only flags, and the lists sit past the allocation unread).
-size_t block_lds_bytes(int nq_pad, int tr, int tc, bool mixed, bool lists, bool both) {
+// slots: of the list, 0: one per pair.
+size_t block_lds_bytes(int nq_pad, int tr, int tc, bool mixed, bool lists, bool both, int slots) {
   size_t dbl = (size_t)blk::ypoint_doubles(mixed) * nq_pad * tc + blk::ROW_NF * (size_t)tr +
                3 * (size_t)nq_pad + 7 * (size_t)tc + (both ? 3 * (size_t)tr : 0);
   if (mixed) dbl += 3 * (size_t)tc + 6 * (size_t)tr + 6 * (size_t)tc;
   const size_t ints = (size_t)4 * tr + 4 * (size_t)tc + 36;
-  return dbl * 8 + ints * 4 + (lists ? (size_t)2 * (2 * (size_t)tr * tc + blk::kSortPad) : 0);
+  return dbl * 8 + ints * 4 + (lists ? 2 * (2 * (size_t)(slots ? slots : tr * tc) + blk::kSortPad) : 0);
 }
 
 // The limit of a requested sub-tile shape (bem_tune): not what the kernels take,
@@ -151,21 +152,28 @@ bool block_tile_shape(int nq_pad, bool mixed, size_t lds_budget, int *tr, int *t
 // Laplace blocks of 64 x 64, seven points: 70 us whole, 43 aiming at 128, 29 at
 // 256, 26 at 512); up to 767 blocks are dealt out (both layers, 556 blocks: 386
 // -> 312; 674 blocks 377 -> 324); 1041 lose by it (1236 -> 1315).
-int split_blocks(const BlockArgs &a, bool coupling, bool mixed, bool lists, bool both, int *tc,
-                 size_t *lds_bytes) {
+//
+// A mirrored list counts edge-adjacent pairs twice and is refused where a full
+// sub-tile's pairs pass its entries.  Narrowed ones keep that limit and have the
+// slots for it: their own pairs may pass their entries where the full one's do not.
+void split_blocks(BlockArgs *a, bool coupling, bool mixed, bool lists, bool both, size_t *lds_bytes) {
   constexpr int64_t kDealt = 768, kDealtCoupling = 1024, kNarrow = 320, kMost = 4096;
-  if (a.nblocks <= 0 || a.nblocks >= (coupling ? kDealtCoupling : kDealt)) return 1;
-  const int64_t mr = std::max<int64_t>(a.row_len / a.nblocks, 1);
-  const int64_t mc = std::max<int64_t>(a.col_len / a.nblocks, 1);
-  const int64_t down = (mr + a.tr - 1) / a.tr;
-  const bool narrow = a.nblocks < (coupling ? kDealt : kNarrow);
+  a->wide = a->tc;
+  a->slots = a->tr * a->tc;
+  a->split = 1;
+  if (a->nblocks <= 0 || a->nblocks >= (coupling ? kDealtCoupling : kDealt)) return;
+  const int64_t mr = std::max<int64_t>(a->row_len / a->nblocks, 1);
+  const int64_t mc = std::max<int64_t>(a->col_len / a->nblocks, 1);
+  const int64_t down = (mr + a->tr - 1) / a->tr;
+  const bool narrow = a->nblocks < (coupling ? kDealt : kNarrow);
   const int64_t tiles = !narrow ? 0 : coupling ? 1536 : 512;
-  int c = *tc;
-  while (c > 8 && a.nblocks * down * ((mc + c - 1) / c) < tiles) c = std::max(8, c / 2);
-  *tc = c;
-  *lds_bytes = block_lds_bytes(a.nq_pad, a.tr, c, mixed, lists, both);
+  int c = a->tc;
+  while (c > 8 && a->nblocks * down * ((mc + c - 1) / c) < tiles) c = std::max(8, c / 2);
+  a->tc = c;
+  a->slots = std::min(2 * a->tr * c, a->tr * a->wide);
+  *lds_bytes = block_lds_bytes(a->nq_pad, a->tr, c, mixed, lists, both, a->slots);
   const int64_t turns = coupling && narrow ? 1 : 2;
-  return (int)std::min<int64_t>(turns * down * ((mc + c - 1) / c), kMost / a.nblocks);
+  a->split = (int)std::min<int64_t>(turns * down * ((mc + c - 1) / c), kMost / a->nblocks);
 }
 
 hipError_t launch_blocks(int kernel, int layer, int rule, bool coupling, bool mixed,

@@ -235,7 +235,7 @@ int assemble_blocks(bem_ctx *ctx, const bem_mesh *mesh, const bem_op *op,
   if (!bem::block_tile_shape(a.nq_pad, mixed, ctx->lds_budget, &a.tr, &a.tc, &lds, coupling,
                              both))
     return fail(ctx, BEM_EUNSUPPORTED, "quadrature order too high for the LDS budget");
-  a.split = bem::split_blocks(a, coupling, mixed, !coupling || mixed, both, &a.tc, &lds);
+  bem::split_blocks(&a, coupling, mixed, !coupling || mixed, both, &lds);
   a.near_ratio = op->near_singular_ratio;
   a.ss = bem::ss_args(*rules);
   a.kappa = op->kernel == BEM_HELMHOLTZ ? op->kappa : 0.0;

@@ -131,6 +131,8 @@ struct BlockArgs {
   const double *sums;  // DevRules::sums, mixed form sums32 (float)
   int32_t nq, nq_pad;
   int32_t tr, tc;      // sub-tile rows / columns
+  int32_t wide, slots; // columns of a full sub-tile, which may list tr * wide
+                       // pairs; list slots of this one (at least tr * tc)
   int32_t split;       // workgroups per block (per-block kernels)
   int32_t *brief;      // per block: whether its Helmholtz phases are short
                        // (launch_begin), null: every work item finds out
@@ -369,12 +371,12 @@ hipError_t launch_entries(int kernel, int layer, bool mixed, const EntryArgs &a,
 bool block_tile_shape(int nq_pad, bool mixed, size_t lds_budget, int *tr, int *tc,
                       size_t *lds_bytes, bool coupling = false, bool both = false);
 size_t block_lds_bytes(int nq_pad, int tr, int tc, bool mixed, bool lists = true,
-                       bool both = false);
+                       bool both = false, int slots = 0);
 // bytes that a requested sub-tile shape is limited by (bem_tune)
 size_t requested_lds_bytes(int nq, int x_chunk, int tr, int tc, bool mixed, bool both);
-// smaller sub-tiles and workgroups per block for a launch of few blocks
-int split_blocks(const BlockArgs &a, bool coupling, bool mixed, bool lists, bool both, int *tc,
-                 size_t *lds_bytes);
+// smaller sub-tiles (a->tc, slots) and workgroups per block (a->split) for a
+// launch of few blocks
+void split_blocks(BlockArgs *a, bool coupling, bool mixed, bool lists, bool both, size_t *lds_bytes);
 int rule_chunk(int nq, int kernel);
 // kernel variant of a rule (regular_rule, order, points) and the room of its
 // column points in LDS

@@ -296,7 +296,7 @@ int bem_assemble_nearfield_learned(bem_ctx *ctx, const bem_mesh *mesh, const bem
   // sub-tiles than blocks (Helmholtz, order 6, 64 or 32 columns: 702 blocks 1.33 and
   // 1.10 ms, 1041 blocks 1.80 and 2.01)
   if (a.nblocks < 768 && a.tc > 32) a.tc = 32;
-  a.split = split_blocks(a, false, false, true, false, &a.tc, &lds);
+  split_blocks(&a, false, false, true, false, &lds);
   a.ss = ss_args(*plain);
   a.kappa = op->kernel == BEM_HELMHOLTZ ? op->kappa : 0.0;
   a.flags = ctx->flags;

@@ -554,7 +554,8 @@ int bem_plan_batched(bem_ctx *ctx, const bem_op *op, int32_t nbatch, const bem_b
       a.sums = p->mixed ? rules->sums32 : rules->sums;
       a.nq_pad = nqp;
       a.tr = sh[k].first;
-      a.tc = sh[k].second;
+      a.tc = a.wide = sh[k].second;
+      a.slots = a.tr * a.tc;
       a.ss = ss_args(*rules);
       a.kappa = op->kernel == BEM_HELMHOLTZ ? op->kappa : 0.0;
       a.near_ratio = op->near_singular_ratio;
