@@ -39,7 +39,7 @@ enum RowField {
 //                  Read as 16-byte words (broadcast in a wave).  The general sums
 //                  and the learned form keep the column triangles instead,
 //                  [kColumnFields][TC] doubles, the general sums then 4 |y_b -
-//                  v0_j|^2 of the points, [nq][TC] doubles (mixed: floats)
+//                  c_j|^2 of the points, [nq][TC] doubles (mixed: floats)
 //   rg[ROW_NF][TR] row geometry
 //   rule[3][nqp]   s, t, w of the triangle rule
 //   cn[4][TC]      column normals n_j, <Y, n_j> (one value on the triangle's
@@ -202,7 +202,8 @@ struct TablePtr {
 };
 
 // Points of a column triangle for the general sums: the rule's coordinates
-// and weight (general_table, scalar loads) and 4 |y - v0|^2 from LDS.
+// from the centroid and weight (general_table, scalar loads) and 4 |y - c|^2
+// from LDS.
 template <class T>
 struct PointsOfTriangle {
   const T *g;
@@ -210,7 +211,7 @@ struct PointsOfTriangle {
   typename TablePtr<T>::type t;
   int n;
   struct P { T g, u, v, w; };
-  __device__ __forceinline__ P get(int b) const { return {g[b * stride], t[b], t[n + b], t[2 * n + b]}; }
+  __device__ __forceinline__ P get(int b) const { return {g[b * stride], t[4 * n + b], t[5 * n + b], t[2 * n + b]}; }
 };
 
 // Two points per step, the next one's LDS reads issued before the current
@@ -382,13 +383,13 @@ struct EntrySums {
 // Offsets in the table of a Duffy rule of order Q (duffy_table): per xi
 // (xi, xi^2, w_xi xi, w_xi xi^2); the half-width nodes delta > 0 of eta =
 // 1/2 +- delta, their squares, the eta weights w (pairs, then the centre of an
-// odd order) and w delta of the pairs; and for every (xi, pair) xi delta and
-// (xi, eta) the full weight.
+// odd order) and w delta of the pairs; for every (xi, pair) xi delta and
+// (xi, eta) the full weight; and per xi c = xi - 2/3 and c^2.
 template <int Q>
 struct DuffyAt {
   static constexpr int H = Q / 2, HC = (Q + 1) / 2;
   static constexpr int J = 0, D = 4 * Q, D2 = D + H, W = D2 + H, WD = W + HC, XD = WD + H,
-                       WF = XD + Q * H;
+                       WF = XD + Q * H, CC = WF + Q * HC;
 };
 
 // Sums over the point pairs of one regular entry, Duffy rule of order Q on
@@ -398,7 +399,10 @@ struct DuffyAt {
 // operations per column point, then per xi two or three and per symmetric eta
 // pair 1/2 +- delta three (2 to 2.4 per point pair, from 4 for coordinates of
 // every x-point); equal weights of a pair are applied once, to its sum.  The
-// rule's constants are wave-uniform (scalar registers).
+// rule's constants are wave-uniform (scalar registers).  FP32 takes the
+// polynomial about the row's centroid, where its terms are a quarter as large
+// (largest error of 64 x 64 sheets 0.03 triangle sizes apart, order 4: 1.4e-5 about
+// the vertex, 1e-6 about the centroid, 5e-6 with plain coordinates).
 // Every xi unrolled, products of constants and the double layer's point weights
 // w <X - Y, n_j> (w (n0 + xi na +- xi delta nb)) kept: up to 72 of 229 registers
 // for Laplace, no spills (a loop over xi instead, order 5 / 6: coupling of 6272
@@ -430,21 +434,34 @@ __device__ __forceinline__ void duffy_sums(const EntryGeo &g, const double *tabl
   typedef DuffyAt<Q> C;
   constexpr int H = C::H, HC = C::HC;
   constexpr bool ODD = Q & 1, HELM = KERNEL == BEM_HELMHOLTZ;
-  constexpr bool FP64 = std::is_same<T, double>::value;
+  constexpr bool FP64 = std::is_same<T, double>::value, CEN = !FP64;
   constexpr bool ROLL = HELM && (FP64 ? LAYER == BEM_SLP && Q >= 5 : LAYER != BEM_DLP || Q >= 5);
   constexpr bool LIN = ROLL && LAYER == kBoth;    // double-layer weights in three sums
   constexpr bool FLY = ROLL && LAYER == BEM_DLP;  // formed at every point pair
   const typename TablePtr<T>::type c = TablePtr<T>::of(table);
   // short phases: coordinates scaled by f so that kappa r needs no factor
   const double ka = fabs(kappa), f = HELM && SHORT ? ka * M::kScale : 1.0;
-  const T V0 = (T)(f * g.V[0]), V1 = (T)(f * g.V[1]), V2 = (T)(f * g.V[2]);
+  // FP32: from the centroid V + A / 3 (xi = 2/3, eta = 1/2) instead of V
+  const double third = CEN ? 1.0 / 3.0 : 0.0;
+  const T V0 = (T)(f * fma(third, g.A[0], g.V[0])), V1 = (T)(f * fma(third, g.A[1], g.V[1])),
+          V2 = (T)(f * fma(third, g.A[2], g.V[2]));
   const T A0 = (T)(f * g.A[0]), A1 = (T)(f * g.A[1]), A2 = (T)(f * g.A[2]);
   const T B0 = (T)(f * g.B[0]), B1 = (T)(f * g.B[1]), B2 = (T)(f * g.B[2]);
   const T c1 = (T)(f * f * g.c1), k0 = (T)(f * f * g.k0), a22 = (T)(f * f * g.a22), mf = (T)-f;
-  T K[HC];
+  // terms in xi alone: xi^2 K, from the centroid c^2 k0 + xi^2 K (unrolled: of
+  // every point, kept)
+  T K[HC], KC[CEN && !ROLL ? Q : 1][HC];
 #pragma unroll
-  for (int k = 0; k < H; ++k) K[k] = M::mad(c[C::D2 + k], a22, k0);
-  if (ODD) K[HC - 1] = k0;
+  for (int k = 0; k < HC; ++k) {
+    const T base = CEN ? (T)0 : k0;
+    K[k] = k < H ? M::mad(c[C::D2 + k], a22, base) : base;
+  }
+  if constexpr (CEN && !ROLL) {
+#pragma unroll
+    for (int j = 0; j < Q; ++j)
+#pragma unroll
+      for (int k = 0; k < HC; ++k) KC[j][k] = M::mad(c[4 * j + 1], K[k], c[C::CC + 2 * j + 1] * k0);
+  }
   T WN[ROLL ? 1 : Q][Q], n0 = 0, na = 0, nb = 0;
   if constexpr (LAYER != BEM_SLP) {
     n0 = (T)(fma(g.V[0], g.n[0], fma(g.V[1], g.n[1], g.V[2] * g.n[2])) - g.yn);
@@ -500,26 +517,32 @@ __device__ __forceinline__ void duffy_sums(const EntryGeo &g, const double *tabl
     if constexpr (HELM && SHORT) {
       // the row centroid (xi = 2/3, eta = 1/2); only the reference of the
       // phases, so the hardware estimate serves
-      const T q0 = M::mad((T)(4.0 / 9.0), k0, M::mad((T)(2.0 / 3.0), R, U));
+      const T q0 = CEN ? U : M::mad((T)(4.0 / 9.0), k0, M::mad((T)(2.0 / 3.0), R, U));
       kr0 = M::ref(q0);
       M::sincos_short(kr0 - kr00, &sy, &cy);
     }
     PointSums<KERNEL, LAYER, T> ps;
     T txr = 0, txi = 0, tbr = 0, tbi = 0;  // LIN: xi and xi delta moments
-    // the q points of one xi (x), weight wx; j: its index if unrolled
-    auto row = [&](int j, T x, T x2, T wx, T wxx) {
-      const T E = M::mad(x, R, U);
-      T O = M::mad(x, c1, S);
+    // the q points of one xi (x, from the centroid xc), weight wx; j: its index
+    // if unrolled
+    auto row = [&](int j, T x, T x2, T wx, T wxx, T xc, T xc2) {
+      T E = M::mad(xc, R, U);
+      if (CEN && ROLL) E = M::mad(xc2, k0, E);
+      T O = M::mad(xc, c1, S);
       if (ROLL) O *= x;
+      auto middle = [&](int k) -> T {
+        if constexpr (CEN && !ROLL) return E + KC[j][k];
+        else return CEN && k >= H ? E : M::mad(x2, K[k], E);
+      };
       T s[Q], h[Q];
 #pragma unroll
       for (int k = 0; k < H; ++k) {
-        const T mid = M::mad(x2, K[k], E);
+        const T mid = middle(k);
         const T dl = ROLL ? c[C::D + k] : c[C::XD + j * H + k];
         s[2 * k] = M::mad(dl, O, mid);
         s[2 * k + 1] = M::mad(-dl, O, mid);
       }
-      if (ODD) s[Q - 1] = M::mad(x2, K[HC - 1], E);
+      if (ODD) s[Q - 1] = middle(HC - 1);
 #pragma unroll
       for (int k = 0; k < Q; ++k) h[k] = M::rsq(s[k]);
       // weighted sums over eta: into the point's sums (full weights) or first
@@ -604,18 +627,20 @@ __device__ __forceinline__ void duffy_sums(const EntryGeo &g, const double *tabl
     };
     if constexpr (ROLL) {
       // the next xi's constants are read before this one's arithmetic
-      T x = c[0], x2 = c[1], wx = c[2], wxx = c[3];
+      T x = c[0], x2 = c[1], wx = c[2], wxx = c[3], xc = x, xc2 = x2;
+      if (CEN) xc = c[C::CC], xc2 = c[C::CC + 1];
 #pragma unroll 1
       for (int j = 0; j < Q; ++j) {
-        const int p = 4 * (j + 1 < Q ? j + 1 : j);
+        const int n = j + 1 < Q ? j + 1 : j, p = 4 * n;
         const T nx = c[p], nx2 = c[p + 1], nwx = c[p + 2], nwxx = c[p + 3];
-        row(0, x, x2, wx, wxx);
-        x = nx, x2 = nx2, wx = nwx, wxx = nwxx;
+        const T nc = CEN ? c[C::CC + 2 * n] : nx, nc2 = CEN ? c[C::CC + 2 * n + 1] : nx2;
+        row(0, x, x2, wx, wxx, xc, xc2);
+        x = nx, x2 = nx2, wx = nwx, wxx = nwxx, xc = nc, xc2 = nc2;
       }
     } else {
 #pragma unroll
       for (int j = 0; j < Q; ++j) {
-        row(j, c[4 * j], c[4 * j + 1], (T)0, (T)0);
+        row(j, c[4 * j], c[4 * j + 1], (T)0, (T)0, c[CEN ? C::CC + 2 * j : 4 * j], (T)0);
         // one xi's chains at a time: scheduled across, they spill
         if constexpr (HELM) __builtin_amdgcn_sched_barrier(0);
       }
@@ -633,9 +658,10 @@ __device__ __forceinline__ void duffy_sums(const EntryGeo &g, const double *tabl
 }
 
 // The same for any triangle rule (general_table, in T and in FP64), x-points in register chunks
-// of XC (zero weights and the last point repeated past the end).  With X0 = 2
-// (v0_i - v0_j), x = v0_i + (s/2) A + (e/2) B and E = 2 e_j the squared distance
-// is a polynomial of the rule coordinates of both triangles,
+// of XC (zero weights and the last point repeated past the end).  With X0 twice
+// the difference of the centroids, x = c_i + (s/2) A + (e/2) B, E = 2 e_j and s, u,
+// v counted from the centroids the squared distance is a polynomial of the rule
+// coordinates of both triangles,
 //   4 |x - y|^2 = |X0|^2 + s <X0, A> + e <X0, B> + s^2 k0 + s e c1 + e^2 a22
 //     - u <2 X0 + s A + e B, E1> - v <2 X0 + s A + e B, E2> + |u E1 + v E2|^2:
 // nine coefficients of the pair, nine operations per x-point for its three
@@ -661,15 +687,15 @@ __device__ __forceinline__ void general_sums(const EntryGeo &g, const double *co
   double c0 = 0, n0 = 0, ns = 0, nt = 0, m0 = 0, m1 = 0, m2 = 0;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    // relative to the column triangle's first vertex (mixed: already)
-    const double x = std::is_same<T, double>::value ? g.V[k] - col[k * TC] : g.V[k];
+    const double x = fma(1.0 / 3.0, g.A[k], g.V[k]) - g.cen[k];
     const double f1 = col[(3 + k) * TC], f2 = col[(6 + k) * TC];
     X[k] = (T)x, A[k] = (T)g.A[k], B[k] = (T)g.B[k], E1[k] = (T)f1, E2[k] = (T)f2;
     c0 = fma(x, x, c0);  // its rounding is in every point pair: in FP64
     if constexpr (LAYER != BEM_SLP)
-      n0 = fma(x, g.n[k], n0), ns = fma(fma(-0.25, g.B[k], 0.5 * g.A[k]), g.n[k], ns), nt = fma(0.5 * g.B[k], g.n[k], nt);
+      n0 = fma(g.V[k], g.n[k], n0), ns = fma(fma(-0.25, g.B[k], 0.5 * g.A[k]), g.n[k], ns), nt = fma(0.5 * g.B[k], g.n[k], nt);
     if constexpr (LAYER == kBoth) m0 = fma(-x, g.m[k], m0), m1 = fma(f1, g.m[k], m1), m2 = fma(f2, g.m[k], m2);
   }
+  n0 -= g.yn;
   const T C0 = (T)c0, K0 = (T)g.k0, C1 = (T)g.c1, A22 = (T)g.a22;
   const T ra = dot(X, A), rb = dot(X, B);
   const T p0 = (T)-2 * dot(X, E1), pa = -dot(A, E1), pb = -dot(B, E1);
@@ -684,8 +710,8 @@ __device__ __forceinline__ void general_sums(const EntryGeo &g, const double *co
 #pragma unroll
     for (int a = 0; a < XC; ++a) {
       const int k = min(ch + a, nq - 1);
-      const T s = c[k], e = c[3 * nq + k];
-      r[a] = M::mad(c[4 * nq + k], K0, M::mad(c[5 * nq + k], C1, M::mad(c[6 * nq + k], A22, M::mad(s, ra, M::mad(e, rb, C0)))));
+      const T s = c[4 * nq + k], e = c[3 * nq + k];
+      r[a] = M::mad(c[6 * nq + k], K0, M::mad(c[7 * nq + k], C1, M::mad(c[8 * nq + k], A22, M::mad(s, ra, M::mad(e, rb, C0)))));
       p[a] = M::mad(s, pa, M::mad(e, pb, p0));
       q[a] = M::mad(s, qa, M::mad(e, qb, q0));
       W[a] = ch + a < nq ? c[2 * nq + k] : (T)0;
@@ -725,7 +751,9 @@ __device__ __forceinline__ void seven_sums(const EntryGeo &g, const double *tabl
   constexpr int XC = 7;
   const typename TablePtr<T>::type c = TablePtr<T>::of(table);
   const uniform_ptr d = (uniform_ptr)table64;
-  const T V0 = (T)g.V[0], V1 = (T)g.V[1], V2 = (T)g.V[2];
+  // from the row's centroid
+  const T V0 = (T)fma(1.0 / 3.0, g.A[0], g.V[0]), V1 = (T)fma(1.0 / 3.0, g.A[1], g.V[1]),
+          V2 = (T)fma(1.0 / 3.0, g.A[2], g.V[2]);
   const T A0 = (T)g.A[0], A1 = (T)g.A[1], A2 = (T)g.A[2];
   const T B0 = (T)g.B[0], B1 = (T)g.B[1], B2 = (T)g.B[2];
   T m0 = 0, m1 = 0, m2 = 0;
@@ -741,7 +769,7 @@ __device__ __forceinline__ void seven_sums(const EntryGeo &g, const double *tabl
   T q[XC], WN[XC];
 #pragma unroll
   for (int a = 0; a < XC; ++a) {
-    q[a] = (T)fma(d[4 * XC + a], g.k0, fma(d[5 * XC + a], g.c1, d[6 * XC + a] * g.a22));
+    q[a] = (T)fma(d[6 * XC + a], g.k0, fma(d[7 * XC + a], g.c1, d[8 * XC + a] * g.a22));
     if constexpr (LAYER != BEM_SLP) WN[a] = (T)(d[2 * XC + a] * fma(d[a], ns, fma(d[XC + a], nt, n0)));
   }
   EntrySums<KERNEL, LAYER, false, T> sum;
@@ -754,7 +782,7 @@ __device__ __forceinline__ void seven_sums(const EntryGeo &g, const double *tabl
     const T S = M::mad(D0, B0, M::mad(D1, B1, D2 * B2));
     T sq[XC], h[XC];
 #pragma unroll
-    for (int a = 0; a < XC; ++a) sq[a] = M::mad(c[3 * XC + a], S, M::mad(c[a], R, U + q[a]));
+    for (int a = 0; a < XC; ++a) sq[a] = M::mad(c[3 * XC + a], S, M::mad(c[4 * XC + a], R, U + q[a]));
 #pragma unroll
     for (int a = 0; a < XC; ++a) h[a] = M::rsq(sq[a]);
     PointSums<KERNEL, LAYER, T> ps;

@@ -204,18 +204,20 @@ __device__ __forceinline__ void stage_triangles(const BlockArgs &a, const Lds &l
 }
 
 // Phase B: what the regular sums keep of the columns, then a barrier.
-// Rules with kernels of their own: the column points of the rule in l.rule.  General rules: the triangles, and 4 |y - v0|^2 of every point.
+// Rules with kernels of their own: the column points of the rule in l.rule.  General rules: the triangles, and 4 |y - c|^2 of every point.
 template <int RULE, bool MIXED>
 __device__ void stage_columns(const BlockArgs &a, const Lds &l, const BlockHdr &h, int tc) {
   const int TC = a.tc, nqp = a.nq_pad;
   const int64_t L = a.ldg;
   const double cx = h.cx, cy = h.cy, cz = h.cz;
-  constexpr bool LOCAL = MIXED || RULE >= kRule4;  // relative to the triangle's first vertex
+  // relative to the triangle's first vertex, resp. centroid
+  constexpr bool LOCAL = MIXED || RULE >= kRule4;
+  constexpr double s0 = RULE >= kRule4 ? 2.0 / 3.0 : 0.0, t0 = 0.5 * s0;
   if constexpr (RULE >= kRule4) stage_triangles(a, l, h, tc);
   for (int k = thread_id(); k < tc * a.nq; k += kThreads) {
     const int cl = k % tc, q = k / tc;
     const int id = l.cid[cl];
-    const double s = l.rule[q], t = l.rule[nqp + q];
+    const double s = l.rule[q] - s0, t = l.rule[nqp + q] - t0;
     const double P0 = 2.0 * fma(s, a.geo[G_E1X * L + id], fma(t, a.geo[G_E2X * L + id], LOCAL ? 0.0 : a.geo[G_V0X * L + id] - cx));
     const double P1 = 2.0 * fma(s, a.geo[G_E1Y * L + id], fma(t, a.geo[G_E2Y * L + id], LOCAL ? 0.0 : a.geo[G_V0Y * L + id] - cy));
     const double P2 = 2.0 * fma(s, a.geo[G_E1Z * L + id], fma(t, a.geo[G_E2Z * L + id], LOCAL ? 0.0 : a.geo[G_V0Z * L + id] - cz));

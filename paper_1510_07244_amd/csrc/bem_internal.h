@@ -27,7 +27,8 @@ struct TriRule {
 TriRule triangle_rule(int rule, int q);
 // Constants of the Duffy rule of order q in the block kernels' layout (DuffyAt).
 std::vector<double> duffy_table(int q);
-// Constants of any other rule: s, t, w, e = t - s / 2, s^2, s e, e^2 [7][points].
+// Constants of any other rule, with s' = s - 2/3 and t' = t - 1/3 from the
+// centroid: s, t, w, e = t - s / 2, s', t', s'^2, s' e, e^2 [9][points].
 std::vector<double> general_table(const TriRule &r);
 
 // Sauter-Schwab rule of one singular class, factored as (x^, y^) = xi g(eta):

@@ -97,16 +97,20 @@ std::vector<double> duffy_table(int q) {
     for (int k = 0; k < H; ++k) t.push_back(x[j] * delta(k));
   for (int j = 0; j < q; ++j)
     for (int k = 0; k < HC; ++k) t.push_back(w[j] * x[j] * w[k]);
+  for (int j = 0; j < q; ++j) {
+    const double c = x[j] - 2.0 / 3.0;
+    t.insert(t.end(), {c, c * c});
+  }
   return t;
 }
 
 std::vector<double> general_table(const TriRule &r) {
   const size_t n = r.s.size();
-  std::vector<double> t(7 * n);
+  std::vector<double> t(9 * n);
   for (size_t k = 0; k < n; ++k) {
-    const double s = r.s[k], e = r.t[k] - 0.5 * s;
-    const double row[7] = {s, r.t[k], r.w[k], e, s * s, s * e, e * e};
-    for (int f = 0; f < 7; ++f) t[f * n + k] = row[f];
+    const double s = r.s[k], e = r.t[k] - 0.5 * s, c = s - 2.0 / 3.0, d = r.t[k] - 1.0 / 3.0;
+    const double row[9] = {s, r.t[k], r.w[k], e, c, d, c * c, c * e, e * e};
+    for (int f = 0; f < 9; ++f) t[f * n + k] = row[f];
   }
   return t;
 }
