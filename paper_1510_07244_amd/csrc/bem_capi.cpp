@@ -116,7 +116,7 @@ int get_rules(bem_ctx *ctx, const bem_op *op, const bem::DevRules **out) {
     d.nq = (int)tr.s.size();
     const bool duffy = bem::rule_is_duffy(bem::rule_variant(op->regular_rule, op->q_regular, d.nq));
     const std::vector<double> t = duffy ? bem::duffy_table(op->q_regular) : bem::general_table(tr);
-    const std::vector<float> t32(t.begin(), t.end());
+    const std::vector<float> t32 = duffy ? bem::duffy_table32(op->q_regular) : bem::general_table32(tr);
     std::vector<double> f((t.size() + 1) / 2);
     std::memcpy(f.data(), t32.data(), t32.size() * sizeof(float));
     const size_t at_sums = put({&t}), at_sums32 = put({&f});

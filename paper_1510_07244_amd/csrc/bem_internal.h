@@ -30,6 +30,10 @@ std::vector<double> duffy_table(int q);
 // Constants of any other rule, with s' = s - 2/3 and t' = t - 1/3 from the
 // centroid: s, t, w, e = t - s / 2, s', t', s'^2, s' e, e^2 [9][points].
 std::vector<double> general_table(const TriRule &r);
+// The same in FP32, with weights whose sum is that of the exact ones to a
+// rounding of the last.
+std::vector<float> duffy_table32(int q);
+std::vector<float> general_table32(const TriRule &r);
 
 // Sauter-Schwab rule of one singular class, factored as (x^, y^) = xi g(eta):
 // per region and (eta1, eta2, eta3) Gauss triple the map g at xi = 1

@@ -115,6 +115,40 @@ std::vector<double> general_table(const TriRule &r) {
   return t;
 }
 
+// Weights rounded to FP32 one by one have a sum that is off by up to 4e-8 (the
+// seven-point rule by 3e-8, order 3 in products of two weights by 3.7e-8), a bias
+// of every entry as large as the rounding of its sum.  The rounding error of one
+// weight is carried to the next instead: mult(k) times weight k enters the sum.
+template <class At, class Mult>
+static void carry_weights(std::vector<float> &t, const std::vector<double> &exact, int n, At &&at, Mult &&mult) {
+  double carry = 0.0;
+  for (int k = 0; k < n; ++k) {
+    const double w = exact[at(k)], m = mult(k);
+    t[at(k)] = (float)(w + carry / m);
+    carry += m * (w - (double)t[at(k)]);
+  }
+}
+
+std::vector<float> duffy_table32(int q) {
+  const std::vector<double> d = duffy_table(q);
+  std::vector<float> t(d.begin(), d.end());
+  const int H = q / 2, HC = (q + 1) / 2;
+  const int W = 4 * q + 2 * H, WF = W + HC + H + q * H;  // DuffyAt
+  auto pair = [&](int k) { return k < H ? 2.0 : 1.0; };  // an eta pair's weight enters twice
+  carry_weights(t, d, q, [](int j) { return 4 * j + 2; }, [](int) { return 1.0; });
+  carry_weights(t, d, HC, [&](int k) { return W + k; }, pair);
+  carry_weights(t, d, q * HC, [&](int k) { return WF + k; }, [&](int k) { return pair(k % HC); });
+  return t;
+}
+
+std::vector<float> general_table32(const TriRule &r) {
+  const std::vector<double> d = general_table(r);
+  std::vector<float> t(d.begin(), d.end());
+  const int n = (int)r.s.size();
+  carry_weights(t, d, n, [&](int k) { return 2 * n + k; }, [](int) { return 1.0; });
+  return t;
+}
+
 // One point of a Sauter-Schwab region: returns (x^1, x^2, y^1, y^2) and the
 // Jacobian of the region map at (xi, h1, h2, h3) in [0,1]^4.  The maps send
 // [0,1]^4 onto a piece of {0 <= x2 <= x1 <= 1}^2 such that the pieces of one
