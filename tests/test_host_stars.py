@@ -5,7 +5,14 @@ import numpy as np
 import pytest
 
 from bem_inputs import octahedron_sphere
-from paper_1510_07244_amd.p1 import vertex_stars
+
+
+@pytest.fixture(scope="module")
+def vertex_stars():
+    # not while tests are collected: the library would be loaded ahead of torch,
+    # and with it another HIP runtime than torch's
+    from paper_1510_07244_amd.p1 import vertex_stars
+    return vertex_stars
 
 
 def _search(tri, vertices):
@@ -17,7 +24,7 @@ def _search(tri, vertices):
 
 @pytest.mark.parametrize("n,count", [(1, 6), (3, 1), (3, 0), (4, 40)])
 @pytest.mark.parametrize("columns", [3, 4])
-def test_stars(n, count, columns):
+def test_stars(vertex_stars, n, count, columns):
     m = octahedron_sphere(n)
     rng = np.random.default_rng(n)
     vertices = rng.permutation(m.v.shape[0])[:count]
@@ -27,7 +34,7 @@ def test_stars(n, count, columns):
         assert a.dtype == np.int32 and np.array_equal(a, b)
 
 
-def test_ids_from_the_end_are_refused():
+def test_ids_from_the_end_are_refused(vertex_stars):
     m = octahedron_sphere(3)
     last = int(m.tri.max())
     for bad in ([-1], [3, -2], [-1 - last]):
@@ -44,7 +51,7 @@ def test_ids_from_the_end_are_refused():
     assert np.array_equal(b[0], np.append(a[0], a[0][-1])) and all(np.array_equal(x, y) for x, y in zip(a[1:], b[1:]))
 
 
-def test_a_vertex_named_twice_keeps_its_last_place():
+def test_a_vertex_named_twice_keeps_its_last_place(vertex_stars):
     m = octahedron_sphere(3)
     ptr, t_ids, locs, tset = vertex_stars(m.tri, np.array([5, 5, 2]))
     one = vertex_stars(m.tri, np.array([5, 2]))
