@@ -22,6 +22,13 @@ by its reading of the pass's closing 512 MiB copy, counted FLOPs, issue
 counters -- beside the algorithmic bytes and flops and the durations of the
 same launches in a kernel trace of the bench; ends with the values bench.py
 reads for roofline.traffic and the hash of the sources they stay valid for.
+
+busy: how much of its launch each kernel keeps the vector units busy, from
+counter runs with SQ_ACTIVE_INST_VALU (quad-cycles, over the 1024 SIMDs) and
+GRBM_GUI_ACTIVE (cycles, summed over the 8 XCDs), one CSV per measured case:
+
+    python bench_profile.py busy --csv CASE=DIR/..._counter_collection.csv ... \
+        --cmd "COMMAND" --title "TITLE" > profiles/X.md
 """
 import argparse
 import collections
@@ -142,6 +149,26 @@ def _counter_rows(path):
     for (_, name, wg), v in sorted(per.items()):
         out.setdefault((name, wg), []).append(v)
     return out
+
+
+def cmd_busy(a):
+    out = [f"# {a.title}", "", "Command (repository root, MI355X, one GPU), NAME a case of `perf/cases.py`:", "",
+           "    " + a.cmd, "",
+           "Made by `bench_profile.py busy` from the runs' counter-collection CSVs; the last dispatch of",
+           "each launch.  VALU busy = 4 SQ_ACTIVE_INST_VALU / 1024 SIMDs / (GRBM_GUI_ACTIVE / 8 XCDs);",
+           "counters on, launches one at a time, so the durations are longer than the cases' own.", "",
+           "| Case | Kernel | Workgroups | Duration us | SQ_INSTS_VALU | SQ_WAVES | VALU busy |",
+           "|---|---|---|---|---|---|---|"]
+    for arg in a.csv:
+        case, path = arg.split("=", 1)
+        for (name, wg), runs in _counter_rows(path).items():
+            v = runs[-1]
+            if not name.startswith("k_") or "duration_ns" not in v or not v.get("GRBM_GUI_ACTIVE"):
+                continue
+            busy = 4 * v["SQ_ACTIVE_INST_VALU"] / 1024 / (v["GRBM_GUI_ACTIVE"] / 8)
+            out.append(f"| {case} | `{name}` | {wg} | {v['duration_ns'] / 1e3:.1f} | {v['SQ_INSTS_VALU']:.4g} | "
+                       f"{v['SQ_WAVES']:.4g} | {busy:.2f} |")
+    print("\n".join(out))
 
 
 def cmd_traffic(a):
@@ -272,6 +299,10 @@ def main():
     c.add_argument("--cmd", required=True)
     c.add_argument("--title", required=True)
     c.add_argument("--min-grid", type=int, default=0)
+    b = sub.add_parser("busy")
+    b.add_argument("--csv", nargs="+", required=True, help="CASE=counter-collection CSV")
+    b.add_argument("--cmd", required=True)
+    b.add_argument("--title", required=True)
     r = sub.add_parser("traffic")
     r.add_argument("--csv", nargs="+", required=True, help="counter-collection CSVs")
     r.add_argument("--cmd", nargs="+", required=True)
@@ -289,7 +320,7 @@ def main():
     r.add_argument("--sources", nargs="+", required=True)
     r.add_argument("--root", default=".")
     a = p.parse_args()
-    {"trace": cmd_trace, "counters": cmd_counters, "traffic": cmd_traffic}[a.what](a)
+    {"trace": cmd_trace, "counters": cmd_counters, "traffic": cmd_traffic, "busy": cmd_busy}[a.what](a)
 
 
 if __name__ == "__main__":

@@ -422,7 +422,7 @@ struct DuffyAt {
 // three terms are summed separately and combined per column point.
 // Per point pair (FP64 instructions, v_rsq_f64 as four): Laplace single, double,
 // both layers 12, 14, 16 -> 10.3, 12.8, 15.2; Helmholtz 46, 50, 55 -> 28, 34,
-// 43 with short phases.  Vector units 94 % busy (18432 triangles, Helmholtz
+// 43 with short phases.  Vector units 95 % busy (18432 triangles, Helmholtz
 // coupling): 38.6 -> 29.9 ms; Laplace coupling (8192, q = 4) 2.13 -> 1.82 ms,
 // one-pass near field 0.69 -> 0.59 ms, Helmholtz (32768, q = 5) 22.3 -> 17.8 ms.
 // FP64 and FP32 matrix instructions were no help: they do not overlap with the

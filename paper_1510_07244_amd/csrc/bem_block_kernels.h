@@ -3,8 +3,9 @@
 // is processed by one workgroup: regular pairs one entry per lane, the rest
 // (singular pairs; near-singular pairs in the mixed form) grouped by class in
 // LDS and done one pair per lane in FP64.
-//   k_blocks      one workgroup per block, looping over its sub-tiles (one
-//                 layer, or the single and the double layer in one pass);
+//   k_blocks      a block's sub-tiles dealt to gridDim.y workgroups, each
+//                 looping over its share (one layer, or the single and the
+//                 double layer in one pass);
 //   k_persistent  a fixed grid of workgroups popping sub-tiles of many
 //                 blocks (of many meshes) from a cost-sorted global queue.
 // Both call the same sub-tile code, so their results are bitwise equal.

@@ -8,7 +8,7 @@
 
 namespace bem {
 
-// one workgroup per block; layer: BEM_SLP, BEM_DLP or 2 (both)
+// a.nb x a.split workgroups; layer: BEM_SLP, BEM_DLP or 2 (both)
 template <int KERNEL, bool MIXED>
 struct BlockLaunch {
   static hipError_t blocks(int layer, int rule, bool coupling, const BlockArgs &a, size_t lds,

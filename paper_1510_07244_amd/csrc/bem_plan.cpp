@@ -79,10 +79,9 @@ hipError_t d2h(std::vector<T> *dst, const T *src, int64_t n) {
 
 // Estimated cost of one sub-tile in regular point-pair units of the single
 // layer: regular entries use nqp^2 point pairs; a pair with k common
-// vertices has 2, 5 or 6 regions of q_s^3 eta points (k = 1, 2, 3), each
-// about twice a regular point pair's work and summed one pair per lane:
-// 8 k q_s^3 (measured on the near field of the 8192-triangle sphere, the
-// singular pass takes about 1/6 of the launch for 1/40 of its flops).  The
+// vertices counts 8 k q_s^3, for its lane alone in a chunk of one class (the
+// near field of the 8192-triangle sphere when the rule was summed point by
+// point: about 1/6 of the launch for 1/40 of its flops).  The
 // other layers scale the regular part by their issue slots per point pair
 // over the single layer's (Laplace 10.3 : 12.8 : 15.2 for single, double, both
 // in one pass; Helmholtz, with the sine and cosine, about 28 : 34 : 43) and the
